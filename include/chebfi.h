@@ -479,8 +479,8 @@ abi_status abi_apply_H_noalloc(abi_system sys, const void *X, void *HX, int64_t 
  *                      direct-to-LDS 128 x 128 tile (default)
  *   ABI_TUNE_FFT_BATCH bands per FFT batch (1..4096)
  *   ABI_TUNE_OVERLAP   0/1: FFT passes on a second stream beside the projection
- *   ABI_TUNE_GENERIC_FFT 0/1: runtime-size FFT passes also for cubic boxes that
- *                      have compile-time specialised ones (for testing them)
+ *   ABI_TUNE_GENERIC_FFT 0/1: runtime-size FFT passes also for boxes that have
+ *                      compile-time specialised ones (for testing them)
  *   ABI_TUNE_MIXED_GEMM form of the mixed projector products: 0 split-BF16
  *                      (default), 1 FP32 MFMA, 2 split-BF16 single-buffered
  *                      64 x 64 tile (comparison forms)

@@ -622,12 +622,8 @@ abi_status abi_set_system(const abi_system_desc *desc, void *stream, abi_system 
       }
       plane[s->n3] = (int32_t)s->npw;
     }
-    s->zocc = ~0ull;
-    if (s->n3 <= 64) {
-      s->zocc = 0;
-      for (int i3 = 0; i3 < s->n3; ++i3)
-        if (plane[i3] < plane[i3 + 1]) s->zocc |= 1ull << i3;
-    }
+    for (int i3 = 0; i3 < s->n3; ++i3)
+      if (plane[i3] < plane[i3 + 1]) (i3 < 64 ? s->zocc : s->zocc_hi) |= 1ull << (i3 & 63);
     std::vector<double> tw(3 * kMaxN * 2, 0.0);
     for (int c = 0; c < 3; ++c) {
       const int n = desc->ngrid[c];

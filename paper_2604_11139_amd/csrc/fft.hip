@@ -298,147 +298,148 @@ __global__ __launch_bounds__(256) void rho_accum_kernel(int64_t nbox, int nb, in
   rho[r] += scale * acc;
 }
 
-// ---- compile-time specialised passes for cubic boxes (building blocks in fft_dev.h) ----
+// ---- compile-time specialised passes (building blocks in fft_dev.h) --------------------
+// Passes A and C for square planes of a listed edge N (any n3), the z passes for
+// a listed n3 (any plane): one workgroup holds one plane, or kZRow bytes' worth of
+// neighbouring z pencils.  All are bound by their HBM bytes when the waves in
+// flight cover the latency; see cthreads for the thread count.
 
 template <typename T, int N>
-__global__ __launch_bounds__(kCT) void cpass_a_kernel(const C2<T> *__restrict__ X, int64_t ldx,
-                                                      int band0, const int32_t *__restrict__ box_index,
-                                                      const int32_t *__restrict__ plane,
-                                                      const double2 *__restrict__ twg,
-                                                      C2<T> *__restrict__ box) {
-  constexpr int NXY = N * N, LD = cld<N>();
+__global__ __launch_bounds__((cthreads<N, N>())) void cpass_a_kernel(
+    const C2<T> *__restrict__ X, int64_t ldx, int band0, const int32_t *__restrict__ box_index,
+    const int32_t *__restrict__ plane, const double2 *__restrict__ twg, C2<T> *__restrict__ box) {
+  constexpr int NXY = N * N, LD = cld<N>(), CT = cthreads<N, N>();
   __shared__ C2<T> buf[N * LD];
   __shared__ C2<T> tw[N];
   const int i3 = blockIdx.x;
   const int bl = blockIdx.y;
-  // a plane with no sphere points is left unwritten: the middle passes read it as zero
-  if (plane[i3] == plane[i3 + 1]) return;
-  for (int i = threadIdx.x; i < N; i += kCT) tw[i] = to_c2<T>(twg[i]);
-  for (int i = threadIdx.x; i < N * LD; i += kCT) buf[i] = C2<T>{0, 0};
-  __syncthreads();
   const int s0 = plane[i3], s1 = plane[i3 + 1];
+  // a plane with no sphere points is left unwritten: the middle passes read it as zero
+  if (s0 == s1) return;
   const C2<T> *xb = X + (int64_t)(band0 + bl) * ldx;
   const int off = i3 * NXY;
-  for (int idx = s0 + threadIdx.x; idx < s1; idx += kCT) {
+  // the plane's sphere rows (a disk: at most pi/4 of it when the sphere fits the
+  // box) are fetched before the plane is cleared, all in flight together
+  constexpr int FULL = (NXY * 4 / 5 + CT - 1) / CT, U = FULL < 6 ? FULL : 6;
+  T xr[U], xi[U];
+  int xe[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int idx = min(s0 + (int)threadIdx.x + u * CT, s1 - 1);
+    const C2<T> v = xb[idx];
+    xr[u] = v.x;
+    xi[u] = v.y;
+    xe[u] = box_index[idx] - off;
+  }
+  for (int i = threadIdx.x; i < N; i += CT) tw[i] = to_c2<T>(twg[i]);
+  for (int i = threadIdx.x; i < N * LD; i += CT) buf[i] = C2<T>{0, 0};
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (s0 + (int)threadIdx.x + u * CT < s1)
+      buf[(xe[u] / N) * LD + xe[u] % N] = C2<T>{xr[u], xi[u]};
+  for (int idx = s0 + threadIdx.x + U * CT; idx < s1; idx += CT) {
     const int e = box_index[idx] - off;
     buf[(e / N) * LD + e % N] = xb[idx];
   }
   __syncthreads();
-  cfft<T, N, 0, 1, N, 1, LD, +1>(buf, tw);  // x: N pencils of stride-1 elements
+  cfft<T, N, 0, 1, N, 1, LD, +1, 1, 0, CT>(buf, tw);  // x: N pencils of stride-1 elements
   // y: pencil i1, element i2; the last stage writes the box plane
-  C2<T> *dst = box + (int64_t)bl * NXY * N + off;
+  C2<T> *dst = box + (int64_t)bl * NXY * gridDim.x + off;
   auto ldm = [&](int pa, int e) { return buf[pa + e * LD]; };
   auto stm = [&](int pa, int e, C2<T> v) { buf[pa + e * LD] = v; };
   auto stg = [&](int pa, int e, C2<T> v) { dst[pa + e * N] = v; };
-  cfft_io<T, N, 0, 1, N, +1, true, false>(tw, ldm, stg, ldm, stm);
+  cfft_io<T, N, 0, 1, N, +1, true, false, CT>(tw, ldm, stg, ldm, stm);
 }
 
-template <typename T, typename VT, int N>
-__global__ __launch_bounds__(kCT) void cpass_b_kernel(C2<T> *__restrict__ box,
-                                                      const VT *__restrict__ V,
-                                                      const double2 *__restrict__ twg,
-                                                      uint64_t zocc) {
-  constexpr int LD = cld<N>();
-  __shared__ C2<T> buf[N * LD];
+// Reciprocal z-planes that hold sphere points, one bit each.
+struct ZOcc {
+  uint64_t lo, hi;
+};
+
+// z pencils per workgroup: 512 bytes of neighbouring pencils (64 complex64, 32
+// complex128), so that every element row of a load or store is a whole run of
+// 512 contiguous bytes whatever the plane's edges are (the pencils of a box are
+// numbered i1 + n1 i2: a slab of one i2 would give rows of n1 elements, 288
+// bytes and 216 of 512 threads busy at 36), and an LDS row is one bank sweep.
+template <typename T> constexpr int zpencils() { return 512 / (int)sizeof(C2<T>); }
+
+// Work of a z pass: the filter's pass B (inverse z transform, times V, forward
+// transform), the inverse transform alone (density, adjoint's forward bands), or
+// the adjoint's pass B (also Re[conj(adjoint) * forward] over the forward band).
+enum { Z_FILTER = 0, Z_INVERSE = 1, Z_ADJOINT = 2 };
+
+template <typename T, int N, int MODE>
+__global__ __launch_bounds__((cthreads<N, zpencils<T>()>())) void zpass_kernel(
+    C2<T> *__restrict__ box, C2<T> *__restrict__ fwd, const T *__restrict__ V, int nxy,
+    const double2 *__restrict__ twg, ZOcc zocc) {
+  constexpr int Q = zpencils<T>(), CT = cthreads<N, Q>();
+  __shared__ C2<T> buf[N * Q];
   __shared__ C2<T> tw[N];
-  const int i2 = blockIdx.x;
-  const int bl = blockIdx.y;
-  for (int i = threadIdx.x; i < N; i += kCT) tw[i] = to_c2<T>(twg[2 * kMaxN + i]);
+  const int q0 = blockIdx.x * Q;
+  const int left = nxy - q0;  // pencils of this workgroup: the last one may be short
+  for (int i = threadIdx.x; i < N; i += CT) tw[i] = to_c2<T>(twg[2 * kMaxN + i]);
   __syncthreads();
-  // z transforms of the slab (pencil i1, element i3): the first stage reads the
-  // box, the forward transform's last stage applies V, the inverse's last
-  // stage writes the box
-  C2<T> *src = box + (int64_t)bl * N * N * N + (int64_t)N * i2;
-  const VT *v = V + (int64_t)N * i2;
-  constexpr int64_t ZS = (int64_t)N * N;
-  auto ldm = [&](int pa, int e) { return buf[pa + e * LD]; };
-  auto stm = [&](int pa, int e, C2<T> x) { buf[pa + e * LD] = x; };
+  const int64_t o = (int64_t)blockIdx.y * nxy * N + q0;
+  C2<T> *src = box + o;
+  const T *v = V + q0;
+  auto ldm = [&](int pa, int e) { return buf[pa + e * Q]; };
+  auto stm = [&](int pa, int e, C2<T> x) { buf[pa + e * Q] = x; };
   // reciprocal planes g3 without sphere points: zero in (pass A leaves them
   // unwritten), not written out (pass C does not read them)
-  auto occ = [&](int e) { return ((zocc >> e) & 1ull) != 0; };
-  auto ldg = [&](int pa, int e) { return occ(e) ? src[pa + e * ZS] : C2<T>{0, 0}; };
-  auto stg = [&](int pa, int e, C2<T> x) {
-    if (occ(e)) src[pa + e * ZS] = x;
-  };
-  auto stv = [&](int pa, int e, C2<T> x) { buf[pa + e * LD] = cscale(x, (T)v[pa + e * ZS]); };
-  cfft_io<T, N, 0, 1, N, +1, false, true>(tw, ldg, stv, ldm, stm);
-  cfft_io<T, N, 0, 1, N, -1, true, false>(tw, ldm, stg, ldm, stm);
-}
-
-// z-inverse FFT only (the box then holds the bands in real space).
-template <typename T, int N>
-__global__ __launch_bounds__(kCT) void cpass_b_inv_kernel(C2<T> *__restrict__ box,
-                                                          const double2 *__restrict__ twg,
-                                                          uint64_t zocc) {
-  constexpr int LD = cld<N>();
-  __shared__ C2<T> buf[N * LD];
-  __shared__ C2<T> tw[N];
-  const int i2 = blockIdx.x;
-  const int bl = blockIdx.y;
-  for (int i = threadIdx.x; i < N; i += kCT) tw[i] = to_c2<T>(twg[2 * kMaxN + i]);
-  __syncthreads();
-  C2<T> *src = box + (int64_t)bl * N * N * N + (int64_t)N * i2;
-  constexpr int64_t ZS = (int64_t)N * N;
-  auto ldm = [&](int pa, int e) { return buf[pa + e * LD]; };
-  auto stm = [&](int pa, int e, C2<T> x) { buf[pa + e * LD] = x; };
-  // input planes g3 without sphere points are zero; the output is real space (all z)
+  auto occ = [&](int e) { return (((N > 64 && e >= 64 ? zocc.hi : zocc.lo) >> (e & 63)) & 1) != 0; };
+  // (every load is issued: a pencil past the end reads the last one, an empty
+  // plane's element plane 0's, which the workgroup reads anyway; a branch around
+  // each load kept them from overlapping, 48 against 40 us per 64 64^3 complex64
+  // boxes)
   auto ldg = [&](int pa, int e) {
-    return ((zocc >> e) & 1ull) ? src[pa + e * ZS] : C2<T>{0, 0};
+    const bool in = occ(e);
+    const C2<T> x = src[min(pa, left - 1) + (in ? e * nxy : 0)];
+    return in ? x : C2<T>{0, 0};
   };
-  auto stg = [&](int pa, int e, C2<T> x) { src[pa + e * ZS] = x; };
-  cfft_io<T, N, 0, 1, N, +1, false, false>(tw, ldg, stg, ldm, stm);
+  if constexpr (MODE == Z_INVERSE) {  // real space out: all planes
+    auto stg = [&](int pa, int e, C2<T> x) {
+      if (pa < left) src[pa + e * nxy] = x;
+    };
+    cfft_io<T, N, 0, 1, Q, +1, false, false, CT>(tw, ldg, stg, ldm, stm);
+  } else {
+    C2<T> *fw = fwd + o;
+    // V (and the forward band) fetched ahead of the stage that multiplies by it
+    struct Pre {
+      T v;
+      C2<T> y;
+    };
+    auto pre = [&](int pa, int e) {
+      const int r = min(pa, left - 1) + e * nxy;
+      Pre p{v[r], C2<T>{0, 0}};
+      if constexpr (MODE == Z_ADJOINT) p.y = fw[r];
+      return p;
+    };
+    auto stv = [&](int pa, int e, C2<T> x, const Pre &p) {
+      if constexpr (MODE == Z_ADJOINT)
+        if (pa < left) fw[pa + e * nxy] = C2<T>{x.x * p.y.x + x.y * p.y.y, (T)0};
+      buf[pa + e * Q] = cscale(x, p.v);
+    };
+    auto stg = [&](int pa, int e, C2<T> x) {
+      if (pa < left && occ(e)) src[pa + e * nxy] = x;
+    };
+    cfft_io<T, N, 0, 1, Q, +1, false, true, CT>(tw, ldg, stv, ldm, stm, pre);
+    cfft_io<T, N, 0, 1, Q, -1, true, false, CT>(tw, ldm, stg, ldm, stm);
+  }
 }
 
-// Adjoint pass B: z-inverse of the adjoint band, Re[conj(adjoint) * forward]
-// written over the forward band's real-space box (real part), then * V and the
-// z-forward FFT of the adjoint band.
-template <typename T, typename VT, int N>
-__global__ __launch_bounds__(kCT) void cpass_b_adj_kernel(C2<T> *__restrict__ box,
-                                                          C2<T> *__restrict__ fwd,
-                                                          const VT *__restrict__ V,
-                                                          const double2 *__restrict__ twg,
-                                                          uint64_t zocc) {
-  constexpr int LD = cld<N>();
-  __shared__ C2<T> buf[N * LD];
-  __shared__ C2<T> tw[N];
-  const int i2 = blockIdx.x;
-  const int bl = blockIdx.y;
-  for (int i = threadIdx.x; i < N; i += kCT) tw[i] = to_c2<T>(twg[2 * kMaxN + i]);
-  __syncthreads();
-  const int64_t o = (int64_t)bl * N * N * N + (int64_t)N * i2;
-  C2<T> *src = box + o;
-  C2<T> *fw = fwd + o;
-  const VT *v = V + (int64_t)N * i2;
-  constexpr int64_t ZS = (int64_t)N * N;
-  auto ldm = [&](int pa, int e) { return buf[pa + e * LD]; };
-  auto stm = [&](int pa, int e, C2<T> x) { buf[pa + e * LD] = x; };
-  // the adjoint band's planes g3 without sphere points: zero in, not written
-  // out; the forward band's box is real space (all z)
-  auto occ = [&](int e) { return ((zocc >> e) & 1ull) != 0; };
-  auto ldg = [&](int pa, int e) { return occ(e) ? src[pa + e * ZS] : C2<T>{0, 0}; };
-  auto stg = [&](int pa, int e, C2<T> x) {
-    if (occ(e)) src[pa + e * ZS] = x;
-  };
-  // the z-inverse's last stage: Re[conj(a) y] over the forward box, a V into LDS
-  auto stv = [&](int pa, int e, C2<T> a) {
-    const int64_t r = pa + e * ZS;
-    const C2<T> y = fw[r];
-    fw[r] = C2<T>{a.x * y.x + a.y * y.y, (T)0};
-    buf[pa + e * LD] = cscale(a, (T)v[r]);
-  };
-  cfft_io<T, N, 0, 1, N, +1, false, true>(tw, ldg, stv, ldm, stm);
-  cfft_io<T, N, 0, 1, N, -1, true, false>(tw, ldm, stg, ldm, stm);
-}
-
+// (Gathering two or three rows per thread at once, all their loads in flight
+// together, made this pass slower: 53.5 -> 59.5 us for 256 36^3 complex64 bands,
+// 68.6 -> 76.6 us for 64 64^3 ones.)
 template <typename T, int N>
-__global__ __launch_bounds__(kCT) void cpass_c_kernel(
+__global__ __launch_bounds__((cthreads<N, N>())) void cpass_c_kernel(
     const C2<T> *__restrict__ box, const double2 *__restrict__ twg,
     const int32_t *__restrict__ box_index, const int32_t *__restrict__ plane,
     const double *__restrict__ kin, int band0, const C2<T> *__restrict__ Yk, int64_t ldk,
     const C2<T> *__restrict__ Yprev, int64_t ldp, C2<T> *__restrict__ Out, int64_t ldo, T alpha,
     T cshift, T beta, T scale, const C2<T> *__restrict__ E, int64_t lde,
     const double *__restrict__ coef, PlanesOut po) {
-  constexpr int NXY = N * N, LD = cld<N>();
+  constexpr int NXY = N * N, LD = cld<N>(), CT = cthreads<N, N>();
   __shared__ C2<T> buf[N * LD];
   __shared__ C2<T> tw[N];
   if (coef) {  // (alpha, cshift, beta) of this step from device memory (captured filters)
@@ -448,26 +449,26 @@ __global__ __launch_bounds__(kCT) void cpass_c_kernel(
   }
   const int i3 = blockIdx.x;
   const int bl = blockIdx.y;
-  if (plane[i3] == plane[i3 + 1]) return;  // no sphere points to gather in this plane
-  for (int i = threadIdx.x; i < N; i += kCT) tw[i] = to_c2<T>(twg[i]);
+  const int s0 = plane[i3], s1 = plane[i3 + 1];
+  if (s0 == s1) return;  // no sphere points to gather in this plane
+  for (int i = threadIdx.x; i < N; i += CT) tw[i] = to_c2<T>(twg[i]);
   __syncthreads();
   const int off = i3 * NXY;
-  const C2<T> *src = box + (int64_t)bl * NXY * N + off;
+  const C2<T> *src = box + (int64_t)bl * NXY * gridDim.x + off;
   {  // y: pencil i1, element i2; the first stage reads the box plane
     auto ldm = [&](int pa, int e) { return buf[pa + e * LD]; };
     auto stm = [&](int pa, int e, C2<T> v) { buf[pa + e * LD] = v; };
     auto ldg = [&](int pa, int e) { return src[pa + e * N]; };
-    cfft_io<T, N, 0, 1, N, -1, false, true>(tw, ldg, stm, ldm, stm);
+    cfft_io<T, N, 0, 1, N, -1, false, true, CT>(tw, ldg, stm, ldm, stm);
   }
-  cfft<T, N, 0, 1, N, 1, LD, -1>(buf, tw);
-  const int s0 = plane[i3], s1 = plane[i3 + 1];
+  cfft<T, N, 0, 1, N, 1, LD, -1, 1, 0, CT>(buf, tw);
   const int64_t b = band0 + bl;
   const C2<T> *yk = Yk + b * ldk;
   C2<T> *out = Out + b * ldo;
   const C2<T> *ex = E ? E + b * lde : nullptr;
   if (Yprev != nullptr) {
     const C2<T> *yp = Yprev + b * ldp;
-    sphere_store<T>(s0, s1, kCT, po, b, out, [&](int idx) {
+    sphere_store<T>(s0, s1, CT, po, b, out, [&](int idx) {
       const int e = box_index[idx] - off;
       const C2<T> loc = cscale(buf[(e / N) * LD + e % N], scale);
       const C2<T> x = yk[idx];
@@ -479,7 +480,7 @@ __global__ __launch_bounds__(kCT) void cpass_c_kernel(
       return o;
     });
   } else {
-    sphere_store<T>(s0, s1, kCT, po, b, out, [&](int idx) {
+    sphere_store<T>(s0, s1, CT, po, b, out, [&](int idx) {
       const int e = box_index[idx] - off;
       const C2<T> loc = cscale(buf[(e / N) * LD + e % N], scale);
       const C2<T> x = yk[idx];
@@ -491,162 +492,139 @@ __global__ __launch_bounds__(kCT) void cpass_c_kernel(
   }
 }
 
-template <typename T, int N>
-void launch_cubic(const abi_system_s *s, const void *Yk, int64_t ldk, const void *Yprev,
-                  int64_t ldp, void *Out, int64_t ldo, int band0, int nb, void *box, const void *V,
-                  double alpha, double cshift, double beta, hipStream_t st, Profiler *prof,
-                  double bytesA, double bytesB, double bytesC, const void *E, int64_t lde,
-                  PlanesOut po) {
-  typedef C2<T> V2;
-  typedef typename std::conditional<std::is_same<T, double>::value, double, float>::type VT;
-  const double2 *tw = reinterpret_cast<const double2 *>(s->d_tw);
-  V2 *bx = reinterpret_cast<V2 *>(box);
-  int tok = prof ? prof->begin(PROF_FFT_A, bytesA, st) : -1;
-  hipLaunchKernelGGL((cpass_a_kernel<T, N>), dim3(N, nb), dim3(kCT), 0, st,
-                     reinterpret_cast<const V2 *>(Yk), ldk, band0, s->d_box, s->d_plane, tw, bx);
-  CHEBFI_HIP(hipGetLastError());
-  if (prof) prof->end(tok, st);
-  tok = prof ? prof->begin(PROF_FFT_B, bytesB, st) : -1;
-  hipLaunchKernelGGL((cpass_b_kernel<T, VT, N>), dim3(N, nb), dim3(kCT), 0, st, bx,
-                     reinterpret_cast<const VT *>(V), tw, s->zocc);
-  CHEBFI_HIP(hipGetLastError());
-  if (prof) prof->end(tok, st);
-  tok = prof ? prof->begin(PROF_FFT_C, bytesC, st) : -1;
-  const T scale = (T)(1.0 / ((double)N * N * N));
-  hipLaunchKernelGGL((cpass_c_kernel<T, N>), dim3(N, nb), dim3(kCT), 0, st, bx, tw, s->d_box,
-                     s->d_plane, s->d_kin, band0, reinterpret_cast<const V2 *>(Yk), ldk,
-                     reinterpret_cast<const V2 *>(Yprev), ldp, reinterpret_cast<V2 *>(Out), ldo,
-                     (T)alpha, (T)cshift, (T)beta, scale, reinterpret_cast<const V2 *>(E), lde,
-                     s->coef_dev, po);
-  CHEBFI_HIP(hipGetLastError());
-  if (prof) prof->end(tok, st);
-}
+// Edges with compile-time transforms.
+#define CHEBFI_EDGES(X)                                                                         \
+  X(12) X(15) X(16) X(18) X(20) X(24) X(25) X(27) X(30) X(32) X(36) X(40) X(45) X(48) X(50) \
+  X(54) X(60) X(64) X(72) X(75) X(80) X(81) X(90) X(96)
 
-template <typename T, int N>
-void adjoint_cubic(const abi_system_s *s, const void *Ak1, int64_t lda1, const void *Yk,
-                   int64_t ldy, void *Ak, int64_t ldak, bool accumulate, int band0, int nb,
-                   void *box1, void *box2, const void *V, double gamma, double cshift, double *dV,
-                   hipStream_t st) {
-  typedef C2<T> V2;
-  typedef typename std::conditional<std::is_same<T, double>::value, double, float>::type VT;
-  const double2 *tw = reinterpret_cast<const double2 *>(s->d_tw);
-  V2 *b1 = reinterpret_cast<V2 *>(box1);
-  V2 *b2 = reinterpret_cast<V2 *>(box2);
-  hipLaunchKernelGGL((cpass_a_kernel<T, N>), dim3(N, nb), dim3(kCT), 0, st,
-                     reinterpret_cast<const V2 *>(Ak1), lda1, band0, s->d_box, s->d_plane, tw, b1);
-  hipLaunchKernelGGL((cpass_a_kernel<T, N>), dim3(N, nb), dim3(kCT), 0, st,
-                     reinterpret_cast<const V2 *>(Yk), ldy, band0, s->d_box, s->d_plane, tw, b2);
-  hipLaunchKernelGGL((cpass_b_inv_kernel<T, N>), dim3(N, nb), dim3(kCT), 0, st, b2, tw,
-                     s->zocc);
-  hipLaunchKernelGGL((cpass_b_adj_kernel<T, VT, N>), dim3(N, nb), dim3(kCT), 0, st, b1, b2,
-                     reinterpret_cast<const VT *>(V), tw, s->zocc);
-  const int64_t nbox = (int64_t)N * N * N;
-  hipLaunchKernelGGL(dv_reduce_kernel<T>, dim3((unsigned)((nbox + 255) / 256)), dim3(256), 0, st,
-                     nbox, nb, (const V2 *)b2, gamma / (double)nbox, dV);
-  const T scale = (T)(1.0 / (double)nbox);
-  hipLaunchKernelGGL((cpass_c_kernel<T, N>), dim3(N, nb), dim3(kCT), 0, st, b1, tw, s->d_box,
-                     s->d_plane, s->d_kin, band0, reinterpret_cast<const V2 *>(Ak1), lda1,
-                     accumulate ? reinterpret_cast<const V2 *>(Ak) : (const V2 *)nullptr, ldak,
-                     reinterpret_cast<V2 *>(Ak), ldak, (T)gamma, (T)cshift, (T)-1, scale,
-                     (const V2 *)nullptr, (int64_t)0, (const double *)nullptr,
-                     PlanesOut{nullptr, 0, 0});
-  CHEBFI_HIP(hipGetLastError());
-}
-
-template <typename T, int N>
-void density_cubic(const abi_system_s *s, const void *Psi, int64_t ld, int band0, int nb,
-                   void *box, const double *w, double *rho, hipStream_t st) {
-  typedef C2<T> V2;
-  const double2 *tw = reinterpret_cast<const double2 *>(s->d_tw);
-  V2 *bx = reinterpret_cast<V2 *>(box);
-  hipLaunchKernelGGL((cpass_a_kernel<T, N>), dim3(N, nb), dim3(kCT), 0, st,
-                     reinterpret_cast<const V2 *>(Psi), ld, band0, s->d_box, s->d_plane, tw, bx);
-  hipLaunchKernelGGL((cpass_b_inv_kernel<T, N>), dim3(N, nb), dim3(kCT), 0, st, bx, tw,
-                     s->zocc);
-  const int64_t nbox = (int64_t)N * N * N;
-  hipLaunchKernelGGL(rho_accum_kernel<T>, dim3((unsigned)((nbox + 255) / 256)), dim3(256), 0, st,
-                     nbox, nb, band0, (const V2 *)bx, w, 1.0 / (double)nbox, rho);
-  CHEBFI_HIP(hipGetLastError());
-}
-
-// Edges with compile-time specialised passes (cubic boxes).
-#define CHEBFI_CUBIC_SIZES(X) \
-  X(12) X(15) X(16) X(18) X(20) X(24) X(25) X(27) X(30) X(32) X(36) X(40) X(45) X(48) X(64)
-
-template <typename T>
-bool try_cubic_adjoint(const abi_system_s *s, const void *Ak1, int64_t lda1, const void *Yk,
-                       int64_t ldy, void *Ak, int64_t ldak, bool accumulate, int band0, int nb,
-                       void *box1, void *box2, const void *V, double gamma, double cshift,
-                       double *dV, hipStream_t st) {
-  if (s->n1 != s->n2 || s->n1 != s->n3) return false;
-  if (s->generic_fft) return false;
-#define CHEBFI_CASE(N_)                                                                      \
-  case N_:                                                                                   \
-    adjoint_cubic<T, N_>(s, Ak1, lda1, Yk, ldy, Ak, ldak, accumulate, band0, nb, box1, box2, \
-                         V, gamma, cshift, dV, st);                                          \
+bool listed_edge(int n) {
+#define CHEBFI_CASE(N_) case N_:
+  switch (n) {
+    CHEBFI_EDGES(CHEBFI_CASE)
     return true;
-  switch (s->n1) {
-    CHEBFI_CUBIC_SIZES(CHEBFI_CASE)
     default:
       return false;
   }
 #undef CHEBFI_CASE
-}
-
-template <typename T>
-bool try_cubic_density(const abi_system_s *s, const void *Psi, int64_t ld, int band0, int nb,
-                       void *box, const double *w, double *rho, hipStream_t st) {
-  if (s->n1 != s->n2 || s->n1 != s->n3) return false;
-  if (s->generic_fft) return false;
-#define CHEBFI_CASE(N_)                                                       \
-  case N_:                                                                    \
-    density_cubic<T, N_>(s, Psi, ld, band0, nb, box, w, rho, st);             \
-    return true;
-  switch (s->n1) {
-    CHEBFI_CUBIC_SIZES(CHEBFI_CASE)
-    default:
-      return false;
-  }
-#undef CHEBFI_CASE
-}
-
-template <typename T>
-bool try_cubic(const abi_system_s *s, const void *Yk, int64_t ldk, const void *Yprev, int64_t ldp,
-               void *Out, int64_t ldo, int band0, int nb, void *box, const void *V, double alpha,
-               double cshift, double beta, hipStream_t st, Profiler *prof, double bA, double bB,
-               double bC, const void *E, int64_t lde, PlanesOut po) {
-  if (s->n1 != s->n2 || s->n1 != s->n3) return false;
-  if (s->generic_fft) return false;
-#define CHEBFI_CUBIC(N_)                                                                     \
-  case N_:                                                                                   \
-    launch_cubic<T, N_>(s, Yk, ldk, Yprev, ldp, Out, ldo, band0, nb, box, V, alpha, cshift,  \
-                        beta, st, prof, bA, bB, bC, E, lde, po);                             \
-    return true;
-  switch (s->n1) {
-    CHEBFI_CUBIC(12)
-    CHEBFI_CUBIC(15)
-    CHEBFI_CUBIC(16)
-    CHEBFI_CUBIC(18)
-    CHEBFI_CUBIC(20)
-    CHEBFI_CUBIC(24)
-    CHEBFI_CUBIC(25)
-    CHEBFI_CUBIC(27)
-    CHEBFI_CUBIC(30)
-    CHEBFI_CUBIC(32)
-    CHEBFI_CUBIC(36)
-    CHEBFI_CUBIC(40)
-    CHEBFI_CUBIC(45)
-    CHEBFI_CUBIC(48)
-    CHEBFI_CUBIC(64)
-    default:
-      return false;
-  }
-#undef CHEBFI_CUBIC
 }
 
 template <typename F> void set_lds(F kernel, size_t bytes) {
   CHEBFI_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+}
+
+// Which passes of a handle are compile-time specialised: the z passes for a
+// listed n3, passes A and C for square planes of a listed edge when the z passes
+// are too (they leave planes without sphere points unwritten, which only the
+// specialised z passes know); the runtime-size ones otherwise.
+bool special_z(const abi_system_s *s) { return !s->generic_fft && listed_edge(s->n3); }
+bool special_planes(const abi_system_s *s) {
+  return special_z(s) && s->n1 == s->n2 && listed_edge(s->n1);
+}
+
+// Thread counts and LDS bytes of the runtime-size passes.
+template <typename T> struct RuntimeShape {
+  int tA, tB;
+  size_t ldsA, ldsB;
+  explicit RuntimeShape(const BoxPlan &plan) {
+    const int n1 = plan.d[0].n, n2 = plan.d[1].n, n3 = plan.d[2].n;
+    tA = std::max(stage_threads(plan.d[0], n2), stage_threads(plan.d[1], n1));
+    tB = stage_threads(plan.d[2], n1);
+    CHEBFI_REQUIRE(tA <= 512 && tB <= 512, ABI_ERR_GRID, "FFT plane too large for one workgroup");
+    ldsA = sizeof(C2<T>) * (size_t)(n2 * (n1 + 1) + n1 + n2);
+    ldsB = sizeof(C2<T>) * (size_t)(n3 * (n1 + 1) + n3);
+  }
+};
+
+// Pass A of bands band0 .. band0 + nb - 1 of X into `box`.
+template <typename T>
+void launch_a(const abi_system_s *s, const void *X, int64_t ldx, int band0, int nb, void *box,
+              hipStream_t st) {
+  const C2<T> *x = reinterpret_cast<const C2<T> *>(X);
+  C2<T> *bx = reinterpret_cast<C2<T> *>(box);
+  const double2 *tw = reinterpret_cast<const double2 *>(s->d_tw);
+  const dim3 grid(s->n3, nb);
+  if (special_planes(s)) {
+#define CHEBFI_CASE(N_)                                                                       \
+  case N_:                                                                                    \
+    hipLaunchKernelGGL((cpass_a_kernel<T, N_>), grid, dim3(cthreads<N_, N_>()), 0, st, x, ldx, \
+                       band0, s->d_box, s->d_plane, tw, bx);                                  \
+    break;
+    switch (s->n1) { CHEBFI_EDGES(CHEBFI_CASE) }
+#undef CHEBFI_CASE
+  } else {
+    const RuntimeShape<T> r(s->plan);
+    set_lds(pass_a_kernel<T>, r.ldsA);
+    hipLaunchKernelGGL(pass_a_kernel<T>, grid, dim3(r.tA), r.ldsA, st, x, ldx, band0, s->d_box,
+                       s->d_plane, s->plan, tw, bx);
+  }
+  CHEBFI_HIP(hipGetLastError());
+}
+
+// z pass of nb boxes (`fwd`: the forward bands' boxes, Z_ADJOINT only).
+template <typename T, int MODE>
+void launch_z(const abi_system_s *s, void *box, void *fwd, const void *V, int nb, hipStream_t st) {
+  C2<T> *bx = reinterpret_cast<C2<T> *>(box), *fw = reinterpret_cast<C2<T> *>(fwd);
+  const T *v = reinterpret_cast<const T *>(V);
+  const double2 *tw = reinterpret_cast<const double2 *>(s->d_tw);
+  if (special_z(s)) {
+    constexpr int Q = zpencils<T>();
+    const int nxy = s->n1 * s->n2;
+    const dim3 grid((nxy + Q - 1) / Q, nb);
+    const ZOcc occ{s->zocc, s->zocc_hi};
+#define CHEBFI_CASE(N_)                                                                           \
+  case N_:                                                                                        \
+    hipLaunchKernelGGL((zpass_kernel<T, N_, MODE>), grid, dim3(cthreads<N_, Q>()), 0, st, bx, fw, \
+                       v, nxy, tw, occ);                                                          \
+    break;
+    switch (s->n3) { CHEBFI_EDGES(CHEBFI_CASE) }
+#undef CHEBFI_CASE
+  } else {
+    const RuntimeShape<T> r(s->plan);
+    const dim3 grid(s->n2, nb), threads(r.tB);
+    if constexpr (MODE == Z_FILTER) {
+      set_lds(pass_b_kernel<T, T>, r.ldsB);
+      hipLaunchKernelGGL((pass_b_kernel<T, T>), grid, threads, r.ldsB, st, bx, v, s->plan, tw);
+    } else if constexpr (MODE == Z_INVERSE) {
+      set_lds(pass_b_inv_kernel<T>, r.ldsB);
+      hipLaunchKernelGGL(pass_b_inv_kernel<T>, grid, threads, r.ldsB, st, bx, s->plan, tw);
+    } else {
+      set_lds(pass_b_adj_kernel<T>, r.ldsB);
+      hipLaunchKernelGGL(pass_b_adj_kernel<T>, grid, threads, r.ldsB, st, bx, fw, v, s->plan, tw);
+    }
+  }
+  CHEBFI_HIP(hipGetLastError());
+}
+
+// Pass C of nb boxes into bands band0 .. of Out.
+template <typename T>
+void launch_c(const abi_system_s *s, const void *box, int band0, int nb, const void *Yk,
+              int64_t ldk, const void *Yprev, int64_t ldp, void *Out, int64_t ldo, double alpha,
+              double cshift, double beta, const void *E, int64_t lde, const double *coef,
+              PlanesOut po, hipStream_t st) {
+  typedef const C2<T> *In;
+  const double2 *tw = reinterpret_cast<const double2 *>(s->d_tw);
+  const T scale = (T)(1.0 / ((double)s->n1 * (double)s->n2 * (double)s->n3));
+  const dim3 grid(s->n3, nb);
+  if (special_planes(s)) {
+#define CHEBFI_CASE(N_)                                                                         \
+  case N_:                                                                                      \
+    hipLaunchKernelGGL((cpass_c_kernel<T, N_>), grid, dim3(cthreads<N_, N_>()), 0, st, (In)box, \
+                       tw, s->d_box, s->d_plane, s->d_kin, band0, (In)Yk, ldk, (In)Yprev, ldp,  \
+                       (C2<T> *)Out, ldo, (T)alpha, (T)cshift, (T)beta, scale, (In)E, lde,      \
+                       coef, po);                                                               \
+    break;
+    switch (s->n1) { CHEBFI_EDGES(CHEBFI_CASE) }
+#undef CHEBFI_CASE
+  } else {
+    const RuntimeShape<T> r(s->plan);
+    set_lds(pass_c_kernel<T>, r.ldsA);
+    hipLaunchKernelGGL(pass_c_kernel<T>, grid, dim3(r.tA), r.ldsA, st, (In)box, s->plan, tw,
+                       s->d_box, s->d_plane, s->d_kin, band0, (In)Yk, ldk, (In)Yprev, ldp,
+                       (C2<T> *)Out, ldo, (T)alpha, (T)cshift, (T)beta, scale, (In)E, lde, coef,
+                       po);
+  }
+  CHEBFI_HIP(hipGetLastError());
 }
 
 }  // namespace
@@ -657,54 +635,21 @@ void launch_local_potential(const abi_system_s *s, const void *Yk, int64_t ldk, 
                             const void *V, double alpha, double cshift, double beta,
                             hipStream_t st, Profiler *prof, const void *E, int64_t lde,
                             void *ypl, int64_t ldpl, int64_t pspl) {
-  using V2 = C2<T>;
-  const BoxPlan &plan = s->plan;
   const PlanesOut po{std::is_same<T, float>::value ? (unsigned short *)ypl : nullptr, ldpl, pspl};
-  const int n1 = plan.d[0].n, n2 = plan.d[1].n, n3 = plan.d[2].n;
-  const double2 *tw = reinterpret_cast<const double2 *>(s->d_tw);
-  const int tA = std::max(stage_threads(plan.d[0], n2), stage_threads(plan.d[1], n1));
-  const int tB = stage_threads(plan.d[2], n1);
-  CHEBFI_REQUIRE(tA <= 512 && tB <= 512, ABI_ERR_GRID, "FFT plane too large for one workgroup");
-  const size_t ldsA = sizeof(V2) * (size_t)(n2 * (n1 + 1) + n1 + n2);
-  const size_t ldsB = sizeof(V2) * (size_t)(n3 * (n1 + 1) + n3);
-  set_lds(pass_a_kernel<T>, ldsA);
-  set_lds(pass_c_kernel<T>, ldsA);
-  if (std::is_same<T, double>::value)
-    set_lds(pass_b_kernel<T, double>, ldsB);
-  else
-    set_lds(pass_b_kernel<T, float>, ldsB);
-  V2 *bx = reinterpret_cast<V2 *>(box);
   // algorithmic HBM bytes of each pass (sphere rows, box planes, V once)
-  const double es = (double)sizeof(V2), nbx = (double)n1 * n2 * n3, np = (double)s->npw;
-  const double bytesA = nb * (np + nbx) * es;
-  const double bytesB = nb * 2.0 * nbx * es + nbx * (double)sizeof(T);
-  const double bytesC = nb * (nbx + np * ((Yprev ? 3.0 : 2.0) + (E ? 1.0 : 0.0))) * es;
-  if (try_cubic<T>(s, Yk, ldk, Yprev, ldp, Out, ldo, band0, nb, box, V, alpha, cshift, beta, st,
-                   prof, bytesA, bytesB, bytesC, E, lde, po))
-    return;
-  int tok = prof ? prof->begin(PROF_FFT_A, bytesA, st) : -1;
-  hipLaunchKernelGGL(pass_a_kernel<T>, dim3(n3, nb), dim3(tA), ldsA, st,
-                     reinterpret_cast<const V2 *>(Yk), ldk, band0, s->d_box, s->d_plane, plan, tw,
-                     bx);
-  CHEBFI_HIP(hipGetLastError());
+  const double es = (double)sizeof(C2<T>), np = (double)s->npw;
+  const double nbx = (double)s->n1 * s->n2 * s->n3;
+  int tok = prof ? prof->begin(PROF_FFT_A, nb * (np + nbx) * es, st) : -1;
+  launch_a<T>(s, Yk, ldk, band0, nb, box, st);
   if (prof) prof->end(tok, st);
-  tok = prof ? prof->begin(PROF_FFT_B, bytesB, st) : -1;
-  if (std::is_same<T, double>::value)
-    hipLaunchKernelGGL((pass_b_kernel<T, double>), dim3(n2, nb), dim3(tB), ldsB, st, bx,
-                       reinterpret_cast<const double *>(V), plan, tw);
-  else
-    hipLaunchKernelGGL((pass_b_kernel<T, float>), dim3(n2, nb), dim3(tB), ldsB, st, bx,
-                       reinterpret_cast<const float *>(V), plan, tw);
-  CHEBFI_HIP(hipGetLastError());
+  tok = prof ? prof->begin(PROF_FFT_B, nb * 2.0 * nbx * es + nbx * (double)sizeof(T), st) : -1;
+  launch_z<T, Z_FILTER>(s, box, nullptr, V, nb, st);
   if (prof) prof->end(tok, st);
-  tok = prof ? prof->begin(PROF_FFT_C, bytesC, st) : -1;
-  const T scale = (T)(1.0 / ((double)n1 * (double)n2 * (double)n3));
-  hipLaunchKernelGGL(pass_c_kernel<T>, dim3(n3, nb), dim3(tA), ldsA, st, bx, plan, tw, s->d_box,
-                     s->d_plane, s->d_kin, band0, reinterpret_cast<const V2 *>(Yk), ldk,
-                     reinterpret_cast<const V2 *>(Yprev), ldp, reinterpret_cast<V2 *>(Out), ldo,
-                     (T)alpha, (T)cshift, (T)beta, scale, reinterpret_cast<const V2 *>(E), lde,
-                     s->coef_dev, po);
-  CHEBFI_HIP(hipGetLastError());
+  tok = prof ? prof->begin(PROF_FFT_C,
+                           nb * (nbx + np * ((Yprev ? 3.0 : 2.0) + (E ? 1.0 : 0.0))) * es, st)
+             : -1;
+  launch_c<T>(s, box, band0, nb, Yk, ldk, Yprev, ldp, Out, ldo, alpha, cshift, beta, E, lde,
+              s->coef_dev, po, st);
   if (prof) prof->end(tok, st);
 }
 
@@ -713,70 +658,27 @@ void launch_adjoint_local(const abi_system_s *s, const void *Ak1, int64_t lda1, 
                           int64_t ldy, void *Ak, int64_t ldak, bool accumulate, int band0, int nb,
                           void *box1, void *box2, const void *V, double gamma, double cshift,
                           double *dV, hipStream_t st) {
-  using V2 = C2<T>;
-  if (try_cubic_adjoint<T>(s, Ak1, lda1, Yk, ldy, Ak, ldak, accumulate, band0, nb, box1, box2, V,
-                           gamma, cshift, dV, st))
-    return;
-  const BoxPlan &plan = s->plan;
-  const int n1 = plan.d[0].n, n2 = plan.d[1].n, n3 = plan.d[2].n;
-  const double2 *tw = reinterpret_cast<const double2 *>(s->d_tw);
-  const int tA = std::max(stage_threads(plan.d[0], n2), stage_threads(plan.d[1], n1));
-  const int tB = stage_threads(plan.d[2], n1);
-  CHEBFI_REQUIRE(tA <= 512 && tB <= 512, ABI_ERR_GRID, "FFT plane too large for one workgroup");
-  const size_t ldsA = sizeof(V2) * (size_t)(n2 * (n1 + 1) + n1 + n2);
-  const size_t ldsB = sizeof(V2) * (size_t)(n3 * (n1 + 1) + n3);
-  set_lds(pass_a_kernel<T>, ldsA);
-  set_lds(pass_c_kernel<T>, ldsA);
-  set_lds(pass_b_inv_kernel<T>, ldsB);
-  set_lds(pass_b_adj_kernel<T>, ldsB);
-  V2 *b1 = reinterpret_cast<V2 *>(box1);
-  V2 *b2 = reinterpret_cast<V2 *>(box2);
-  hipLaunchKernelGGL(pass_a_kernel<T>, dim3(n3, nb), dim3(tA), ldsA, st,
-                     reinterpret_cast<const V2 *>(Ak1), lda1, band0, s->d_box, s->d_plane, plan, tw,
-                     b1);
-  hipLaunchKernelGGL(pass_a_kernel<T>, dim3(n3, nb), dim3(tA), ldsA, st,
-                     reinterpret_cast<const V2 *>(Yk), ldy, band0, s->d_box, s->d_plane, plan, tw,
-                     b2);
-  hipLaunchKernelGGL(pass_b_inv_kernel<T>, dim3(n2, nb), dim3(tB), ldsB, st, b2, plan, tw);
-  hipLaunchKernelGGL(pass_b_adj_kernel<T>, dim3(n2, nb), dim3(tB), ldsB, st, b1, b2,
-                     reinterpret_cast<const T *>(V), plan, tw);
-  const int64_t nbox = (int64_t)n1 * n2 * n3;
+  launch_a<T>(s, Ak1, lda1, band0, nb, box1, st);
+  launch_a<T>(s, Yk, ldy, band0, nb, box2, st);
+  launch_z<T, Z_INVERSE>(s, box2, nullptr, nullptr, nb, st);
+  launch_z<T, Z_ADJOINT>(s, box1, box2, V, nb, st);
+  const int64_t nbox = (int64_t)s->n1 * s->n2 * s->n3;
   hipLaunchKernelGGL(dv_reduce_kernel<T>, dim3((unsigned)((nbox + 255) / 256)), dim3(256), 0, st,
-                     nbox, nb, (const V2 *)b2, gamma / (double)nbox, dV);
-  const T scale = (T)(1.0 / (double)nbox);
-  // Ak = gamma (local + (kin - c) Ak1) + Ak   (beta = -1 adds the previous content)
-  hipLaunchKernelGGL(pass_c_kernel<T>, dim3(n3, nb), dim3(tA), ldsA, st, b1, plan, tw, s->d_box,
-                     s->d_plane, s->d_kin, band0, reinterpret_cast<const V2 *>(Ak1), lda1,
-                     accumulate ? reinterpret_cast<const V2 *>(Ak) : (const V2 *)nullptr, ldak,
-                     reinterpret_cast<V2 *>(Ak), ldak, (T)gamma, (T)cshift, (T)-1, scale,
-                     (const V2 *)nullptr, (int64_t)0, (const double *)nullptr,
-                     PlanesOut{nullptr, 0, 0});
+                     nbox, nb, (const C2<T> *)box2, gamma / (double)nbox, dV);
   CHEBFI_HIP(hipGetLastError());
+  // Ak = gamma (local + (kin - c) Ak1) + Ak   (beta = -1 adds the previous content)
+  launch_c<T>(s, box1, band0, nb, Ak1, lda1, accumulate ? Ak : nullptr, ldak, Ak, ldak, gamma,
+              cshift, -1.0, nullptr, 0, nullptr, PlanesOut{nullptr, 0, 0}, st);
 }
 
 template <typename T>
 void launch_density(const abi_system_s *s, const void *Psi, int64_t ld, int band0, int nb,
                     void *box, const double *w, double *rho, hipStream_t st) {
-  using V2 = C2<T>;
-  if (try_cubic_density<T>(s, Psi, ld, band0, nb, box, w, rho, st)) return;
-  const BoxPlan &plan = s->plan;
-  const int n1 = plan.d[0].n, n2 = plan.d[1].n, n3 = plan.d[2].n;
-  const double2 *tw = reinterpret_cast<const double2 *>(s->d_tw);
-  const int tA = std::max(stage_threads(plan.d[0], n2), stage_threads(plan.d[1], n1));
-  const int tB = stage_threads(plan.d[2], n1);
-  CHEBFI_REQUIRE(tA <= 512 && tB <= 512, ABI_ERR_GRID, "FFT plane too large for one workgroup");
-  const size_t ldsA = sizeof(V2) * (size_t)(n2 * (n1 + 1) + n1 + n2);
-  const size_t ldsB = sizeof(V2) * (size_t)(n3 * (n1 + 1) + n3);
-  set_lds(pass_a_kernel<T>, ldsA);
-  set_lds(pass_b_inv_kernel<T>, ldsB);
-  V2 *bx = reinterpret_cast<V2 *>(box);
-  hipLaunchKernelGGL(pass_a_kernel<T>, dim3(n3, nb), dim3(tA), ldsA, st,
-                     reinterpret_cast<const V2 *>(Psi), ld, band0, s->d_box, s->d_plane, plan, tw,
-                     bx);
-  hipLaunchKernelGGL(pass_b_inv_kernel<T>, dim3(n2, nb), dim3(tB), ldsB, st, bx, plan, tw);
-  const int64_t nbox = (int64_t)n1 * n2 * n3;
+  launch_a<T>(s, Psi, ld, band0, nb, box, st);
+  launch_z<T, Z_INVERSE>(s, box, nullptr, nullptr, nb, st);
+  const int64_t nbox = (int64_t)s->n1 * s->n2 * s->n3;
   hipLaunchKernelGGL(rho_accum_kernel<T>, dim3((unsigned)((nbox + 255) / 256)), dim3(256), 0, st,
-                     nbox, nb, band0, (const V2 *)bx, w, 1.0 / (double)nbox, rho);
+                     nbox, nb, band0, (const C2<T> *)box, w, 1.0 / (double)nbox, rho);
   CHEBFI_HIP(hipGetLastError());
 }
 

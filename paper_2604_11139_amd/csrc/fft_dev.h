@@ -4,6 +4,9 @@
 // of a stage.  Shared by the single-system passes and the batched passes.
 #pragma once
 
+#include <type_traits>
+#include <utility>
+
 #include "cplx.h"
 #include "internal.h"
 
@@ -139,6 +142,39 @@ template <typename T> struct Dft<T, 8> {
   }
 };
 
+// Radix A*B DFT for coprime A and B without twiddles (Good 1958, Thomas 1963):
+// input B n1 + A n2, output k1 eB + k2 eA (mod A B) with eB = 1 mod A, 0 mod B
+// and eA = 0 mod A, 1 mod B; all indices are compile-time constants.
+constexpr int idempotent(int a, int b) {  // multiple of b that is 1 mod a
+  int e = b;
+  while (e % a != 1) e += b;
+  return e;
+}
+template <typename T, int A, int B> struct DftCoprime {
+  static __device__ __forceinline__ void run(C2<T> *x, int sgn) {
+    constexpr int N = A * B, eB = idempotent(A, B), eA = idempotent(B, A);
+    C2<T> t[A][B];
+#pragma unroll
+    for (int n2 = 0; n2 < B; ++n2) {
+      C2<T> a[A];
+#pragma unroll
+      for (int n1 = 0; n1 < A; ++n1) a[n1] = x[(B * n1 + A * n2) % N];
+      Dft<T, A>::run(a, sgn);
+#pragma unroll
+      for (int k1 = 0; k1 < A; ++k1) t[k1][n2] = a[k1];
+    }
+#pragma unroll
+    for (int k1 = 0; k1 < A; ++k1) {
+      Dft<T, B>::run(t[k1], sgn);
+#pragma unroll
+      for (int k2 = 0; k2 < B; ++k2) x[(k1 * eB + k2 * eA) % N] = t[k1][k2];
+    }
+  }
+};
+template <typename T> struct Dft<T, 10> : DftCoprime<T, 2, 5> {};
+template <typename T> struct Dft<T, 12> : DftCoprime<T, 3, 4> {};
+template <typename T> struct Dft<T, 15> : DftCoprime<T, 3, 5> {};
+
 // One Stockham stage of radix R over `npen` pencils of length n held in LDS.
 // Element e of pencil q sits at buf[q*pstride + e*estride].  p is the product
 // of the radices already applied.
@@ -231,9 +267,9 @@ inline int stage_threads(const Plan1D &pl, int npen) {
   return need > 512 ? need : 512;
 }
 
-// ---- compile-time specialised passes for cubic boxes ------------------------
-// Same three passes as above with the box edge N, the radix sequence, the
-// pencil strides and the thread count known at compile time, so that all
+// ---- compile-time specialised passes ------------------------------------------
+// Same three passes as above with the transform length N, the radix sequence,
+// the pencil strides and the thread count known at compile time, so that all
 // index arithmetic reduces to constant multiplies and shifts.  A plane sits in
 // LDS with a row stride of N + 1 elements, and the lanes of a wave take
 // consecutive pencils in both directions: pencils along a row are then an odd
@@ -258,10 +294,33 @@ CHEBFI_CPLAN(36, 2, 6, 6, 1)
 CHEBFI_CPLAN(40, 2, 8, 5, 1)
 CHEBFI_CPLAN(45, 2, 5, 9, 1)
 CHEBFI_CPLAN(48, 2, 8, 6, 1)
+CHEBFI_CPLAN(50, 2, 5, 10, 1)
+CHEBFI_CPLAN(54, 2, 6, 9, 1)
+CHEBFI_CPLAN(60, 2, 6, 10, 1)
 CHEBFI_CPLAN(64, 2, 8, 8, 1)
+CHEBFI_CPLAN(72, 2, 8, 9, 1)
+CHEBFI_CPLAN(75, 2, 5, 15, 1)
+CHEBFI_CPLAN(80, 2, 8, 10, 1)
+CHEBFI_CPLAN(81, 2, 9, 9, 1)
+CHEBFI_CPLAN(90, 2, 9, 10, 1)
+CHEBFI_CPLAN(96, 2, 8, 12, 1)
 #undef CHEBFI_CPLAN
 
-constexpr int kCT = 512;  // threads of the specialised passes (16 waves per CU per 4 planes)
+constexpr int kCT = 512;  // threads of the batched passes (16 waves per CU per 4 planes)
+
+// Threads of a pass over NPEN pencils of length N: one butterfly of the widest
+// stage per thread, in as few rounds as keep the workgroup at 576 threads or
+// fewer (a 36 x 36 plane has 216 radix-6 butterflies: 256 threads, not 512 of
+// which 300 wait at every barrier).
+template <int N, int NPEN>
+constexpr int cthreads() {
+  int w = 0;
+  for (int i = 0; i < CPlan<N>::ns; ++i)
+    if (NPEN * (N / CPlan<N>::r[i]) > w) w = NPEN * (N / CPlan<N>::r[i]);
+  int k = 1;
+  while ((w + k - 1) / k > 576) ++k;
+  return ((w + k - 1) / k + 63) / 64 * 64;
+}
 
 // LDS row pitch of an N x N plane in the specialised passes: odd, so that the
 // lanes of a wave walking consecutive pencils across rows (8-byte elements,
@@ -275,20 +334,20 @@ constexpr int cld() {
 // NG groups of NPEN pencils (group g's pencils start at g * GS): several
 // planes of one LDS buffer transformed by one pass over all their pencils.
 template <typename T, int N, int R, int P, int NPEN, int ES, int PS, int SGN, int NG = 1,
-          int GS = 0>
+          int GS = 0, int CT = kCT>
 __device__ __forceinline__ void cstage(C2<T> *buf, const C2<T> *tw) {
   constexpr int NBF = N / R;
   constexpr int NP = NG * NPEN;
   constexpr int TOTAL = NP * NBF;
   constexpr int M = N / (P * R);
-  constexpr int MAXB = (TOTAL + kCT - 1) / kCT;
+  constexpr int MAXB = (TOTAL + CT - 1) / CT;
   C2<T> y[MAXB][R];
   int dst[MAXB];
 #pragma unroll
   for (int c = 0; c < MAXB; ++c) {
-    const int i = threadIdx.x + c * kCT;
+    const int i = threadIdx.x + c * CT;
     dst[c] = -1;
-    if (TOTAL % kCT == 0 || i < TOTAL) {
+    if (TOTAL % CT == 0 || i < TOTAL) {
       const int pa = i % NP, bf = i / NP;
       const int base = NG == 1 ? pa * PS : (pa / NPEN) * GS + (pa % NPEN) * PS;
       C2<T> x[R];
@@ -312,7 +371,7 @@ __device__ __forceinline__ void cstage(C2<T> *buf, const C2<T> *tw) {
   __syncthreads();
 #pragma unroll
   for (int c = 0; c < MAXB; ++c) {
-    if (TOTAL % kCT == 0 || dst[c] >= 0) {
+    if (TOTAL % CT == 0 || dst[c] >= 0) {
 #pragma unroll
       for (int t = 0; t < R; ++t) buf[dst[c] + t * P * ES] = y[c][t];
     }
@@ -321,12 +380,12 @@ __device__ __forceinline__ void cstage(C2<T> *buf, const C2<T> *tw) {
 }
 
 template <typename T, int N, int S, int P, int NPEN, int ES, int PS, int SGN, int NG = 1,
-          int GS = 0>
+          int GS = 0, int CT = kCT>
 __device__ __forceinline__ void cfft(C2<T> *buf, const C2<T> *tw) {
   if constexpr (S < CPlan<N>::ns) {
     constexpr int R = CPlan<N>::r[S];
-    cstage<T, N, R, P, NPEN, ES, PS, SGN, NG, GS>(buf, tw);
-    cfft<T, N, S + 1, P * R, NPEN, ES, PS, SGN, NG, GS>(buf, tw);
+    cstage<T, N, R, P, NPEN, ES, PS, SGN, NG, GS, CT>(buf, tw);
+    cfft<T, N, S + 1, P * R, NPEN, ES, PS, SGN, NG, GS, CT>(buf, tw);
   }
 }
 
@@ -336,25 +395,40 @@ __device__ __forceinline__ void cfft(C2<T> *buf, const C2<T> *tw) {
 // and the last one write straight to it (or fuse a pointwise product into its
 // store), saving a pass of the plane through LDS.  SYNC_MID: a barrier
 // between the reads and the writes (needed when both are the same LDS plane).
-template <typename T, int N, int R, int P, int NPEN, int SGN, bool SYNC_MID, class Ld, class St>
-__device__ __forceinline__ void cstage_io(const C2<T> *tw, Ld ld, St st) {
+// With `pre`, st also gets pre(pencil, element), fetched before the stage reads.
+struct NoPre {};
+template <class Pre> struct PreValue {
+  typedef decltype(std::declval<Pre>()(0, 0)) type;
+};
+template <> struct PreValue<NoPre> {
+  typedef int type;
+};
+template <typename T, int N, int R, int P, int NPEN, int SGN, bool SYNC_MID, int CT, class Ld,
+          class St, class Pre = NoPre>
+__device__ __forceinline__ void cstage_io(const C2<T> *tw, Ld ld, St st, Pre pre = Pre()) {
+  constexpr bool PRE = !std::is_same<Pre, NoPre>::value;
   constexpr int NBF = N / R;
   constexpr int TOTAL = NPEN * NBF;
   constexpr int M = N / (P * R);
-  constexpr int MAXB = (TOTAL + kCT - 1) / kCT;
+  constexpr int MAXB = (TOTAL + CT - 1) / CT;
   C2<T> y[MAXB][R];
   int eo[MAXB], pp[MAXB];
+  typename PreValue<Pre>::type pv[PRE ? MAXB : 1][PRE ? R : 1];
 #pragma unroll
   for (int c = 0; c < MAXB; ++c) {
-    const int i = threadIdx.x + c * kCT;
+    const int i = threadIdx.x + c * CT;
     eo[c] = -1;
     pp[c] = 0;
-    if (TOTAL % kCT == 0 || i < TOTAL) {
+    if (TOTAL % CT == 0 || i < TOTAL) {
       const int pa = i % NPEN, bf = i / NPEN;
+      const int k = bf % P;
+      if constexpr (PRE) {
+#pragma unroll
+        for (int t = 0; t < R; ++t) pv[c][t] = pre(pa, (bf - k) * R + k + t * P);
+      }
       C2<T> x[R];
 #pragma unroll
       for (int t = 0; t < R; ++t) x[t] = ld(pa, bf + t * NBF);
-      const int k = bf % P;
       if (P > 1) {
 #pragma unroll
         for (int t = 1; t < R; ++t) {
@@ -373,9 +447,14 @@ __device__ __forceinline__ void cstage_io(const C2<T> *tw, Ld ld, St st) {
   if (SYNC_MID) __syncthreads();
 #pragma unroll
   for (int c = 0; c < MAXB; ++c) {
-    if (TOTAL % kCT == 0 || eo[c] >= 0) {
+    if (TOTAL % CT == 0 || eo[c] >= 0) {
 #pragma unroll
-      for (int t = 0; t < R; ++t) st(pp[c], eo[c] + t * P, y[c][t]);
+      for (int t = 0; t < R; ++t) {
+        if constexpr (PRE)
+          st(pp[c], eo[c] + t * P, y[c][t], pv[c][t]);
+        else
+          st(pp[c], eo[c] + t * P, y[c][t]);
+      }
     }
   }
 }
@@ -384,23 +463,24 @@ __device__ __forceinline__ void cstage_io(const C2<T> *tw, Ld ld, St st) {
 // LDS if IN_LDS, else from global memory), the last one writes through stl
 // (into LDS if OUT_LDS), the stages between through the LDS accessors ldm /
 // stm.  A barrier follows every stage whose output is in LDS.
-template <typename T, int N, int S, int P, int NPEN, int SGN, bool IN_LDS, bool OUT_LDS, class Ld0,
-          class StL, class LdM, class StM>
-__device__ __forceinline__ void cfft_io(const C2<T> *tw, Ld0 ld0, StL stl, LdM ldm, StM stm) {
+template <typename T, int N, int S, int P, int NPEN, int SGN, bool IN_LDS, bool OUT_LDS,
+          int CT = kCT, class Ld0, class StL, class LdM, class StM, class Pre = NoPre>
+__device__ __forceinline__ void cfft_io(const C2<T> *tw, Ld0 ld0, StL stl, LdM ldm, StM stm,
+                                        Pre pre = Pre()) {
   if constexpr (S < CPlan<N>::ns) {
     constexpr int R = CPlan<N>::r[S];
     constexpr bool first = S == 0, last = S + 1 == CPlan<N>::ns;
     constexpr bool rd = first ? IN_LDS : true, wr = last ? OUT_LDS : true;
     if constexpr (first && last)
-      cstage_io<T, N, R, P, NPEN, SGN, rd && wr>(tw, ld0, stl);
+      cstage_io<T, N, R, P, NPEN, SGN, rd && wr, CT>(tw, ld0, stl, pre);
     else if constexpr (first)
-      cstage_io<T, N, R, P, NPEN, SGN, rd && wr>(tw, ld0, stm);
+      cstage_io<T, N, R, P, NPEN, SGN, rd && wr, CT>(tw, ld0, stm);
     else if constexpr (last)
-      cstage_io<T, N, R, P, NPEN, SGN, rd && wr>(tw, ldm, stl);
+      cstage_io<T, N, R, P, NPEN, SGN, rd && wr, CT>(tw, ldm, stl, pre);
     else
-      cstage_io<T, N, R, P, NPEN, SGN, true>(tw, ldm, stm);
+      cstage_io<T, N, R, P, NPEN, SGN, true, CT>(tw, ldm, stm);
     if constexpr (wr) __syncthreads();
-    cfft_io<T, N, S + 1, P * R, NPEN, SGN, IN_LDS, OUT_LDS>(tw, ld0, stl, ldm, stm);
+    cfft_io<T, N, S + 1, P * R, NPEN, SGN, IN_LDS, OUT_LDS, CT>(tw, ld0, stl, ldm, stm, pre);
   }
 }
 

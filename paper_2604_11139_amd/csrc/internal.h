@@ -240,7 +240,8 @@ struct abi_system_s {
   double *d_kin = nullptr;         // npw
   int32_t *d_box = nullptr;        // npw, box index of each sphere point
   int32_t *d_plane = nullptr;      // n3+1 sphere ranges per i3 plane
-  uint64_t zocc = ~0ull;           // bit i3: z-plane i3 holds sphere points (n3 <= 64)
+  // bit i3: z-plane i3 holds sphere points (zocc_hi: planes 64..95)
+  uint64_t zocc = 0, zocc_hi = 0;
   double *d_P = nullptr;           // npw x nproj complex (interleaved), ld = npw
   double *d_D = nullptr;           // natom*16 complex, row-major per atom
   double *d_V = nullptr;           // n1*n2*n3
