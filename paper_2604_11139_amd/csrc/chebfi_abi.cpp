@@ -763,7 +763,8 @@ abi_status abi_apply_H_noalloc(abi_system s, const void *X, void *HX, int64_t nb
     if (!fp32 && s->nproj > 0) {
       // the FP64 path runs the FFT passes before the projector products: keep
       // room for the split-K parts and C' behind the box batch
-      const int64_t splits = nband == 1 ? 1 : zgemm_splits(s->nproj, nband, s->npw);
+      const ArenaScope scope(&arena);
+      const int64_t splits = proj_splits(s, nband, dtype);
       arena.reserve = sizeof(double2) * (size_t)s->nproj * nband * (splits + 1) + 512;
     }
     const int overlap = s->overlap;

@@ -28,4 +28,14 @@ template <typename T> __device__ __forceinline__ C2<T> to_c2(double2 v) {
   return C2<T>{(T)v.x, (T)v.y};
 }
 
+// float -> bf16 (round to nearest even) and back, as bits
+__device__ __forceinline__ unsigned short bf16_bits(float x) {
+  unsigned u = __float_as_uint(x);
+  u += 0x7FFFu + ((u >> 16) & 1u);
+  return (unsigned short)(u >> 16);
+}
+__device__ __forceinline__ float bf16_float(unsigned short h) {
+  return __uint_as_float(((unsigned)h) << 16);
+}
+
 }  // namespace chebfi

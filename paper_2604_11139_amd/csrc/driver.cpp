@@ -26,11 +26,28 @@ static int proj_planes_variant(int variant) { return variant >= 15 ? variant - 2
 
 }  // namespace
 
-int mixed_proj_splits(abi_system_s *s, int64_t nband) {
+int mixed_proj_splits(abi_system_s *s, int64_t nband, bool fewest) {
   // 9..12 share the 128 x 128 tile of planes variant 7, 13 the 128 x 256 one of
   // 12, 14..16 the 128 x 128 one
   const int v = s->pl_proj == 13 ? 12 : s->pl_proj >= 9 ? 7 : s->pl_proj;
-  return proj_planes_splits(v, s->nproj, nband, s->npw);
+  return proj_planes_splits(v, s->nproj, nband, s->npw, fewest);
+}
+
+int proj_splits(abi_system_s *s, int64_t nband, int32_t dtype) {
+  const bool fp32 = dtype == ABI_C64, planes = fp32 && s->mixed_gemm == 0;
+  if (nband == 1 && !fp32) return 1;
+  auto count = [&](bool fewest) {
+    return planes ? mixed_proj_splits(s, nband, fewest)
+                  : zgemm_splits(s->nproj, nband, s->npw, fewest);
+  };
+  const int n = count(false);
+  if (!g_scratch_arena) return n;
+  // partials, C', its planes, the projector part E and one box, 256-byte aligned
+  const size_t eb = elem_bytes(dtype), c = (size_t)s->nproj * nband;
+  const size_t need = eb * c * (n + 1) + (planes ? 8 * (size_t)s->ldPB * nband : 0) +
+                      (planes ? eb * (size_t)s->npw * nband : 0) +
+                      eb * (size_t)s->n1 * s->n2 * s->n3 + 8 * 256;
+  return need <= g_scratch_arena->size ? n : count(true);
 }
 
 bool proj_chains_planes(const abi_system_s *s) {
@@ -88,9 +105,7 @@ int project_t(abi_system_s *s, const void *X, int64_t ldx, int64_t nband, hipStr
   const int nproj = s->nproj;
   const bool single = (nband == 1) && !fp32;
   const bool planes = fp32 && s->mixed_gemm == 0;
-  const int splits = single ? 1
-                     : planes ? mixed_proj_splits(s, nband)
-                              : zgemm_splits(nproj, nband, npw);
+  const int splits = proj_splits(s, nband, fp32 ? ABI_C64 : ABI_C128);
   V2 *cpart = (V2 *)s->cpart.get(sizeof(V2) * (size_t)splits * nproj * nband);
   const double flops = 8.0 * (double)nproj * (double)npw * (double)nband;
   // the split-BF16 products time themselves (a planes variant's split pass apart)
@@ -113,7 +128,8 @@ int project_t(abi_system_s *s, const void *X, int64_t ldx, int64_t nband, hipStr
 }
 
 // Out += P C' for nproj x nband coefficients C' (ld nproj) of the block's type;
-// store_only (split-BF16 products only): Out = P C'.
+// store_only (split-BF16 products only): Out = P C'.  A null C' means its bf16
+// planes are in s->cplanes already.
 template <typename T>
 void expand_t(abi_system_s *s, const C2<T> *cprime, void *Out, int64_t ldo, int64_t nband,
               hipStream_t st, bool store_only = false) {
@@ -125,7 +141,7 @@ void expand_t(abi_system_s *s, const C2<T> *cprime, void *Out, int64_t ldo, int6
   const bool planes = fp32 && s->mixed_gemm == 0;
   CHEBFI_REQUIRE(!store_only || (planes && !single), ABI_ERR_STATE,
                  "store-only expansion needs the split-BF16 products");
-  if (planes)
+  if (planes && cprime)
     split_planes(nproj, nband, cprime, nproj, s->cplanes.get(8 * (size_t)s->ldPB * nband),
                  s->ldPB, st);
   const double flops = 8.0 * (double)nproj * (double)npw * (double)nband;
@@ -206,10 +222,15 @@ void apply_core_t(abi_system_s *s, const void *X, int64_t ldx, const void *Xprev
     V2 *cpart = nullptr;
     const int splits = project_t<T>(s, X, ldx, nband, st, &cpart, have_planes);
     if (Craw) launch_sum_parts(nproj, nband, cpart, splits, Craw, st, fp32);
-    cprime = (V2 *)s->cprime.get(sizeof(V2) * (size_t)nproj * nband);
+    void *cpl = nullptr;  // pre: straight into the expansion's planes
+    if (pre)
+      cpl = s->cplanes.get(8 * (size_t)s->ldPB * nband);
+    else
+      cprime = (V2 *)s->cprime.get(sizeof(V2) * (size_t)nproj * nband);
     const int tok =
         s->prof.begin(PROF_DAPPLY, (double)sizeof(V2) * nproj * nband * (splits + 1), st);
-    launch_dapply(s->natom, nband, cpart, splits, s->d_D, alpha, cprime, st, fp32, s->coef_dev);
+    launch_dapply(s->natom, nband, cpart, splits, s->d_D, alpha, cprime, st, fp32, s->coef_dev,
+                  cpl, s->ldPB);
     s->prof.end(tok, st);
   }
   if (side) CHEBFI_HIP(hipStreamWaitEvent(st, s->ev_join, 0));

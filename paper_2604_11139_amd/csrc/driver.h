@@ -52,7 +52,11 @@ void gen_step(abi_system_s *s, const void *X, int64_t ldx, const void *Xprev, in
 // have_planes: X's bf16 planes are already in s->planes (no split pass).
 // proj_chains_planes: the projection variant reads planes that the previous
 // filter step's last FFT pass can write (15, 16).
-int mixed_proj_splits(abi_system_s *s, int64_t nband);
+int mixed_proj_splits(abi_system_s *s, int64_t nband, bool fewest = false);
+// K-split count of the projection of nband bands of `dtype` as apply_core runs it.
+// A no-allocation call takes the fewest chunks when the larger count's partial
+// products would not fit its scratch array beside the other work buffers.
+int proj_splits(abi_system_s *s, int64_t nband, int32_t dtype);
 bool proj_chains_planes(const abi_system_s *s);
 void mixed_project(abi_system_s *s, const void *X, int64_t ldx, int64_t nband, void *part,
                    int splits, hipStream_t st, bool have_planes = false);

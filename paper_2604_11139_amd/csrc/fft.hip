@@ -37,14 +37,6 @@ struct PlanesOut {
   unsigned short *p;
   int64_t ld, ps;
 };
-__device__ __forceinline__ unsigned short bf16_bits(float x) {
-  unsigned u = __float_as_uint(x);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (unsigned short)(u >> 16);
-}
-__device__ __forceinline__ float bf16_float(unsigned short h) {
-  return __uint_as_float(((unsigned)h) << 16);
-}
 // Out[idx] = value(idx) over the sphere rows [s0, s1) with nt threads, and with
 // po.p (T = float) the bf16 planes of each value.  (Pairing neighbouring
 // lanes' planes into 32-bit stores by a shuffle measured slower: the pass is

@@ -306,6 +306,29 @@ static int best_splits(int64_t tiles, int64_t kmax, int per_cu) {
   return (int)best;
 }
 
+// Split-K count of a product whose `tiles` output tiles cannot fill the chip even
+// with the shortest chunks best_splits allows: every chunk still has a compute
+// unit to itself, so its time is its K steps in sequence (step_us each: the
+// loads' latency or the matrix cores' time of a lone workgroup) plus what it
+// costs to start, and the sum of the partials grows with the count (a read of
+// eight partials in flight is about one microsecond).  At 1503 plane waves x 8
+// projectors x 32 bands the FP64 projection took 73 us in three chunks of 512,
+// 7.5 in 24; the mixed one at 1597 x 12 x 17 55 us in two of 800, 9.3 in 10.
+static int lone_splits(int64_t tiles, int64_t k, int step, double step_us) {
+  const int64_t cus = device_cus(), steps = (k + step - 1) / step;
+  const int64_t smax = std::min<int64_t>({64, steps, std::max<int64_t>(1, cus / tiles)});
+  int64_t best = 1;
+  double best_us = 1e300;
+  for (int64_t s = 1; s <= smax; ++s) {
+    const double us = (double)((steps + s - 1) / s) * step_us + 0.125 * (double)s;
+    if (us < best_us) {
+      best_us = us;
+      best = s;
+    }
+  }
+  return (int)best;
+}
+
 int zgemm_herm_splits(int64_t m, int64_t k) {
   const int64_t nt = (m + BM - 1) / BM;
   return best_splits(nt * (nt + 1) / 2, (k + 511) / 512, 2);
@@ -328,8 +351,9 @@ void zgemm_herm(int64_t m, int64_t k, const void *A, int64_t lda, const void *B,
   CHEBFI_HIP(hipGetLastError());
 }
 
-int zgemm_splits(int64_t m, int64_t n, int64_t k) {
+int zgemm_splits(int64_t m, int64_t n, int64_t k, bool fewest) {
   const int64_t tiles = ((m + BM - 1) / BM) * ((n + BN - 1) / BN);
+  if (!fewest && tiles * ((k + 511) / 512) < device_cus()) return lone_splits(tiles, k, BK, 2.0);
   // keep at least ~512 K per chunk; two 256-thread workgroups per CU (66 KB LDS each)
   return best_splits(tiles, (k + 511) / 512, 2);
 }
@@ -1930,12 +1954,14 @@ static int pl_bm(int variant) { return (variant == 2 || variant == 3) ? 64 : var
 static int pl_bn(int variant) { return (variant == 2 || variant == 6) ? 64 : variant == 12 ? 256 : 128; }
 static bool pl_one_per_cu(int variant) { return variant == 4 || variant == 5 || variant >= 7; }
 
-int proj_planes_splits(int variant, int64_t nproj, int64_t nband, int64_t npw) {
+int proj_planes_splits(int variant, int64_t nproj, int64_t nband, int64_t npw, bool fewest) {
   // at least 1024 plane waves per chunk; the double-buffered 128 x 128 tiles hold
   // 128 KB of LDS (one workgroup per CU), the single-stage ones two per CU
   const int64_t tiles = ((nproj + pl_bm(variant) - 1) / pl_bm(variant)) *
                         ((nband + pl_bn(variant) - 1) / pl_bn(variant));
   const int per_cu = pl_one_per_cu(variant) ? 1 : 2;
+  if (!fewest && tiles * ((npw + 1023) / 1024) < device_cus())
+    return lone_splits(tiles, npw, XBK, 2.4);
   return best_splits(tiles, (npw + 1023) / 1024, per_cu);
 }
 

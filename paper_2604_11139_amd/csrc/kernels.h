@@ -81,8 +81,10 @@ void split_planes(int64_t rows, int64_t cols, const void *X, int64_t ld, void *p
 void split_planes_t(int64_t rows, int64_t cols, const void *X, int64_t ld, void *planes,
                     int64_t ldp, hipStream_t st);
 // `variant` selects the tile shape (0..6, see gemm.hip); proj_planes_splits
-// gives the K split count that fills the chip for that shape.
-int proj_planes_splits(int variant, int64_t nproj, int64_t nband, int64_t npw);
+// gives the K split count that fills the chip for that shape (fewest: the count
+// with at least 1024 plane waves per chunk, for calls short of work memory).
+int proj_planes_splits(int variant, int64_t nproj, int64_t nband, int64_t npw,
+                       bool fewest = false);
 void proj_gemm_planes(int64_t nproj, int64_t nband, int64_t npw, const void *Apl, int64_t lda,
                       int64_t psa, const void *Ypl, int64_t ldy, int64_t psy, void *part,
                       int splits, hipStream_t st, int variant);
@@ -114,8 +116,9 @@ void rr_rotate_planes(int64_t npw, int64_t m, const void *Apl, int64_t lda, cons
 void proj_gemv(int64_t npw, int nproj, const void *P, const void *x, void *c, hipStream_t st);
 void expand_gemv(int64_t npw, int nproj, const void *P, const void *c, void *out, hipStream_t st);
 
-// Number of K splits that fills the chip for an m x n output.
-int zgemm_splits(int64_t m, int64_t n, int64_t k);
+// Number of K splits that fills the chip for an m x n output (fewest: with at
+// least 512 K per chunk).
+int zgemm_splits(int64_t m, int64_t n, int64_t k, bool fewest = false);
 // C (m x m, ldc) = A^H B for a product known to be Hermitian (Gram matrices):
 // only the 64 x 64 tiles on and above the diagonal are multiplied (split-K
 // into `part`, splits x m x m), the lower triangle is the conjugate mirror.
@@ -129,10 +132,12 @@ void zsum_parts(int64_t m, int64_t n, const void *part, int splits, void *C, int
 
 // ---- stream.hip -------------------------------------------------------------
 // Cprime[4R+i, b] = alpha * sum_j D_R[i][j] * sum_z part[z][4R+j, b]
-// (fp32: complex float partials and output, FP64 arithmetic inside)
+// (fp32: complex float partials and output, FP64 arithmetic inside; with
+// `planes` the output is the bf16 planes of Cprime, split_planes layout with
+// stride ldpl, and Cprime is not written)
 void launch_dapply(int natom, int64_t nband, const void *part, int splits, const void *D,
                    double alpha, void *Cprime, hipStream_t st, bool fp32 = false,
-                   const double *coef = nullptr);
+                   const double *coef = nullptr, void *planes = nullptr, int64_t ldpl = 0);
 
 // rq[b] = Re(x_b^H hx_b) / Re(x_b^H sx_b); sx_b = x_b when SX is null
 void launch_rayleigh_quotients(int64_t npw, int64_t nband, const void *X, int64_t ldx,

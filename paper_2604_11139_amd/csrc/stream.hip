@@ -35,35 +35,66 @@ __device__ double block_sum(double v, double *scratch) {
   return t;
 }
 
-template <typename T>
-__global__ void dapply_kernel(int natom, int64_t nband, const C2<T> *__restrict__ part,
-                              int splits, const double2 *__restrict__ D, double alpha,
-                              C2<T> *__restrict__ Cp, const double *__restrict__ coef) {
+// One thread per output row (j = row of C', lanes of four share an atom, so the
+// partials are read coalesced and the four sums meet through shuffles), ZG waves
+// per 64 rows that share the partials of a row: a serial sum by one thread per
+// atom waited once per partial, 18.6 us at 22 partials of 256 x 512 complex64;
+// now 8.6 at 32, of which about 4 is the launch.
+// planes: the four bf16 planes of C' (split_planes layout, stride ldpl, rows
+// nproj .. ldpl - 1 zero) instead of C' itself: the expansion's operand without
+// a pass of its own.
+template <typename T, int ZG>
+__global__ __launch_bounds__(64 * ZG) void dapply_kernel(
+    int64_t nproj, int64_t nband, const C2<T> *__restrict__ part, int splits,
+    const double2 *__restrict__ D, double alpha, C2<T> *__restrict__ Cp,
+    unsigned short *__restrict__ pl, int64_t ldpl, const double *__restrict__ coef) {
+  __shared__ double2 red[ZG][64];
   if (coef) alpha = coef[0];  // (this step's alpha from device memory: captured filters)
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)natom * nband) return;
-  const int64_t R = idx % natom, b = idx / natom;
-  const int64_t nproj = 4 * (int64_t)natom;
+  const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+  const int64_t rows = pl ? ldpl : nproj;  // a multiple of 4
+  const int64_t idx = (int64_t)blockIdx.x * 64 + lane;
+  const int64_t b = idx / rows, row = idx - b * rows;
+  const bool in = b < nband && row < nproj;
   const int64_t mn = nproj * nband;
-  double2 c[4];
+  double2 c{0, 0};
+  if (in) {
+    const C2<T> *p = part + row + b * nproj;
+    const int per = (splits + ZG - 1) / ZG, z1 = min(splits, (g + 1) * per);
+#pragma unroll 8
+    for (int z = g * per; z < z1; ++z) {
+      const C2<T> v = p[(int64_t)z * mn];
+      c.x += (double)v.x;
+      c.y += (double)v.y;
+    }
+  }
+  if (ZG > 1) {
+    red[g][lane] = c;
+    __syncthreads();
+    if (g > 0) return;
+#pragma unroll
+    for (int q = 1; q < ZG; ++q) c = cadd(c, red[q][lane]);
+  }
+  const double2 *d = D + 4 * (in ? row : 0);  // row j of its atom's 4 x 4 block
+  double2 s{0, 0};
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    double2 s{0, 0};
-    for (int z = 0; z < splits; ++z) {
-      const C2<T> v = part[(int64_t)z * mn + (4 * R + j) + b * nproj];
-      s.x += (double)v.x;
-      s.y += (double)v.y;
+    const int src = (lane & ~3) + j;
+    s = cadd(s, cmul(d[j], double2{__shfl(c.x, src, 64), __shfl(c.y, src, 64)}));
+  }
+  const C2<T> o = in ? C2<T>{(T)(alpha * s.x), (T)(alpha * s.y)} : C2<T>{0, 0};
+  if constexpr (sizeof(T) == 4) {
+    if (pl) {
+      if (b >= nband) return;
+      const int64_t ps = ldpl * nband;
+      const unsigned short hr = bf16_bits(o.x), hi = bf16_bits(o.y);
+      pl[idx] = hr;
+      pl[ps + idx] = hi;
+      pl[2 * ps + idx] = bf16_bits(o.x - bf16_float(hr));
+      pl[3 * ps + idx] = bf16_bits(o.y - bf16_float(hi));
+      return;
     }
-    c[j] = s;
   }
-  const double2 *d = D + 16 * R;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    double2 s{0, 0};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) s = cadd(s, cmul(d[4 * i + j], c[j]));
-    Cp[(4 * R + i) + b * nproj] = C2<T>{(T)(alpha * s.x), (T)(alpha * s.y)};
-  }
+  if (in) Cp[row + b * nproj] = o;
 }
 
 // rq[b] = Re(x^H hx) / Re(x^H sx), sx = x when SX is null (S = I)
@@ -440,6 +471,7 @@ __global__ void sum_parts_kernel(int64_t mn, int splits, const C2<T> *__restrict
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= mn) return;
   double sx = 0.0, sy = 0.0;
+#pragma unroll 8  // (eight partials in flight: the sum keeps its order)
   for (int z = 0; z < splits; ++z) {
     const C2<T> v = part[(int64_t)z * mn + idx];
     sx += (double)v.x;
@@ -471,6 +503,7 @@ __global__ void gen_combine_kernel(int64_t mn, int splits, const C2<T> *__restri
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= mn) return;
   double gx = 0.0, gy = 0.0;
+#pragma unroll 8  // (eight partials in flight: the sum keeps its order)
   for (int z = 0; z < splits; ++z) {
     const C2<T> v = part[(int64_t)z * mn + idx];
     gx += (double)v.x;
@@ -495,6 +528,7 @@ __global__ void parts_to_c128_kernel(int64_t mn, int splits, const C2<T> *__rest
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= mn) return;
   double sx = 0.0, sy = 0.0;
+#pragma unroll 8  // (eight partials in flight: the sum keeps its order)
   for (int z = 0; z < splits; ++z) {
     const C2<T> v = part[(int64_t)z * mn + idx];
     sx += (double)v.x;
@@ -643,19 +677,33 @@ void launch_d2f(int64_t n, const double *src, float *dst, hipStream_t st) {
   CHEBFI_HIP(hipGetLastError());
 }
 
-void launch_dapply(int natom, int64_t nband, const void *part, int splits, const void *D,
-                   double alpha, void *Cprime, hipStream_t st, bool fp32, const double *coef) {
-  const int64_t total = (int64_t)natom * nband;
-  if (total <= 0) return;
-  if (fp32)
-    hipLaunchKernelGGL(dapply_kernel<float>, dim3(nblk(total, 256)), dim3(256), 0, st, natom,
-                       nband, (const float2 *)part, splits, (const double2 *)D, alpha,
-                       (float2 *)Cprime, coef);
+template <typename T>
+static void dapply_t(int64_t nproj, int64_t nband, const void *part, int splits, const void *D,
+                     double alpha, void *Cp, void *planes, int64_t ldpl, const double *coef,
+                     hipStream_t st) {
+  const dim3 grid(nblk((planes ? ldpl : nproj) * nband, 64));
+  // from eight partials on, four waves share them
+  if (splits >= 8)
+    hipLaunchKernelGGL((dapply_kernel<T, 4>), grid, dim3(256), 0, st, nproj, nband,
+                       (const C2<T> *)part, splits, (const double2 *)D, alpha, (C2<T> *)Cp,
+                       (unsigned short *)planes, ldpl, coef);
   else
-    hipLaunchKernelGGL(dapply_kernel<double>, dim3(nblk(total, 256)), dim3(256), 0, st, natom,
-                       nband, (const double2 *)part, splits, (const double2 *)D, alpha,
-                       (double2 *)Cprime, coef);
+    hipLaunchKernelGGL((dapply_kernel<T, 1>), grid, dim3(64), 0, st, nproj, nband,
+                       (const C2<T> *)part, splits, (const double2 *)D, alpha, (C2<T> *)Cp,
+                       (unsigned short *)planes, ldpl, coef);
   CHEBFI_HIP(hipGetLastError());
+}
+
+void launch_dapply(int natom, int64_t nband, const void *part, int splits, const void *D,
+                   double alpha, void *Cprime, hipStream_t st, bool fp32, const double *coef,
+                   void *planes, int64_t ldpl) {
+  if (natom <= 0 || nband <= 0) return;
+  if (fp32)
+    dapply_t<float>(4 * (int64_t)natom, nband, part, splits, D, alpha, Cprime, planes, ldpl, coef,
+                    st);
+  else
+    dapply_t<double>(4 * (int64_t)natom, nband, part, splits, D, alpha, Cprime, nullptr, 0, coef,
+                     st);
 }
 
 void launch_rayleigh_quotients(int64_t npw, int64_t nband, const void *X, int64_t ldx,
