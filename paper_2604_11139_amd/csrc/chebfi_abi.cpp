@@ -1955,8 +1955,9 @@ abi_status abi_zheev(int64_t m, void *A, int64_t lda, double *w, void *Z, int64_
     void *work = nullptr;
     CHEBFI_HIP(hipMalloc(&work, zheev_work_bytes(m)));
     try {
-      zheev(m, A, lda, w, Z, ldz, work, st);
+      const int *flag = zheev(m, A, lda, w, Z, ldz, work, st);
       CHEBFI_HIP(hipStreamSynchronize(st));
+      zheev_check(flag);
     } catch (...) {
       (void)hipFree(work);
       throw;

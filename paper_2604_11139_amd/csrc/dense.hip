@@ -12,9 +12,10 @@
 // * U^-1: blocked, diagonal blocks inverted in LDS, off-diagonal panels by GEMM;
 // * Hermitian eigensolver: Householder reduction to real symmetric tridiagonal
 //   form (reflectors H = I - tau u u^H with a real sub-diagonal, applied from
-//   both sides as rank-2 updates gathered in panels of 32 columns: per column
-//   a read-only product with the trailing matrix and a row-parallel finish,
-//   per panel one GEMM update),
+//   both sides as rank-2 updates; matrices up to 2048 are reduced by one launch
+//   that keeps them in registers, larger ones in panels of 32 columns until the
+//   rest fits: per column a read-only product with the trailing matrix and a
+//   row-parallel finish, per panel one GEMM update),
 //   eigenvalues by Sturm-count multisection (one wave per eigenvalue, 64
 //   points per round), eigenvectors of the tridiagonal by inverse iteration
 //   with partial-pivoting LU (one lane per isolated eigenvalue; one workgroup
@@ -23,6 +24,7 @@
 //   classical Householder / bisection / inverse-iteration methods (Wilkinson;
 //   Golub & Van Loan, "Matrix Computations", chapter 8).
 #include <cfloat>
+#include <string>
 
 #include "cplx.h"
 #include "kernels.h"
@@ -460,6 +462,359 @@ __global__ __launch_bounds__(kTriFinT) void tri_fin_kernel(
     s2 = wave_sum(s2);
     if (lane == 0) normpart[blockIdx.x] = s2;
   }
+}
+
+// ---- the whole reduction in registers ------------------------------------------
+// A trailing matrix of N <= 2048 fits the register files: 256 workgroups of 512
+// threads hold eight columns each (workgroup g columns g + G q, thread t rows
+// t + 512 p, up to 128 VGPRs), so the rank-2 updates cost no memory traffic at all
+// and one launch does every column.  The blocked form above needs two launches
+// per column, 6-9 us each however little they do; here a column takes one
+// exchange between the workgroups:
+//   A  the dots z_j = sum_{r >= c+2} conj(A[r, j]) x_r of its own columns with the
+//      current column x (every workgroup holds all of x), and the norm of x;
+//   B  z published, and by its owner column c + 1 as it stands;
+//   C  every workgroup reads all z and that column a: y = A u = a + scal z (u
+//      starts with 1, A is Hermitian), w = tau y + a2 u as in the blocked form;
+//   D  its own columns A -= u w^H + w u^H in registers, and, from a, the next
+//      current column, redundantly in every workgroup.
+// The reflector is computed while z travels.
+//
+// Exchange.  z and the column go through memory as relaxed agent-scope atomics
+// (performed at the memory side, past the L2s of the XCDs, which are not coherent
+// with each other), and a reader polls the words themselves: a word holds
+// kTriEmpty until it is published.  No counter, no barrier between workgroups and
+// no cache write-back (a fence per workgroup makes each XCD write its L2 back
+// once for every workgroup on it: 26 us per barrier).  Three buffers rotate.  A
+// workgroup that has read all of step c knows that every other one has published
+// step c, and so has finished reading step c - 1, and clears its words of that
+// buffer for step c + 2; a wait for those stores precedes its words of step c + 1,
+// which every reader of step c + 2 has seen.  A workgroup with no column left
+// stops after publishing; the words it would clear are never read again.
+//
+// The launch is cooperative: all workgroups are resident, so a published word
+// always arrives.  A wait is bounded all the same (kTriSpins polls, about two
+// seconds); a thread that gives up sets *dead, waits for nothing more, and the
+// caller reports the error.
+constexpr int kTriRegT = 512;    // threads: eight waves
+constexpr int kTriRegC = 8;      // columns per workgroup
+constexpr int kTriRegR = 4;      // most rows per thread (2048 rows)
+constexpr int kTriSpins = 1 << 21;
+constexpr unsigned long long kTriEmpty = 0x7FF4C0DEC0DEC0DEull;  // a NaN no result has
+
+__device__ __forceinline__ void tri_put(unsigned long long *p, double v) {
+  unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  if (b == kTriEmpty) b = 0x7FF8000000000000ull;
+  __hip_atomic_store(p, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long tri_get(const unsigned long long *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// workgroup barrier for LDS alone: global stores stay in flight
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+// Wave sums without LDS traffic (a ds_bpermute per dword and step made the step's
+// five sums 4500 of its 8400 cycles at N = 512; now 1900 of 6400).  permlane32_swap hands
+// the upper half of its first register to the second one's lower half and back,
+// permlane16_swap the odd rows of 16 lanes to the even ones; row_ror rotates
+// within a row.
+union DWords {
+  double v;
+  unsigned w[2];
+};
+// lanes 0-31: a summed over the halves, lanes 32-63: b
+__device__ __forceinline__ double swap32_add(double a, double b) {
+  DWords x{a}, y{b};
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const auto r = __builtin_amdgcn_permlane32_swap(x.w[i], y.w[i], false, false);
+    x.w[i] = r[0];
+    y.w[i] = r[1];
+  }
+  return x.v + y.v;
+}
+// even rows: a summed over the row pair, odd rows: b
+__device__ __forceinline__ double swap16_add(double a, double b) {
+  DWords x{a}, y{b};
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const auto r = __builtin_amdgcn_permlane16_swap(x.w[i], y.w[i], false, false);
+    x.w[i] = r[0];
+    y.w[i] = r[1];
+  }
+  return x.v + y.v;
+}
+template <int N> __device__ __forceinline__ double row_ror_add(double a) {
+  DWords x{a}, y;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    y.w[i] = (unsigned)__builtin_amdgcn_update_dpp(0, (int)x.w[i], 0x120 + N, 0xF, 0xF, true);
+  return x.v + y.v;
+}
+__device__ __forceinline__ double row_sum(double a) {  // over 16 lanes, on all of them
+  return row_ror_add<1>(row_ror_add<2>(row_ror_add<4>(row_ror_add<8>(a))));
+}
+__device__ __forceinline__ double wave_sum_all(double a) {
+  a = swap32_add(a, a);
+  return row_sum(swap16_add(a, a));
+}
+// a summed on lanes 0-31, b on lanes 32-63
+__device__ __forceinline__ double wave_sum_pair(double a, double b) {
+  const double v = swap32_add(a, b);
+  return row_sum(swap16_add(v, v));
+}
+// sums of 16 values: value k + 4 r in out[k] of row r
+__device__ __forceinline__ void wave_sum16(const double (&v)[16], double (&out)[4]) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    out[k] = row_sum(swap16_add(swap32_add(v[k], v[k + 8]), swap32_add(v[k + 4], v[k + 12])));
+}
+
+// words of the exchange buffers: three of (z, column) x N complex
+__device__ __host__ constexpr size_t tri_words(int64_t n) { return 12 * (size_t)n; }
+__global__ __launch_bounds__(256) void tri_clear_kernel(size_t n, unsigned long long *p, int *dead) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) p[i] = kTriEmpty;
+  if (i == 0) *dead = 0;
+}
+
+// Reduces A[c0:, c0:] (N = m - c0 rows); xv holds its first column.
+template <int R>
+__global__ __launch_bounds__(kTriRegT) void tri_reg_kernel(int64_t m, double2 *__restrict__ A,
+                                                           int64_t lda, int64_t c0,
+                                                           const double2 *__restrict__ xv,
+                                                           double *__restrict__ d,
+                                                           double *__restrict__ e,
+                                                           double2 *__restrict__ tau,
+                                                           unsigned long long *xch, int *dead) {
+  constexpr int C = kTriRegC, T = kTriRegT, NW = T / 64;
+  static_assert(2 * C == 16, "wave_sum16 carries the dots of a workgroup");
+  __shared__ double zpart[NW][2 * C];
+  __shared__ double npart[NW];
+  __shared__ double2 alpha_s, ynext_s;
+  __shared__ double yupart[NW][2];
+  __shared__ double2 yown[C], uown[C];
+  const int N = (int)(m - c0), G = gridDim.x, g = blockIdx.x;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  // own columns in registers; own[p]: the column of this workgroup whose index is
+  // row p of this thread, or -1
+  double ax[C][R], ay[C][R];
+  double xr[R], xi[R];
+  int own[R];
+#pragma unroll
+  for (int p = 0; p < R; ++p) {
+    const int r = t + T * p;
+    own[p] = r >= g && r < N && (r - g) % G == 0 ? (r - g) / G : -1;
+    double2 x{0.0, 0.0};
+    if (r < N) x = xv[c0 + r];
+    xr[p] = x.x;
+    xi[p] = x.y;
+#pragma unroll
+    for (int q = 0; q < C; ++q) {
+      const int j = g + G * q;
+      double2 a{0.0, 0.0};
+      if (j > 0 && j < N && r < N) a = A[(c0 + r) + (c0 + j) * lda];
+      ax[q][p] = a.x;
+      ay[q][p] = a.y;
+    }
+    if (r == 1) alpha_s = x;
+  }
+  if (t < C) yown[t] = uown[t] = double2{0.0, 0.0};
+  bool gone = false;  // gave up waiting
+  for (int c = 0; c + 1 < N; ++c) {
+    unsigned long long *zb = xch + (size_t)(c % 3) * 4 * N, *ab = zb + 2 * (size_t)N;
+    const bool writer = (c + 1) % G == g;  // owner of column c + 1
+    // A: column c + 1 as it stands, dots with x, norm of x
+    if (writer) {
+      const int qs = (c + 1) / G;
+#pragma unroll
+      for (int q = 0; q < C; ++q)
+        if (q == qs) {
+#pragma unroll
+          for (int p = 0; p < R; ++p) {
+            const int r = t + T * p;
+            if (r > c && r < N) {
+              tri_put(ab + 2 * r, ax[q][p]);
+              tri_put(ab + 2 * r + 1, ay[q][p]);
+            }
+          }
+        }
+    }
+    double z[2 * C], n2 = 0.0;
+#pragma unroll
+    for (int i = 0; i < 2 * C; ++i) z[i] = 0.0;
+#pragma unroll
+    for (int p = 0; p < R; ++p) {
+      if (T * (p + 1) <= c + 2) continue;  // rows done with
+      const bool below = t + T * p >= c + 2;
+      const double vx = below ? xr[p] : 0.0, vy = below ? xi[p] : 0.0;
+      n2 += vx * vx + vy * vy;
+#pragma unroll
+      for (int q = 0; q < C; ++q) {
+        z[2 * q] += ax[q][p] * vx + ay[q][p] * vy;
+        z[2 * q + 1] += ax[q][p] * vy - ay[q][p] * vx;
+      }
+    }
+    double zs[4];
+    wave_sum16(z, zs);
+    n2 = wave_sum_all(n2);
+    if ((lane & 15) == 0) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) zpart[wave][4 * (lane >> 4) + k] = zs[k];
+    }
+    if (lane == 0) npart[wave] = n2;
+    lds_barrier();
+    // B: publish z (after the clearing stores of the last step have landed)
+    if (t < 2 * C) {
+      const int j = g + G * (t >> 1);
+      double s = 0.0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) s += zpart[w][t];
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      if (j > c && j < N) tri_put(zb + 2 * j + (t & 1), s);
+    }
+    double xn = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) xn += npart[w];
+    const Reflector h = make_reflector(alpha_s, xn);
+    double ur[R], ui[R];
+#pragma unroll
+    for (int p = 0; p < R; ++p) {
+      const int r = t + T * p;
+      const double2 u = cmul(double2{xr[p], xi[p]}, h.scal);
+      ur[p] = r == c + 1 ? 1.0 : r > c + 1 ? u.x : 0.0;
+      ui[p] = r > c + 1 ? u.y : 0.0;
+      if (writer) {
+        if (r > c + 1 && r < N) A[(c0 + r) + (c0 + c) * lda] = double2{ur[p], ui[p]};
+        if (r == c) d[c0 + c] = xr[p];
+      }
+    }
+    if (writer && t == 0) {
+      e[c0 + c] = h.beta;
+      tau[c0 + c] = h.tau;
+    }
+    // (no column of this workgroup is left: the last one goes on, for d[N - 1])
+    if (g + G * ((N - 1 - g) / G) <= c + 1 && c + 2 < N) return;
+    // C: all z and column c + 1 (rows > c)
+    double yx[R], yy[R], cx[R], cy[R];
+    {
+      unsigned long long w0[R], w1[R], w2[R], w3[R];
+      int spins = 0;
+      for (;;) {
+        bool ok = true;
+#pragma unroll
+        for (int p = 0; p < R; ++p) {
+          const int r = t + T * p;
+          w0[p] = w1[p] = w2[p] = w3[p] = 0;
+          if (r > c && r < N) {
+            w0[p] = tri_get(zb + 2 * r);
+            w1[p] = tri_get(zb + 2 * r + 1);
+            w2[p] = tri_get(ab + 2 * r);
+            w3[p] = tri_get(ab + 2 * r + 1);
+          }
+        }
+#pragma unroll
+        for (int p = 0; p < R; ++p)
+          ok = ok && w0[p] != kTriEmpty && w1[p] != kTriEmpty && w2[p] != kTriEmpty &&
+               w3[p] != kTriEmpty;
+        if (ok || gone) break;
+        if (++spins >= kTriSpins) {
+          gone = true;
+          __hip_atomic_store(dead, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      }
+#pragma unroll
+      for (int p = 0; p < R; ++p) {
+        cx[p] = __longlong_as_double((long long)w2[p]);
+        cy[p] = __longlong_as_double((long long)w3[p]);
+        const double2 y =
+            cmul(h.scal, double2{__longlong_as_double((long long)w0[p]),
+                                 __longlong_as_double((long long)w1[p])});
+        yx[p] = cx[p] + y.x;
+        yy[p] = cy[p] + y.y;
+      }
+    }
+    double2 yu{0.0, 0.0};  // y^H u
+#pragma unroll
+    for (int p = 0; p < R; ++p) {
+      yu.x += yx[p] * ur[p] + yy[p] * ui[p];
+      yu.y += yx[p] * ui[p] - yy[p] * ur[p];
+      if (t + T * p == c + 1) ynext_s = double2{yx[p], yy[p]};
+      if (own[p] >= 0) {
+        yown[own[p]] = double2{yx[p], yy[p]};
+        uown[own[p]] = double2{ur[p], ui[p]};
+      }
+    }
+    const double yus = wave_sum_pair(yu.x, yu.y);
+    if ((lane & 31) == 0) yupart[wave][lane >> 5] = yus;
+    lds_barrier();
+    // D: clear the buffer of step c + 2, w, the next current column, the update
+    if (t < 2 * C) {
+      const int j = g + G * (t >> 1);
+      unsigned long long *zn = xch + (size_t)((c + 2) % 3) * 4 * N, *an = zn + 2 * (size_t)N;
+      if (j > c + 1 && j < N) {
+        __hip_atomic_store(zn + 2 * j + (t & 1), kTriEmpty, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(an + 2 * j + (t & 1), kTriEmpty, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+    yu = double2{0.0, 0.0};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) yu = cadd(yu, double2{yupart[w][0], yupart[w][1]});
+    const double2 a2 = cscale(yu, -0.5 * (h.tau.x * h.tau.x + h.tau.y * h.tau.y));
+    const double2 wn = cadd(cmul(h.tau, ynext_s), a2);  // w[c + 1] (u[c + 1] = 1)
+    double wx[R], wy[R];
+#pragma unroll
+    for (int p = 0; p < R; ++p) {
+      const double2 u{ur[p], ui[p]};
+      const double2 w = cadd(cmul(h.tau, double2{yx[p], yy[p]}), cmul(a2, u));
+      wx[p] = w.x;
+      wy[p] = w.y;
+      const double2 x = csub(double2{cx[p], cy[p]}, cadd(cmul(u, conj2(wn)), w));
+      xr[p] = x.x;
+      xi[p] = x.y;
+      if (t + T * p == c + 2) alpha_s = x;
+    }
+#pragma unroll
+    for (int q = 0; q < C; ++q) {
+      if (g + G * q <= c + 1) continue;  // columns done with
+      const double2 uq = uown[q], wq = cadd(cmul(h.tau, yown[q]), cmul(a2, uq));
+#pragma unroll
+      for (int p = 0; p < R; ++p) {
+        if (T * (p + 1) <= c + 1) continue;
+        // u conj(wq) + w conj(uq)
+        ax[q][p] -= ur[p] * wq.x + ui[p] * wq.y + wx[p] * uq.x + wy[p] * uq.y;
+        ay[q][p] -= ui[p] * wq.x - ur[p] * wq.y + wy[p] * uq.x - wx[p] * uq.y;
+      }
+    }
+  }
+  // the last diagonal entry (the owner of column N - 1 alone gets here when N > 1)
+#pragma unroll
+  for (int p = 0; p < R; ++p)
+    if (t + T * p == N - 1 && (N > 1 || g == 0)) d[c0 + N - 1] = xr[p];
+}
+
+// Launches tri_reg_kernel on A[c0:, c0:]; false (nothing launched) when the
+// device cannot hold all its workgroups at once.
+bool launch_tri_reg(int64_t m, double2 *A, int64_t lda, int64_t c0, const double2 *xv, double *d,
+                    double *e, double2 *tau, unsigned long long *xch, int *dead, hipStream_t st) {
+  const int64_t n = m - c0;
+  const unsigned groups = nblk(n, kTriRegC);
+  const void *f = n <= kTriRegT       ? reinterpret_cast<const void *>(tri_reg_kernel<1>)
+                  : n <= 2 * kTriRegT ? reinterpret_cast<const void *>(tri_reg_kernel<2>)
+                                      : reinterpret_cast<const void *>(tri_reg_kernel<kTriRegR>);
+  hipLaunchKernelGGL(tri_clear_kernel, dim3(nblk(tri_words(n), 256)), dim3(256), 0, st,
+                     tri_words(n), xch, dead);
+  void *args[] = {&m, &A, &lda, &c0, &xv, &d, &e, &tau, &xch, &dead};
+  const hipError_t r = hipLaunchCooperativeKernel(f, dim3(groups), dim3(kTriRegT), args, 0, st);
+  if (r == hipSuccess) return true;
+  (void)hipGetLastError();
+  if (r == hipErrorCooperativeLaunchTooLarge || r == hipErrorNotSupported) return false;
+  throw Error{ABI_ERR_DEVICE, std::string("cooperative launch: ") + hipGetErrorString(r)};
 }
 
 // ---------------------------------------------------------------- bisection --
@@ -1094,7 +1449,8 @@ size_t zheev_work_bytes(int64_t m) {
   // arrays and pivots (m x 64 per wave each), and the blocked
   // back-transformation's V (m x nb), G, T (nb x nb), W1, W2 (nb x m)
   const size_t nb = kBtBlock;
-  const size_t tri = 4 * kTriNB * (size_t)m + 3 * (size_t)m + 2 * kTriNB * nblk(m, kTriRows);
+  const size_t tri = 4 * kTriNB * (size_t)m + 3 * (size_t)m + 2 * kTriNB * nblk(m, kTriRows) +
+                     tri_words(std::min<int64_t>(m, kTriRegT * kTriRegR)) / 2 + 1;
   const size_t lane_slab = (size_t)m * 64 * (size_t)((m + 63) / 64);
   // (above kLdsInvitM the clusters' arrays take a global slab per possible leader)
   const size_t invit_slabs = m > kLdsInvitM ? (size_t)m * invit_bytes(m) : 0;
@@ -1102,11 +1458,18 @@ size_t zheev_work_bytes(int64_t m) {
          sizeof(double2) * tri +
          sizeof(double) * (size_t)m * m + (5 * sizeof(double) + 1) * lane_slab +
          sizeof(double2) * ((3 + kBtSplits) * nb * (size_t)m + 2 * nb * nb) + invit_slabs +
-         28 * 256;  // each of the (at most 28) sub-buffers is rounded up to 256 bytes
+         30 * 256;  // each of the (at most 30) sub-buffers is rounded up to 256 bytes
 }
 
-void zheev(int64_t m, void *Av, int64_t lda, double *wout, void *Zv, int64_t ldz, void *work,
-           hipStream_t st) {
+void zheev_check(const int *dead) {
+  if (!dead) return;
+  int v = 0;
+  CHEBFI_HIP(hipMemcpy(&v, dead, sizeof(int), hipMemcpyDeviceToHost));
+  if (v != 0) throw Error{ABI_ERR_DEVICE, "tridiagonalisation: a workgroup waited in vain"};
+}
+
+const int *zheev(int64_t m, void *Av, int64_t lda, double *wout, void *Zv, int64_t ldz, void *work,
+                 hipStream_t st) {
   CHEBFI_REQUIRE(m >= 1 && m <= kEigMaxM, ABI_ERR_ARG, "eigensolver size out of range");
   double2 *A = (double2 *)Av;
   double2 *Z = (double2 *)Zv;
@@ -1132,15 +1495,18 @@ void zheev(int64_t m, void *Av, int64_t lda, double *wout, void *Zv, int64_t ldz
   double2 *yupart = (double2 *)take(sizeof(double2) * m);
   double *normpart = (double *)take(sizeof(double) * nblk(m, kTriRows));
   double2 *stpart = (double2 *)take(sizeof(double2) * 2 * kTriNB * (size_t)nblk(m, kTriRows));
+  const int64_t nreg = std::min<int64_t>(m, kTriRegT * kTriRegR);
+  unsigned long long *xch = (unsigned long long *)take(8 * tri_words(nreg));
+  int *dead = (int *)take(sizeof(int));
   double *S = (double *)take(sizeof(double) * (size_t)m * m);
   const size_t lane_slab = (size_t)m * 64 * nblk(m, 64);  // per array, all waves
   double *lwork = (double *)take(sizeof(double) * 5 * lane_slab);
   unsigned char *lswp = (unsigned char *)take(lane_slab);
 
   launch_hermitize(m, A, lda, st);
-  // reduction to tridiagonal form: two launches per column, and per panel of
-  // kTriNB columns one GEMM update of the trailing matrix and one copy of the
-  // next panel's first column
+  // reduction to tridiagonal form: panels of kTriNB columns (two launches per
+  // column, one GEMM update of the trailing matrix and one copy of the next panel's
+  // first column) until the trailing matrix fits the registers, then one launch
   hipLaunchKernelGGL(tri_start_kernel, dim3(nblk(m, kTriRows)), dim3(64), 0, st, m, A, lda,
                      int64_t{0}, xv, d, normpart);
   int64_t j0 = 0;
@@ -1151,10 +1517,16 @@ void zheev(int64_t m, void *Av, int64_t lda, double *wout, void *Zv, int64_t ldz
     hipLaunchKernelGGL(tri_start_kernel, dim3(nblk(L, kTriRows)), dim3(64), 0, st, m, A, lda, c,
                        xv, d, normpart);
   };
+  bool whole = false;  // the rest of the reduction ran in registers
   for (int64_t c = 0; c + 1 < m; ++c) {
     if (c == j0 + kTriNB) {
       panel_update(c);
       j0 = c;
+    }
+    if (c == j0 && m - c <= kTriRegT * kTriRegR && m - c <= (int64_t)kTriRegC * device_cus() &&
+        launch_tri_reg(m, A, lda, c, xv, d, e, tau, xch, dead, st)) {
+      whole = true;
+      break;
     }
     const int k = (int)(c - j0);
     const int64_t L = m - c - 1;
@@ -1166,7 +1538,7 @@ void zheev(int64_t m, void *Av, int64_t lda, double *wout, void *Zv, int64_t ldz
     hipLaunchKernelGGL(tri_fin_kernel, dim3(nrb), dim3(kTriFinT), 0, st, m, A, lda, c, k, next,
                        nrb, P1, Q, yv, yupart, stpart, tau, xv, d, normpart);
   }
-  if (m >= 2 && m - 1 == j0 + kTriNB) panel_update(m - 1);  // the last diagonal entry
+  if (!whole && m >= 2 && m - 1 == j0 + kTriNB) panel_update(m - 1);  // the last diagonal entry
   CHEBFI_HIP(hipGetLastError());
   // eigenvalues of the tridiagonal
   hipLaunchKernelGGL(tri_prep_kernel, dim3(1), dim3(256), 0, st, m, d, e, e2, stats);
@@ -1240,6 +1612,7 @@ void zheev(int64_t m, void *Av, int64_t lda, double *wout, void *Zv, int64_t ldz
     }
   }
   CHEBFI_HIP(hipGetLastError());
+  return whole ? dead : nullptr;
 }
 
 }  // namespace chebfi

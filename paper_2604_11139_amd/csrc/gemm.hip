@@ -268,7 +268,7 @@ void launch_t(int64_t m, int64_t n, int64_t k, const void *A, int64_t lda, const
 }  // namespace
 
 // Compute units of the current device (cached per device).
-static int device_cus() {
+int device_cus() {
   static int cus[64] = {0};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;

@@ -116,6 +116,8 @@ void rr_rotate_planes(int64_t npw, int64_t m, const void *Apl, int64_t lda, cons
 void proj_gemv(int64_t npw, int nproj, const void *P, const void *x, void *c, hipStream_t st);
 void expand_gemv(int64_t npw, int nproj, const void *P, const void *c, void *out, hipStream_t st);
 
+// Compute units of the current device.
+int device_cus();
 // Number of K splits that fills the chip for an m x n output (fewest: with at
 // least 512 K per chunk).
 int zgemm_splits(int64_t m, int64_t n, int64_t k, bool fewest = false);
@@ -241,8 +243,11 @@ size_t zpotrf_work_bytes(int64_t m);
 void ztrtri_upper(int64_t m, void *A, int64_t lda, void *work, hipStream_t st);
 size_t ztrtri_work_bytes(int64_t m);
 // Hermitian eigensolver: A (m x m, overwritten) -> w ascending, Z.
-void zheev(int64_t m, void *A, int64_t lda, double *w, void *Z, int64_t ldz, void *work,
-           hipStream_t st);
+// Returns a device flag in `work` (or null) to hand to zheev_check once the stream
+// has drained: it throws if a workgroup of the reduction gave up waiting.
+const int *zheev(int64_t m, void *A, int64_t lda, double *w, void *Z, int64_t ldz, void *work,
+                 hipStream_t st);
+void zheev_check(const int *flag);
 size_t zheev_work_bytes(int64_t m);
 
 // Threads per workgroup that one Stockham stage over npen pencils of the plan needs

@@ -52,9 +52,11 @@ bool ortho_rr_basis(abi_system_s *s, int64_t k, int64_t mout, const double2 *Z,
   zgemm(OP_C, OP_N, k, k, k, G, k, T, k, Hs, k, double2{1, 0}, double2{0, 0}, st);
   s->prof.end(tok, st);
   tok = s->prof.begin(PROF_EIG, 16.0 / 3.0 * (double)k * k * k, st);
-  zheev(k, Hs, k, w_dev, Y, k, s->eig1.get(zheev_work_bytes(k)), st);
+  const int *flag = zheev(k, Hs, k, w_dev, Y, k, s->eig1.get(zheev_work_bytes(k)), st);
   s->prof.end(tok, st);
   zgemm(OP_N, OP_N, k, mout, k, G, k, Y, k, C, k, double2{1, 0}, double2{0, 0}, st);
+  CHEBFI_HIP(hipStreamSynchronize(st));
+  zheev_check(flag);
   return true;
 }
 
