@@ -54,12 +54,42 @@ __device__ __forceinline__ void upper_tile(int64_t t, int64_t &ti, int64_t &tj) 
   ti = t - j * (j + 1) / 2;
 }
 
+// Tile of this workgroup in the grid (tiles along x = rows, y = columns,
+// z = K chunks).  Workgroups are handed to the eight XCDs round robin by linear
+// id, so the first 8*floor(T/8) ids are remapped to give each XCD one
+// contiguous range of a linear tile order (the rest keep their id).  That order
+// runs over K chunks slowest, then over groups of `gm` row panels; within a
+// group the row panel varies fastest, then the column.  The workgroups an XCD
+// runs together then share a few A and B panels in its L2.
+__device__ __forceinline__ void grouped_tile(unsigned gm, unsigned &tm, unsigned &tn,
+                                             unsigned &tz) {
+  const unsigned ntm = gridDim.x, ntn = gridDim.y;
+  const unsigned lid = blockIdx.x + ntm * (blockIdx.y + ntn * blockIdx.z);
+  const unsigned q = (ntm * ntn * gridDim.z) >> 3;
+  const unsigned L = lid < 8u * q ? (lid & 7u) * q + (lid >> 3) : lid;
+  const unsigned per_z = ntm * ntn;
+  tz = L / per_z;
+  const unsigned r = L - tz * per_z;
+  const unsigned g = r / (gm * ntn);
+  const unsigned rows = min(gm, ntm - g * gm);
+  const unsigned rr = r - g * gm * ntn;
+  tm = g * gm + rr % rows;
+  tn = rr / rows;
+}
+
 // TAG only separates instantiations (1 = projector products of the H
 // application) so that kernel traces report them apart from the dense ones.
 // TRI: square product known to be Hermitian; the 1-D grid enumerates only the
 // tiles on and above the diagonal (the split-K sum mirrors the rest).
+// Three workgroups per CU (168 registers; the epilogue's operands had cost the
+// unsplit form the third): with two, a SIMD's matrix core idles whenever both its
+// waves are between barriers.  At 115313 x 2048 x 864 the expansion went from 28.3
+// to 26.3 ms with the third and to 24.1 with the tile order below (57.6 -> 67.8
+// TFLOP/s), the projection stays at 26.0 (62.8); two LDS stages with one barrier
+// per step (66 KB, two per CU) took 27.1 and 27.0, raised wave priority around the
+// MFMAs 27.0 and 27.4.
 template <typename T, int OPA, int OPB, bool SPLIT, int TAG, bool TRI = false>
-__global__ __launch_bounds__(256) void zgemm_kernel(int64_t m, int64_t n, int64_t k,
+__global__ __launch_bounds__(256, 3) void zgemm_kernel(int64_t m, int64_t n, int64_t k,
                                                     const C2<T> *__restrict__ A, int64_t lda,
                                                     const C2<T> *__restrict__ B, int64_t ldb,
                                                     C2<T> *__restrict__ C, int64_t ldc,
@@ -72,7 +102,18 @@ __global__ __launch_bounds__(256) void zgemm_kernel(int64_t m, int64_t n, int64_
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int wm = wave & 1, wn = wave >> 1;
-  int64_t row0 = (int64_t)blockIdx.x * BM, col0 = (int64_t)blockIdx.y * BN;
+  int64_t row0, col0;
+  unsigned tz = blockIdx.z;
+  if constexpr (!TRI) {
+    // groups of 16 row panels: the some 96 workgroups an XCD runs together share
+    // 16 A and 6 B panels in its L2 (row panel fastest over the whole grid, each
+    // XCD taking every eighth tile, they shared none: 4 TB/s of operand traffic)
+    // (not worth its divisions, about 1 us, when one round holds all tiles)
+    unsigned tm = blockIdx.x, tn = blockIdx.y;
+    if (gridDim.x * gridDim.y * gridDim.z > 512) grouped_tile(16, tm, tn, tz);
+    row0 = (int64_t)tm * BM;
+    col0 = (int64_t)tn * BN;
+  }
   if constexpr (TRI) {
     static_assert(BM == BN, "square tiles");
     int64_t ti, tj;
@@ -80,7 +121,7 @@ __global__ __launch_bounds__(256) void zgemm_kernel(int64_t m, int64_t n, int64_
     row0 = ti * BM;
     col0 = tj * BN;
   }
-  const int64_t kbeg = (int64_t)blockIdx.z * kchunk;
+  const int64_t kbeg = (int64_t)tz * kchunk;
   const int64_t kend = (kbeg + kchunk < k) ? kbeg + kchunk : k;
 
   Acc acc_re[2][2], acc_im[2][2];
@@ -190,7 +231,7 @@ __global__ __launch_bounds__(256) void zgemm_kernel(int64_t m, int64_t n, int64_
         if (row < m && col < n) {
           const V2 v{acc_re[si][sj][r], acc_im[si][sj][r]};
           if (SPLIT) {
-            part[(int64_t)blockIdx.z * m * n + row + col * m] = v;
+            part[(int64_t)tz * m * n + row + col * m] = v;
           } else {
             const V2 al{(T)alpha.x, (T)alpha.y};
             V2 o = cmul(al, v);
@@ -784,29 +825,6 @@ __global__ __launch_bounds__(64 * NWM * NWN) void zgemm_pl_kernel(
           }
         }
       }
-}
-
-// Tile of this workgroup in the grid (tiles along x = rows, y = columns,
-// z = K chunks).  Workgroups are handed to the eight XCDs round robin by linear
-// id, so the first 8*floor(T/8) ids are remapped to give each XCD one
-// contiguous range of a linear tile order (the rest keep their id).  That order
-// runs over K chunks slowest, then over groups of `gm` row panels; within a
-// group the row panel varies fastest, then the column.  The workgroups an XCD
-// runs together then share a few A and B panels in its L2.
-__device__ __forceinline__ void grouped_tile(unsigned gm, unsigned &tm, unsigned &tn,
-                                             unsigned &tz) {
-  const unsigned ntm = gridDim.x, ntn = gridDim.y;
-  const unsigned lid = blockIdx.x + ntm * (blockIdx.y + ntn * blockIdx.z);
-  const unsigned q = (ntm * ntn * gridDim.z) >> 3;
-  const unsigned L = lid < 8u * q ? (lid & 7u) * q + (lid >> 3) : lid;
-  const unsigned per_z = ntm * ntn;
-  tz = L / per_z;
-  const unsigned r = L - tz * per_z;
-  const unsigned g = r / (gm * ntn);
-  const unsigned rows = min(gm, ntm - g * gm);
-  const unsigned rr = r - g * gm * ntn;
-  tm = g * gm + rr % rows;
-  tn = rr / rows;
 }
 
 // Double-buffered form of the planes x planes kernel: two LDS stages of
