@@ -507,7 +507,7 @@ int rr_lowprec(abi_system_s *s, void *Y, int64_t ld, void *HPsi, int64_t ldh_in,
   float2 *Ye = (float2 *)s->blk4.get(blk);
   float2 *spare = (float2 *)s->blk1.get(blk);
   const int64_t ldm = (M + 31) / 32 * 32;
-  const int splits = proj_planes_splits(7, M, M, npw);
+  const int splits = rr_gram_splits(M, npw);
   const double gflops = 8.0 * (double)M * M * npw;
   // (own planes buffer: a planes variant of the H application reuses s->planes)
   void *ypl = s->rr_planes.get(8 * (size_t)s->ldPA * M);
@@ -519,10 +519,8 @@ int rr_lowprec(abi_system_s *s, void *Y, int64_t ld, void *HPsi, int64_t ldh_in,
     split_planes(npw, M, B, npw, ypl, s->ldPA, st);
     part = s->cpart.get(sizeof(float2) * (size_t)splits * M * M);
     int tok = s->prof.begin(PROF_GRAM, gflops, st);
-    rr_gram_f32(M, npw, ypl, s->ldPA, B, npw, part, splits, st);
-    launch_parts_to_c128(M, M, part, splits, true, G, st);
+    rr_gram_f32(M, npw, ypl, s->ldPA, B, npw, part, splits, G, st);
     s->prof.end(tok, st);
-    launch_hermitize(M, G, M, st);
     tok = s->prof.begin(PROF_CHOL, 4.0 / 3.0 * (double)M * M * M, st);
     zpotrf_upper(M, G, M, info, nullptr, st);
     s->prof.end(tok, st);
@@ -575,10 +573,8 @@ int rr_lowprec(abi_system_s *s, void *Y, int64_t ld, void *HPsi, int64_t ldh_in,
   // (ypl still holds the planes of Ye from its Gram matrix)
   part = s->cpart.get(sizeof(float2) * (size_t)splits * M * M);  // apply_core may regrow it
   int tok = s->prof.begin(PROF_GRAM, gflops, st);
-  rr_gram_f32(M, npw, ypl, s->ldPA, HYe, npw, part, splits, st);
-  launch_parts_to_c128(M, M, part, splits, true, Hs, st);
+  rr_gram_f32(M, npw, ypl, s->ldPA, HYe, npw, part, splits, Hs, st);
   s->prof.end(tok, st);
-  launch_hermitize(M, Hs, M, st);
   tok = s->prof.begin(PROF_CHOL, 16.0 * (double)M * M * M, st);
   ztrtri_upper(M, G, M, trw, st);
   zgemm(OP_N, OP_N, M, M, M, Hs, M, G, M, T, M, double2{1, 0}, double2{0, 0}, st);
@@ -658,7 +654,6 @@ void rr_core(abi_system_s *s, double2 *Y, int64_t ld, double2 *HPsi, int64_t ldh
   int tok = s->prof.begin(PROF_GRAM, gflops, st);
   zgemm_herm(M, npw, Y, ld, SY, lds, G, M, st, part, splits);
   s->prof.end(tok, st);
-  launch_hermitize(M, G, M, st);
   tok = s->prof.begin(PROF_CHOL, 4.0 / 3.0 * (double)M * M * M, st);
   zpotrf_upper(M, G, M, info, nullptr, st);
   s->prof.end(tok, st);
@@ -675,7 +670,6 @@ void rr_core(abi_system_s *s, double2 *Y, int64_t ld, double2 *HPsi, int64_t ldh
   tok = s->prof.begin(PROF_GRAM, gflops, st);
   zgemm_herm(M, npw, Y, ld, HY, npw, Hs, M, st, part, splits);
   s->prof.end(tok, st);
-  launch_hermitize(M, Hs, M, st);
   // U^-1 and the reduced matrix U^-H H_s U^-1
   tok = s->prof.begin(PROF_CHOL, 16.0 * (double)M * M * M, st);
   void *trw = s->eig2.get(ztrtri_work_bytes(M));

@@ -104,12 +104,15 @@ void expand_gemm_planes(int64_t npw, int64_t nband, int64_t nproj, const void *A
                         int64_t psa, const void *Cpl, int64_t ldc_pl, int64_t psc, void *Out,
                         int64_t ldo, hipStream_t st, int variant, bool accumulate = true);
 // Split-BF16 products of the Rayleigh-Ritz step (FP32 accumulation):
-// part[z] = Y_pl^H Y over plane-wave chunk z (m x m per chunk; the planes of
-// Y_pl zero-padded to a multiple of 32, ld lda, Y complex64 with ld ldy), and
+// G = Y_pl^H Y (m x m complex double, ld m) for a product known to be Hermitian:
+// the 128 x 128 tiles on and above the diagonal in `splits` plane-wave chunks
+// (part: splits x m x m complex float), the rest mirrored (the planes of Y_pl
+// zero-padded to a multiple of 32, ld lda, Y complex64 with ld ldy), and
 // Out = A T from the transposed planes of A (npw x m, ld lda) and the planes of
 // T (m x m, ld ldt), both zero-padded along m.
+int rr_gram_splits(int64_t m, int64_t npw);
 void rr_gram_f32(int64_t m, int64_t npw, const void *Apl, int64_t lda, const void *Y,
-                 int64_t ldy, void *part, int splits, hipStream_t st);
+                 int64_t ldy, void *part, int splits, void *G, hipStream_t st);
 void rr_rotate_planes(int64_t npw, int64_t m, const void *Apl, int64_t lda, const void *Tpl,
                       int64_t ldt, void *Out, int64_t ldo, hipStream_t st);
 // Single-band forms: c = P^H x, out += P c.

@@ -34,7 +34,6 @@ bool ortho_rr_basis(abi_system_s *s, int64_t k, int64_t mout, const double2 *Z,
   int tok = s->prof.begin(PROF_GRAM, gflops, st);
   zgemm_herm(k, npw, Z, ld, SZ, ld, G, k, st, part, splits);
   s->prof.end(tok, st);
-  launch_hermitize(k, G, k, st);
   tok = s->prof.begin(PROF_CHOL, 4.0 / 3.0 * (double)k * k * k, st);
   zpotrf_upper(k, G, k, info, nullptr, st);
   s->prof.end(tok, st);
@@ -45,7 +44,6 @@ bool ortho_rr_basis(abi_system_s *s, int64_t k, int64_t mout, const double2 *Z,
   tok = s->prof.begin(PROF_GRAM, gflops, st);
   zgemm_herm(k, npw, Z, ld, HZ, ld, Hs, k, st, part, splits);
   s->prof.end(tok, st);
-  launch_hermitize(k, Hs, k, st);
   tok = s->prof.begin(PROF_CHOL, 16.0 * (double)k * k * k, st);
   ztrtri_upper(k, G, k, s->eig2.get(ztrtri_work_bytes(k)), st);
   zgemm(OP_N, OP_N, k, k, k, Hs, k, G, k, T, k, double2{1, 0}, double2{0, 0}, st);

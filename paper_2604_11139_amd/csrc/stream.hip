@@ -380,19 +380,36 @@ __global__ void scale_rows_kernel(int64_t m, int64_t n, double2 *__restrict__ A,
   a.y *= sc[k];
 }
 
-__global__ void hermitize_kernel(int64_t m, double2 *__restrict__ A, int64_t lda) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= m * m) return;
-  const int64_t i = idx % m, j = idx / m;
-  if (i > j) return;
-  if (i == j) {
-    A[i + j * lda].y = 0.0;
-    return;
+// 32 x 32 blocks (bi <= bj, blockIdx.x in column order of the upper triangle) and
+// their mirrors through LDS: both are read and written along columns (element by
+// element, the mirrored half went one 16-byte word per cache line).
+__global__ __launch_bounds__(256) void hermitize_kernel(int64_t m, double2 *__restrict__ A,
+                                                        int64_t lda) {
+  __shared__ double2 t[32][33], u[32][33];
+  int64_t bj = (int64_t)((sqrt(8.0 * (double)blockIdx.x + 1.0) - 1.0) * 0.5);
+  while ((bj + 1) * (bj + 2) / 2 <= (int64_t)blockIdx.x) ++bj;
+  while (bj * (bj + 1) / 2 > (int64_t)blockIdx.x) --bj;
+  const int64_t bi = (int64_t)blockIdx.x - bj * (bj + 1) / 2;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  const int64_t i = bi * 32 + tx, j = bj * 32 + tx;
+  for (int c = ty; c < 32; c += 8) {
+    const int64_t ci = bi * 32 + c, cj = bj * 32 + c;
+    if (i < m && cj < m) t[c][tx] = A[i + cj * lda];  // (i, cj)
+    if (j < m && ci < m) u[c][tx] = A[j + ci * lda];  // (j, ci)
   }
-  const double2 a = A[i + j * lda], b = A[j + i * lda];
-  const double2 v{0.5 * (a.x + b.x), 0.5 * (a.y - b.y)};
-  A[i + j * lda] = v;
-  A[j + i * lda] = double2{v.x, -v.y};
+  __syncthreads();
+  for (int c = ty; c < 32; c += 8) {
+    const int64_t ci = bi * 32 + c, cj = bj * 32 + c;
+    if (i < m && cj < m) {
+      const double2 a = t[c][tx], b = u[tx][c];
+      A[i + cj * lda] =
+          i == cj ? double2{a.x, 0.0} : double2{0.5 * (a.x + b.x), 0.5 * (a.y - b.y)};
+    }
+    if (bi < bj && j < m && ci < m) {
+      const double2 a = t[tx][c], b = u[c][tx];
+      A[j + ci * lda] = double2{0.5 * (a.x + b.x), 0.5 * (b.y - a.y)};
+    }
+  }
 }
 
 template <typename V2>
@@ -893,7 +910,8 @@ void launch_scale_rows(int64_t m, int64_t n, void *A, int64_t lda, const double 
 }
 
 void launch_hermitize(int64_t m, void *A, int64_t lda, hipStream_t st) {
-  hipLaunchKernelGGL(hermitize_kernel, dim3(nblk(m * m, 256)), dim3(256), 0, st, m,
+  const int64_t nb = (m + 31) / 32;
+  hipLaunchKernelGGL(hermitize_kernel, dim3((unsigned)(nb * (nb + 1) / 2)), dim3(256), 0, st, m,
                      (double2 *)A, lda);
   CHEBFI_HIP(hipGetLastError());
 }
