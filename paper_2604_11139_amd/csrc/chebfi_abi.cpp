@@ -1935,13 +1935,14 @@ abi_status abi_zpotrf_upper(int64_t m, void *A, int64_t lda, void *stream) {
   return guarded([&] {
     CHEBFI_REQUIRE(m >= 1 && A != nullptr && lda >= m, ABI_ERR_ARG, "bad matrix arguments");
     hipStream_t st = S(stream);
-    int *info = nullptr;
-    CHEBFI_HIP(hipMalloc(&info, sizeof(int)));
-    zpotrf_upper(m, A, lda, info, nullptr, st);
+    char *work = nullptr;
+    CHEBFI_HIP(hipMalloc(&work, zpotrf_work_bytes(m) + sizeof(int)));
+    int *info = (int *)(work + zpotrf_work_bytes(m));
+    zpotrf_upper(m, A, lda, info, work, st);
     int h = 0;
     CHEBFI_HIP(hipMemcpyAsync(&h, info, sizeof(int), hipMemcpyDeviceToHost, st));
     CHEBFI_HIP(hipStreamSynchronize(st));
-    (void)hipFree(info);
+    (void)hipFree(work);
     if (h != 0) throw Error{ABI_ERR_NOT_HPD, "not positive definite at pivot " + std::to_string(h)};
   });
 }

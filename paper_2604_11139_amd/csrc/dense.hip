@@ -7,9 +7,10 @@
 // rooflines").  Here every step is a hand-written kernel:
 //
 // * Cholesky A = U^H U: right-looking blocked, 32-column diagonal blocks
-//   factored in LDS by one workgroup, the panel solved column-parallel and the
-//   trailing matrix updated by the MFMA GEMM;
-// * U^-1: blocked, diagonal blocks inverted in LDS, off-diagonal panels by GEMM;
+//   factored and their factors inverted by one workgroup, the panel multiplied by
+//   the inverse and the trailing matrix updated by the MFMA GEMM;
+// * U^-1: 32-column diagonal blocks inverted, then pairs of blocks merged by
+//   batched GEMMs, doubling the size;
 // * Hermitian eigensolver: Householder reduction to real symmetric tridiagonal
 //   form (reflectors H = I - tau u u^H with a real sub-diagonal, applied from
 //   both sides as rank-2 updates; matrices up to 2048 are reduced by one launch
@@ -39,7 +40,6 @@ constexpr int kLdsInvitM = 2560; // clusters' inverse iteration in LDS up to thi
 constexpr int kBtBlock = 64;     // reflectors per block of the back-transformation
 constexpr int kBtMinM = 96;      // smaller problems apply the reflectors one at a time
 constexpr int kBtSplits = 8;     // most K chunks of the V^H Z product
-constexpr int kBtGSplits = 64;   // most K chunks of the V^H V product
 
 __device__ __forceinline__ double wave_sum(double v) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
@@ -81,75 +81,120 @@ __device__ double2 block_sum2(double2 v, double *scratch) {
 inline unsigned nblk(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 
 // ---------------------------------------------------------------- Cholesky --
-// Factor the nb x nb diagonal block at (j0, j0) in LDS (upper, A = U^H U).
-__global__ __launch_bounds__(256) void potrf_diag_kernel(int nb, double2 *__restrict__ A, int64_t lda, int64_t j0,
-                                  int *__restrict__ info) {
-  __shared__ double2 a[NB][NB + 1];  // a[i][j] = A(j0+i, j0+j)
-  const int t = threadIdx.x;
-  for (int idx = t; idx < NB * NB; idx += blockDim.x) {
-    const int i = idx % NB, j = idx / NB;
-    if (i < nb && j < nb) a[i][j] = A[(j0 + i) + (j0 + j) * lda];
-  }
-  __syncthreads();
-  for (int k = 0; k < nb; ++k) {
-    const double dkk = a[k][k].x;
-    const bool bad = !(dkk > 0.0);
-    const double dk = bad ? 1.0 : sqrt(dkk);
-    __syncthreads();
-    if (t == 0) {
-      if (bad && *info == 0) *info = (int)(j0 + k + 1);
-      a[k][k] = double2{dk, 0.0};
-    }
-    for (int j = k + 1 + t; j < nb; j += blockDim.x) a[k][j] = cscale(a[k][j], 1.0 / dk);
-    __syncthreads();
-    for (int idx = t; idx < NB * NB; idx += blockDim.x) {
-      const int i = idx % NB, j = idx / NB;
-      if (i > k && j >= i && j < nb) {
-        const double2 u = a[k][i], v = a[k][j];
-        const double2 cu{u.x, -u.y};
-        a[i][j] = csub(a[i][j], cmul(cu, v));
+// The 32 x 32 kernels are serial chains of 32 steps; what bounds them is the length
+// of a step.  256 threads: thread (column j = t & 31, group g = t >> 5) holds rows
+// g + 8 r in registers, so a step is the owner group's row through LDS, one barrier
+// and four multiply-adds a thread (two LDS buffers take turns).
+
+// x <- the inverse of the upper triangular u (LDS, entries past nb those of the
+// identity), back substitution from the last row: x[r] = row g + 8 r, column j.
+__device__ __forceinline__ void invert_upper32(const double2 (&u)[NB][NB + 1],
+                                               double2 (&row)[2][NB], int j, int g,
+                                               double2 (&x)[NB / 8]) {
+#pragma unroll
+  for (int r = 0; r < NB / 8; ++r) x[r] = double2{g + 8 * r == j ? 1.0 : 0.0, 0.0};
+#pragma unroll
+  for (int r = NB / 8 - 1; r >= 0; --r)
+    for (int q = 7; q >= 0; --q) {
+      const int k = 8 * r + q;
+      if (g == q) {
+        const double2 d = u[k][k];
+        const double den = 1.0 / (d.x * d.x + d.y * d.y);
+        x[r] = cscale(cmul(x[r], double2{d.x, -d.y}), den);
+        row[k & 1][j] = x[r];
+      }
+      __syncthreads();
+      const double2 xk = row[k & 1][j];
+#pragma unroll
+      for (int p = 0; p <= r; ++p) {
+        const int i = g + 8 * p;
+        if (i < k) x[p] = csub(x[p], cmul(u[i][k], xk));
       }
     }
-    __syncthreads();
-  }
-  for (int idx = t; idx < NB * NB; idx += blockDim.x) {
-    const int i = idx % NB, j = idx / NB;
-    if (i <= j && j < nb) A[(j0 + i) + (j0 + j) * lda] = a[i][j];
-  }
 }
 
-// U12 = U11^-H A12 for the panel rows j0..j0+nb-1, columns j1..m-1.
-__global__ __launch_bounds__(64) void potrf_panel_kernel(int nb, int64_t m, double2 *__restrict__ A, int64_t lda,
-                                   int64_t j0) {
+// The nb x nb diagonal block at (j0, j0): its factor (upper, A = U^H U) in place and
+// the factor's inverse in W (column-major, ld NB).
+__global__ __launch_bounds__(256) void potrf_diag_kernel(int nb, double2 *__restrict__ A,
+                                                         int64_t lda, int64_t j0,
+                                                         int *__restrict__ info,
+                                                         double2 *__restrict__ W) {
   __shared__ double2 u[NB][NB + 1];
-  const int t = threadIdx.x;
-  for (int idx = t; idx < nb * nb; idx += blockDim.x) {
-    const int i = idx % nb, j = idx / nb;
-    u[i][j] = A[(j0 + i) + (j0 + j) * lda];
+  __shared__ double2 row[2][NB];
+  const int t = threadIdx.x, j = t & 31, g = t >> 5;
+  double2 a[NB / 8];
+#pragma unroll
+  for (int r = 0; r < NB / 8; ++r) {
+    const int i = g + 8 * r;
+    a[r] = double2{i == j ? 1.0 : 0.0, 0.0};
+    if (i <= j && j < nb) a[r] = A[(j0 + i) + (j0 + j) * lda];
+  }
+#pragma unroll
+  for (int r = 0; r < NB / 8; ++r)
+    for (int q = 0; q < 8; ++q) {
+      const int k = 8 * r + q;
+      if (g == q) {  // (a half-wave: the pivot is on its lane k)
+        const double dkk = __shfl(a[r].x, (t & 32) + k, 64);
+        const bool bad = !(dkk > 0.0);
+        const double dk = bad ? 1.0 : sqrt(dkk);
+        a[r] = j == k ? double2{dk, 0.0} : cscale(a[r], 1.0 / dk);
+        row[k & 1][j] = a[r];
+        if (bad && j == 0 && *info == 0) *info = (int)(j0 + k + 1);
+      }
+      __syncthreads();
+      const double2 v = row[k & 1][j];
+#pragma unroll
+      for (int p = r; p < NB / 8; ++p) {
+        const int i = g + 8 * p;
+        const double2 c = row[k & 1][i];
+        if (i > k && i <= j) a[p] = csub(a[p], cmul(double2{c.x, -c.y}, v));
+      }
+    }
+#pragma unroll
+  for (int r = 0; r < NB / 8; ++r) {
+    const int i = g + 8 * r;
+    u[i][j] = a[r];
+    if (i <= j && j < nb) A[(j0 + i) + (j0 + j) * lda] = a[r];
   }
   __syncthreads();
-  const int64_t col = j0 + nb + (int64_t)blockIdx.x * blockDim.x + t;
-  if (col >= m) return;
-  double2 x[NB];
+  double2 x[NB / 8];
+  invert_upper32(u, row, j, g, x);
 #pragma unroll
-  for (int i = 0; i < NB; ++i) x[i] = (i < nb) ? A[(j0 + i) + col * lda] : double2{0, 0};
-#pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    if (i < nb) {
-      double2 s = x[i];
-#pragma unroll
-      for (int k = 0; k < NB; ++k) {
-        if (k < i) {
-          const double2 cu{u[k][i].x, -u[k][i].y};
-          s = csub(s, cmul(cu, x[k]));
-        }
-      }
-      x[i] = cscale(s, 1.0 / u[i][i].x);
-    }
+  for (int r = 0; r < NB / 8; ++r) W[(g + 8 * r) + j * NB] = x[r];
+}
+
+// U12 = W^H A12 (W = U11^-1) for the panel rows j0 .. j0 + 31, 64 columns per
+// workgroup: the product with the inverse has no chain (the solve by columns walked
+// 32 dependent rows: 26 us a launch, 10.6 now).
+__global__ __launch_bounds__(256) void potrf_panel_kernel(int64_t m, double2 *__restrict__ A,
+                                                          int64_t lda, int64_t j0,
+                                                          const double2 *__restrict__ W) {
+  __shared__ double2 w[NB][NB];       // w[i][k] = W(k, i)
+  __shared__ double2 a[NB][64 + 1];
+  const int t = threadIdx.x, c = t & 63, q = t >> 6;
+  const int64_t col0 = j0 + NB + 64 * (int64_t)blockIdx.x, col = col0 + c;
+  for (int idx = t; idx < NB * NB; idx += 256) w[idx / NB][idx % NB] = W[idx];
+  for (int idx = t; idx < NB * 64; idx += 256) {
+    const int k = idx % NB, cc = idx / NB;
+    a[k][cc] = col0 + cc < m ? A[(j0 + k) + (col0 + cc) * lda] : double2{0.0, 0.0};
   }
+  __syncthreads();
+  double2 x[NB / 4];
 #pragma unroll
-  for (int i = 0; i < NB; ++i)
-    if (i < nb) A[(j0 + i) + col * lda] = x[i];
+  for (int r = 0; r < NB / 4; ++r) {
+    const int i = q + 4 * r;
+    double2 s{0.0, 0.0};
+    for (int k = 0; k <= i; ++k) s = cadd(s, cmul(double2{w[i][k].x, -w[i][k].y}, a[k][c]));
+    x[r] = s;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < NB / 4; ++r) a[q + 4 * r][c] = x[r];
+  __syncthreads();
+  for (int idx = t; idx < NB * 64; idx += 256) {
+    const int k = idx % NB, cc = idx / NB;
+    if (col0 + cc < m) A[(j0 + k) + (col0 + cc) * lda] = a[k][cc];
+  }
 }
 
 __global__ void set_int_kernel(int *p, int v) {
@@ -157,45 +202,28 @@ __global__ void set_int_kernel(int *p, int v) {
 }
 
 // ---------------------------------------------------------------- trtri ----
-// Invert the nb x nb upper triangular diagonal block in place (LDS).
-__global__ __launch_bounds__(256) void trtri_diag_kernel(int nb, double2 *__restrict__ A, int64_t lda, int64_t j0) {
-  static_assert(NB == 32, "one lane group of 32 per column block");
-  __shared__ double2 a[NB][NB + 1];
-  __shared__ double2 r[NB][NB + 1];
-  __shared__ double2 part[8][NB];
-  const int t = threadIdx.x;
-  for (int idx = t; idx < NB * NB; idx += blockDim.x) {
-    const int i = idx % NB, j = idx / NB;
-    if (i < nb && j < nb) a[i][j] = (i <= j) ? A[(j0 + i) + (j0 + j) * lda] : double2{0, 0};
+// Inverts every 32 x 32 upper triangular diagonal block in place (one workgroup each).
+__global__ __launch_bounds__(256) void trtri_diag_kernel(int64_t m, double2 *__restrict__ A,
+                                                         int64_t lda) {
+  __shared__ double2 u[NB][NB + 1];
+  __shared__ double2 row[2][NB];
+  const int t = threadIdx.x, j = t & 31, g = t >> 5;
+  const int64_t j0 = (int64_t)blockIdx.x * NB;
+  const int nb = (int)(m - j0 < NB ? m - j0 : NB);
+#pragma unroll
+  for (int r = 0; r < NB / 8; ++r) {
+    const int i = g + 8 * r;
+    double2 v{i == j ? 1.0 : 0.0, 0.0};
+    if (i <= j && j < nb) v = A[(j0 + i) + (j0 + j) * lda];
+    u[i][j] = v;
   }
   __syncthreads();
-  // rows of R = U^-1 from the bottom: R[i][j] = (delta_ij - sum_{i<k<=j} U[i][k] R[k][j]) / U[i][i]
-  // for all j >= i at once; each column's sum is split over 8 groups of 32 threads
-  const int j = t & 31, g = t >> 5;
-  for (int i = nb - 1; i >= 0; --i) {
-    double2 s{0, 0};
-    if (j < nb && j > i)
-      for (int k = i + 1 + g; k <= j; k += 8) s = cadd(s, cmul(a[i][k], r[k][j]));
-    part[g][j] = s;
-    __syncthreads();
-    if (t < nb) {
-      double2 v{0, 0};
-      if (t >= i) {
-        double2 sum{0, 0};
+  double2 x[NB / 8];
+  invert_upper32(u, row, j, g, x);
 #pragma unroll
-        for (int q = 0; q < 8; ++q) sum = cadd(sum, part[q][t]);
-        v = csub((t == i) ? double2{1.0, 0.0} : double2{0, 0}, sum);
-        const double2 d = a[i][i];
-        const double den = d.x * d.x + d.y * d.y;
-        v = double2{(v.x * d.x + v.y * d.y) / den, (v.y * d.x - v.x * d.y) / den};
-      }
-      r[i][t] = v;
-    }
-    __syncthreads();
-  }
-  for (int idx = t; idx < NB * NB; idx += blockDim.x) {
-    const int i = idx % NB, jj = idx / NB;
-    if (i < nb && jj < nb) A[(j0 + i) + (j0 + jj) * lda] = (i <= jj) ? r[i][jj] : double2{0, 0};
+  for (int r = 0; r < NB / 8; ++r) {
+    const int i = g + 8 * r;
+    if (i < nb && j < nb) A[(j0 + i) + (j0 + j) * lda] = i <= j ? x[r] : double2{0.0, 0.0};
   }
 }
 
@@ -1339,17 +1367,12 @@ __global__ __launch_bounds__(256) void load_u_kernel(int64_t m, const double2 *_
   u[i] = (i == j + 1) ? double2{1.0, 0.0} : A[i + j * lda];
 }
 
-// V (Lr x nb, ld Lr) of the reflectors j0 .. j0+nb-1 on rows j0+1 .. m-1:
-// V[i, k] = 0 above row j0+k+1, 1 on it, A[r, j0+k] below (r = j0 + 1 + i).
-__global__ __launch_bounds__(256) void build_v_kernel(int64_t m, const double2 *__restrict__ A,
-                                                      int64_t lda, int64_t j0, int nb,
-                                                      double2 *__restrict__ V) {
-  const int64_t Lr = m - j0 - 1;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= Lr * nb) return;
-  const int64_t i = idx % Lr, k = idx / Lr;
-  const int64_t r = j0 + 1 + i, top = j0 + k + 1;
-  V[idx] = r < top ? double2{0.0, 0.0} : (r == top ? double2{1.0, 0.0} : A[r + (j0 + k) * lda]);
+// The reduced matrix's columns as the reflectors V (m x m, in place): zero above row
+// c + 1, 1 on it, u_c below.
+__global__ __launch_bounds__(256) void clean_v_kernel(int64_t m, double2 *__restrict__ A,
+                                                      int64_t lda) {
+  const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x, c = blockIdx.y;
+  if (r < m && r <= c + 1) A[r + c * lda] = double2{r == c + 1 ? 1.0 : 0.0, 0.0};
 }
 
 // Upper triangular T with H_{j0} H_{j0+1} ... H_{j0+nb-1} = I - V T V^H (forward
@@ -1358,15 +1381,27 @@ __global__ __launch_bounds__(256) void build_v_kernel(int64_t m, const double2 *
 // itself and G; 16 lanes share a row (lane q sums the terms l = i + q (mod 16)
 // and owns the entries T[i][k] with k = i + q (mod 16), the only ones it
 // reads back), the sum completed by shuffles within the 16 lanes.
+// One workgroup per block of reflectors: all T at once (nref reflectors in blocks of
+// kBtBlock), G given as `splits` partials of 64 x 64 per block (part[z][block]).
 constexpr int kLarftLanes = 16;
 __global__ __launch_bounds__(kBtBlock * kLarftLanes) void larft_kernel(
-    int nb, const double2 *__restrict__ G, const double2 *__restrict__ tau,
+    int64_t nref, int splits, const double2 *__restrict__ part, const double2 *__restrict__ tau,
     double2 *__restrict__ T) {
-  __shared__ double2 Gs[kBtBlock * kBtBlock];  // column-major, ld nb
+  __shared__ double2 Gs[kBtBlock * kBtBlock];  // column-major
   __shared__ double2 Tr[kBtBlock * kBtBlock];  // row-major, ld kBtBlock
   __shared__ double2 taus[kBtBlock];
   const int t = threadIdx.x;
-  for (int idx = t; idx < nb * nb; idx += blockDim.x) Gs[idx] = G[idx];
+  const int64_t blk = blockIdx.x;
+  const int nb = (int)(nref - blk * kBtBlock < kBtBlock ? nref - blk * kBtBlock : kBtBlock);
+  tau += blk * kBtBlock;
+  T += blk * kBtBlock * kBtBlock;
+  for (int idx = t; idx < kBtBlock * kBtBlock; idx += blockDim.x) {
+    double2 s{0.0, 0.0};
+#pragma unroll 8
+    for (int z = 0; z < splits; ++z)
+      s = cadd(s, part[((int64_t)z * gridDim.x + blk) * kBtBlock * kBtBlock + idx]);
+    Gs[idx] = s;
+  }
   if (t < nb) taus[t] = tau[t];
   for (int idx = t; idx < kBtBlock * kBtBlock; idx += blockDim.x) Tr[idx] = double2{0.0, 0.0};
   __syncthreads();
@@ -1376,7 +1411,7 @@ __global__ __launch_bounds__(kBtBlock * kLarftLanes) void larft_kernel(
   for (int k = 1; k < nb; ++k) {  // the same trip count on every lane (shuffles below)
     double2 acc{0.0, 0.0};
     if (i < k)
-      for (int l = i + q; l < k; l += kLarftLanes) acc = cadd(acc, cmul(row[l], Gs[l + k * nb]));
+      for (int l = i + q; l < k; l += kLarftLanes) acc = cadd(acc, cmul(row[l], Gs[l + k * kBtBlock]));
     for (int off = kLarftLanes / 2; off > 0; off >>= 1) {
       acc.x += __shfl_xor(acc.x, off, 64);
       acc.y += __shfl_xor(acc.y, off, 64);
@@ -1387,52 +1422,64 @@ __global__ __launch_bounds__(kBtBlock * kLarftLanes) void larft_kernel(
     }
   }
   __syncthreads();
-  for (int idx = t; idx < nb * nb; idx += blockDim.x)
-    T[idx] = Tr[(idx % nb) * kBtBlock + idx / nb];
+  for (int idx = t; idx < kBtBlock * kBtBlock; idx += blockDim.x)
+    T[idx] = Tr[(idx % kBtBlock) * kBtBlock + idx / kBtBlock];
 }
 
 }  // namespace
 
 // ---------------------------------------------------------------- drivers ----
-size_t zpotrf_work_bytes(int64_t) { return 0; }
+size_t zpotrf_work_bytes(int64_t) { return sizeof(double2) * NB * NB; }
 
-void zpotrf_upper(int64_t m, void *Av, int64_t lda, int *info, void *, hipStream_t st) {
-  double2 *A = (double2 *)Av;
+void zpotrf_upper(int64_t m, void *Av, int64_t lda, int *info, void *work, hipStream_t st) {
+  double2 *A = (double2 *)Av, *W = (double2 *)work;  // inverse of the diagonal block's factor
   hipLaunchKernelGGL(set_int_kernel, dim3(1), dim3(64), 0, st, info, 0);
   for (int64_t j0 = 0; j0 < m; j0 += NB) {
     const int nb = (int)std::min<int64_t>(NB, m - j0);
-    hipLaunchKernelGGL(potrf_diag_kernel, dim3(1), dim3(256), 0, st, nb, A, lda, j0, info);
+    hipLaunchKernelGGL(potrf_diag_kernel, dim3(1), dim3(256), 0, st, nb, A, lda, j0, info, W);
     CHEBFI_HIP(hipGetLastError());
     const int64_t rest = m - j0 - nb;
     if (rest > 0) {
-      hipLaunchKernelGGL(potrf_panel_kernel, dim3(nblk(rest, 64)), dim3(64), 0, st, nb, m, A, lda,
-                         j0);
+      hipLaunchKernelGGL(potrf_panel_kernel, dim3(nblk(rest, 64)), dim3(256), 0, st, m, A, lda, j0,
+                         W);
       CHEBFI_HIP(hipGetLastError());
+      // A22 -= U12^H U12, the tiles on and above the diagonal
       double2 *U12 = A + j0 + (j0 + nb) * lda;
-      double2 *A22 = A + (j0 + nb) + (j0 + nb) * lda;
-      zgemm(OP_C, OP_N, rest, rest, nb, U12, lda, U12, lda, A22, lda, double2{-1.0, 0.0},
-            double2{1.0, 0.0}, st);
+      zgemm_herm_update(rest, nb, U12, lda, A + (j0 + nb) + (j0 + nb) * lda, lda, st);
     }
   }
   launch_zero_lower(m, A, lda, st);
 }
 
-size_t ztrtri_work_bytes(int64_t m) { return sizeof(double2) * (size_t)m * NB; }
+size_t ztrtri_work_bytes(int64_t m) {
+  // the largest level's products: pairs of L x L blocks and a ragged one
+  size_t n = 1;
+  for (int64_t L = NB; L < m; L *= 2)
+    n = std::max(n, (size_t)(m / (2 * L) + 1) * (size_t)(L * L));
+  return sizeof(double2) * n;
+}
 
+// Inverse by doubling: the diagonal blocks of 32 at once, then pairs of neighbouring
+// blocks, [A B; 0 C]^-1 = [A^-1, -A^-1 B C^-1; 0, C^-1], all pairs of one size in
+// one batched product.  (One column panel of 32 at a time took two products and a
+// block inverse per panel, most of it a chain of up to 2048 / 16 K steps by a few
+// workgroups: 12.2 ms at 2048 and 1.09 at 512, now 0.70 and 0.19.)
 void ztrtri_upper(int64_t m, void *Av, int64_t lda, void *work, hipStream_t st) {
-  double2 *A = (double2 *)Av;
-  double2 *T = (double2 *)work;  // m x NB
-  for (int64_t j0 = 0; j0 < m; j0 += NB) {
-    const int nb = (int)std::min<int64_t>(NB, m - j0);
-    hipLaunchKernelGGL(trtri_diag_kernel, dim3(1), dim3(256), 0, st, nb, A, lda, j0);
-    CHEBFI_HIP(hipGetLastError());
-    if (j0 > 0) {
-      // A[0:j0, j0:j0+nb] = -Uinv[0:j0,0:j0] * A[0:j0, j0:j0+nb] * Uinv_jj
-      zgemm(OP_N, OP_N, j0, nb, j0, A, lda, A + j0 * lda, lda, T, j0, double2{1.0, 0.0},
-            double2{0.0, 0.0}, st);
-      zgemm(OP_N, OP_N, j0, nb, nb, T, j0, A + j0 + j0 * lda, lda, A + j0 * lda, lda,
-            double2{-1.0, 0.0}, double2{0.0, 0.0}, st);
-    }
+  double2 *A = (double2 *)Av, *T = (double2 *)work;
+  hipLaunchKernelGGL(trtri_diag_kernel, dim3(nblk(m, NB)), dim3(256), 0, st, m, A, lda);
+  CHEBFI_HIP(hipGetLastError());
+  const double2 one{1.0, 0.0}, minus{-1.0, 0.0}, zero{0.0, 0.0};
+  for (int64_t L = NB; L < m; L *= 2) {
+    const int64_t full = m / (2 * L), step = 2 * L * (lda + 1);
+    // T = B C^-1, B <- -A^-1 T
+    auto merge = [&](int64_t i0, int64_t n, int64_t count, double2 *t) {
+      double2 *a = A + i0 * (lda + 1), *b = A + i0 + (i0 + L) * lda, *c = a + L * (lda + 1);
+      zgemm_batched(L, n, n, b, lda, step, c, lda, step, t, L, L * L, one, zero, count, st);
+      zgemm_batched(L, n, L, a, lda, step, t, L, L * L, b, lda, step, minus, zero, count, st);
+    };
+    if (full > 0) merge(0, L, full, T);
+    const int64_t i0 = full * 2 * L;
+    if (m - i0 > L) merge(i0, m - i0 - L, 1, T + full * L * L);
   }
 }
 
@@ -1447,7 +1494,7 @@ size_t zheev_work_bytes(int64_t m) {
   // column, the reduction's panels P1, Q (m x 2 kTriNB each), y, its partial
   // sums, S (real m x m), the lane-interleaved inverse iteration's five
   // arrays and pivots (m x 64 per wave each), and the blocked
-  // back-transformation's V (m x nb), G, T (nb x nb), W1, W2 (nb x m)
+  // back-transformation's T of every block, W1, W2 (nb x m) and partials
   const size_t nb = kBtBlock;
   const size_t tri = 4 * kTriNB * (size_t)m + 3 * (size_t)m + 2 * kTriNB * nblk(m, kTriRows) +
                      tri_words(std::min<int64_t>(m, kTriRegT * kTriRegR)) / 2 + 1;
@@ -1457,7 +1504,7 @@ size_t zheev_work_bytes(int64_t m) {
   return sizeof(double) * (size_t)(4 * m + 8) + sizeof(double2) * (size_t)(4 * m) +
          sizeof(double2) * tri +
          sizeof(double) * (size_t)m * m + (5 * sizeof(double) + 1) * lane_slab +
-         sizeof(double2) * ((3 + kBtSplits) * nb * (size_t)m + 2 * nb * nb) + invit_slabs +
+         sizeof(double2) * (3 + kBtSplits) * nb * ((size_t)m + nb) + invit_slabs +
          30 * 256;  // each of the (at most 30) sub-buffers is rounded up to 256 bytes
 }
 
@@ -1571,35 +1618,34 @@ const int *zheev(int64_t m, void *Av, int64_t lda, double *wout, void *Zv, int64
   // back-transformation Z = H_0 H_1 ... H_{m-2} S, in blocks of kBtBlock reflectors
   // from the last: Z <- (I - V T V^H) Z = Z - V (T (V^H Z)) on rows j0+1 .. m-1
   const int64_t nref = m - 1;
-  const int64_t nb0 = std::min<int64_t>(kBtBlock, std::max<int64_t>(nref, 1));
   if (m >= kBtMinM) {
-    double2 *V = (double2 *)take(sizeof(double2) * (size_t)m * nb0);
-    double2 *G = (double2 *)take(sizeof(double2) * (size_t)nb0 * nb0);
-    double2 *T = (double2 *)take(sizeof(double2) * (size_t)nb0 * nb0);
-    double2 *W1 = (double2 *)take(sizeof(double2) * (size_t)nb0 * m);
-    double2 *W2 = (double2 *)take(sizeof(double2) * (size_t)nb0 * m);
-    double2 *Wp = (double2 *)take(sizeof(double2) * (size_t)kBtSplits * nb0 * m);
-    for (int64_t jend = nref; jend > 0; jend -= nb0) {
-      const int64_t j0 = std::max<int64_t>(0, jend - nb0);
-      const int nb = (int)(jend - j0);
+    // every block's V^H V and T first (they do not depend on Z), then the blocks
+    const int64_t nblocks = nblk(nref, kBtBlock);
+    double2 *T = (double2 *)take(sizeof(double2) * (size_t)nblocks * kBtBlock * kBtBlock);
+    double2 *W1 = (double2 *)take(sizeof(double2) * (size_t)kBtBlock * m);
+    double2 *W2 = (double2 *)take(sizeof(double2) * (size_t)kBtBlock * m);
+    double2 *Wp = (double2 *)take(sizeof(double2) * (size_t)kBtSplits * kBtBlock * (m + kBtBlock));
+    hipLaunchKernelGGL(clean_v_kernel, dim3(nblk(m, 256), (unsigned)m), dim3(256), 0, st, m, A,
+                       lda);
+    const int spg = (int)std::max<int64_t>(
+        1, std::min<int64_t>({kBtSplits, m / 64, device_cus() / nblocks}));
+    zgemm_diag_tiles(nref, m, A, lda, Wp, spg, st);
+    hipLaunchKernelGGL(larft_kernel, dim3((unsigned)nblocks), dim3(kBtBlock * kLarftLanes), 0, st,
+                       nref, spg, Wp, tau, T);
+    CHEBFI_HIP(hipGetLastError());
+    for (int64_t b = nblocks - 1; b >= 0; --b) {
+      const int64_t j0 = b * kBtBlock;
+      const int nb = (int)std::min<int64_t>(kBtBlock, nref - j0);
       const int64_t Lr = m - j0 - 1;
+      const double2 *V = A + (j0 + 1) + j0 * lda;
       double2 *Zr = Z + (j0 + 1);
-      hipLaunchKernelGGL(build_v_kernel, dim3(nblk(Lr * nb, 256)), dim3(256), 0, st, m, A, lda, j0,
-                         nb, V);
-      // G = V^H V: a 64 x 64 product over Lr rows, split over K to fill the chip
-      const int spg = (int)std::max<int64_t>(
-          1, std::min<int64_t>({Lr / 64, kBtGSplits, (int64_t)kBtSplits * m / nb}));
-      zgemm(OP_C, OP_N, nb, nb, Lr, V, Lr, V, Lr, nullptr, 0, double2{1, 0}, double2{0, 0}, st,
-            Wp, spg);
-      zsum_parts(nb, nb, Wp, spg, G, nb, double2{1, 0}, double2{0, 0}, st);
-      hipLaunchKernelGGL(larft_kernel, dim3(1), dim3(kBtBlock * kLarftLanes), 0, st, nb, G,
-                         tau + j0, T);
       const int sp = std::min(kBtSplits, zgemm_splits(nb, m, Lr));
-      zgemm(OP_C, OP_N, nb, m, Lr, V, Lr, Zr, ldz, nullptr, 0, double2{1, 0}, double2{0, 0}, st, Wp,
-            sp);
+      zgemm(OP_C, OP_N, nb, m, Lr, V, lda, Zr, ldz, nullptr, 0, double2{1, 0}, double2{0, 0}, st,
+            Wp, sp);
       zsum_parts(nb, m, Wp, sp, W1, nb, double2{1, 0}, double2{0, 0}, st);
-      zgemm(OP_N, OP_N, nb, m, nb, T, nb, W1, nb, W2, nb, double2{1, 0}, double2{0, 0}, st);
-      zgemm(OP_N, OP_N, Lr, m, nb, V, Lr, W2, nb, Zr, ldz, double2{-1, 0}, double2{1, 0}, st);
+      zgemm(OP_N, OP_N, nb, m, nb, T + b * kBtBlock * kBtBlock, kBtBlock, W1, nb, W2, nb,
+            double2{1, 0}, double2{0, 0}, st);
+      zgemm(OP_N, OP_N, Lr, m, nb, V, lda, W2, nb, Zr, ldz, double2{-1, 0}, double2{1, 0}, st);
     }
   } else {
     for (int64_t j = m - 2; j >= 0; --j) {

@@ -522,7 +522,7 @@ int rr_lowprec(abi_system_s *s, void *Y, int64_t ld, void *HPsi, int64_t ldh_in,
     rr_gram_f32(M, npw, ypl, s->ldPA, B, npw, part, splits, G, st);
     s->prof.end(tok, st);
     tok = s->prof.begin(PROF_CHOL, 4.0 / 3.0 * (double)M * M * M, st);
-    zpotrf_upper(M, G, M, info, nullptr, st);
+    zpotrf_upper(M, G, M, info, s->eig2.get(zpotrf_work_bytes(M)), st);
     s->prof.end(tok, st);
     launch_diag_min_sq(M, G, M, pmin_dev, st);
     // (the stream drained first, then blocking copies into host variables)
@@ -655,7 +655,7 @@ void rr_core(abi_system_s *s, double2 *Y, int64_t ld, double2 *HPsi, int64_t ldh
   zgemm_herm(M, npw, Y, ld, SY, lds, G, M, st, part, splits);
   s->prof.end(tok, st);
   tok = s->prof.begin(PROF_CHOL, 4.0 / 3.0 * (double)M * M * M, st);
-  zpotrf_upper(M, G, M, info, nullptr, st);
+  zpotrf_upper(M, G, M, info, s->eig2.get(zpotrf_work_bytes(M)), st);
   s->prof.end(tok, st);
   int hinfo = 0;
   CHEBFI_HIP(hipMemcpyAsync(&hinfo, info, sizeof(int), hipMemcpyDeviceToHost, st));

@@ -79,8 +79,10 @@ __device__ __forceinline__ void grouped_tile(unsigned gm, unsigned &tm, unsigned
 
 // TAG only separates instantiations (1 = projector products of the H
 // application) so that kernel traces report them apart from the dense ones.
-// TRI: square product known to be Hermitian; the 1-D grid enumerates only the
-// tiles on and above the diagonal (the split-K sum mirrors the rest).
+// MODE 1: square product known to be Hermitian; the 1-D grid enumerates only the
+// tiles on and above the diagonal (the split-K sum mirrors the rest).  MODE 2: the
+// tiles on the diagonal alone, part[z][tile] 64 x 64 each.  Unsplit, blockIdx.z
+// counts products of a batch, sa / sb / sc apart.
 // Three workgroups per CU (168 registers; the epilogue's operands had cost the
 // unsplit form the third): with two, a SIMD's matrix core idles whenever both its
 // waves are between barriers.  At 115313 x 2048 x 864 the expansion went from 28.3
@@ -88,13 +90,14 @@ __device__ __forceinline__ void grouped_tile(unsigned gm, unsigned &tm, unsigned
 // TFLOP/s), the projection stays at 26.0 (62.8); two LDS stages with one barrier
 // per step (66 KB, two per CU) took 27.1 and 27.0, raised wave priority around the
 // MFMAs 27.0 and 27.4.
-template <typename T, int OPA, int OPB, bool SPLIT, int TAG, bool TRI = false>
+template <typename T, int OPA, int OPB, bool SPLIT, int TAG, int MODE = 0>
 __global__ __launch_bounds__(256, 3) void zgemm_kernel(int64_t m, int64_t n, int64_t k,
                                                     const C2<T> *__restrict__ A, int64_t lda,
                                                     const C2<T> *__restrict__ B, int64_t ldb,
                                                     C2<T> *__restrict__ C, int64_t ldc,
                                                     double2 alpha, double2 beta, int64_t kchunk,
-                                                    C2<T> *__restrict__ part) {
+                                                    C2<T> *__restrict__ part, int64_t sa,
+                                                    int64_t sb, int64_t sc) {
   typedef C2<T> V2;
   typedef typename Mma<T>::acc Acc;
   __shared__ T As[2][BK][BM + PAD];
@@ -104,7 +107,7 @@ __global__ __launch_bounds__(256, 3) void zgemm_kernel(int64_t m, int64_t n, int
   const int wm = wave & 1, wn = wave >> 1;
   int64_t row0, col0;
   unsigned tz = blockIdx.z;
-  if constexpr (!TRI) {
+  if constexpr (MODE == 0) {
     // groups of 16 row panels: the some 96 workgroups an XCD runs together share
     // 16 A and 6 B panels in its L2 (row panel fastest over the whole grid, each
     // XCD taking every eighth tile, they shared none: 4 TB/s of operand traffic)
@@ -114,14 +117,20 @@ __global__ __launch_bounds__(256, 3) void zgemm_kernel(int64_t m, int64_t n, int
     row0 = (int64_t)tm * BM;
     col0 = (int64_t)tn * BN;
   }
-  if constexpr (TRI) {
-    static_assert(BM == BN, "square tiles");
+  static_assert(MODE == 0 || BM == BN, "square tiles");
+  if constexpr (MODE == 2) row0 = col0 = (int64_t)blockIdx.x * BM;
+  if constexpr (MODE == 1) {
     int64_t ti, tj;
     upper_tile(blockIdx.x, ti, tj);
     row0 = ti * BM;
     col0 = tj * BN;
   }
-  const int64_t kbeg = (int64_t)tz * kchunk;
+  if constexpr (!SPLIT && MODE == 0) {
+    A += (int64_t)tz * sa;
+    B += (int64_t)tz * sb;
+    C += (int64_t)tz * sc;
+  }
+  const int64_t kbeg = SPLIT ? (int64_t)tz * kchunk : 0;
   const int64_t kend = (kbeg + kchunk < k) ? kbeg + kchunk : k;
 
   Acc acc_re[2][2], acc_im[2][2];
@@ -230,7 +239,10 @@ __global__ __launch_bounds__(256, 3) void zgemm_kernel(int64_t m, int64_t n, int
         const int64_t col = col0 + wn * 32 + sj * 16 + Mma<T>::row(lane, r);
         if (row < m && col < n) {
           const V2 v{acc_re[si][sj][r], acc_im[si][sj][r]};
-          if (SPLIT) {
+          if (MODE == 2) {
+            part[((int64_t)tz * gridDim.x + blockIdx.x) * BM * BN + (row - row0) +
+                 (col - col0) * BM] = v;
+          } else if (SPLIT) {
             part[(int64_t)tz * m * n + row + col * m] = v;
           } else {
             const V2 al{(T)alpha.x, (T)alpha.y};
@@ -294,20 +306,21 @@ __global__ __launch_bounds__(256) void zsum_herm_kernel(int64_t m, const C2<T> *
 template <typename T, int OPA, int OPB, int TAG>
 void launch_t(int64_t m, int64_t n, int64_t k, const void *A, int64_t lda, const void *B,
               int64_t ldb, void *C, int64_t ldc, double2 alpha, double2 beta, hipStream_t st,
-              void *part, int splits) {
+              void *part, int splits, int64_t batch = 1, int64_t sa = 0, int64_t sb = 0,
+              int64_t sc = 0) {
   typedef C2<T> V2;
   const int64_t chunk = part ? ((k + splits - 1) / splits + BK - 1) / BK * BK : k;
   // every chunk index gets launched; a chunk past the end of K writes zeros
-  const int zs = part ? splits : 1;
+  const int64_t zs = part ? splits : batch;
   dim3 grid((unsigned)((m + BM - 1) / BM), (unsigned)((n + BN - 1) / BN), (unsigned)zs);
   if (part) {
     hipLaunchKernelGGL((zgemm_kernel<T, OPA, OPB, true, TAG>), grid, dim3(256), 0, st, m, n, k,
                        (const V2 *)A, lda, (const V2 *)B, ldb, (V2 *)C, ldc, alpha, beta, chunk,
-                       (V2 *)part);
+                       (V2 *)part, sa, sb, sc);
   } else {
     hipLaunchKernelGGL((zgemm_kernel<T, OPA, OPB, false, TAG>), grid, dim3(256), 0, st, m, n, k,
                        (const V2 *)A, lda, (const V2 *)B, ldb, (V2 *)C, ldc, alpha, beta, chunk,
-                       (V2 *)nullptr);
+                       (V2 *)nullptr, sa, sb, sc);
   }
   CHEBFI_HIP(hipGetLastError());
 }
@@ -387,15 +400,48 @@ void zgemm_herm(int64_t m, int64_t k, const void *A, int64_t lda, const void *B,
   CHEBFI_REQUIRE(part != nullptr && splits >= 1, ABI_ERR_ARG, "Hermitian product needs parts");
   const int64_t nt = (m + BM - 1) / BM;
   const int64_t chunk = ((k + splits - 1) / splits + BK - 1) / BK * BK;
-  hipLaunchKernelGGL((zgemm_kernel<double, OP_C, OP_N, true, 0, true>),
+  hipLaunchKernelGGL((zgemm_kernel<double, OP_C, OP_N, true, 0, 1>),
                      dim3((unsigned)(nt * (nt + 1) / 2), 1, (unsigned)splits), dim3(256), 0, st, m,
                      m, k, (const double2 *)A, lda, (const double2 *)B, ldb, (double2 *)nullptr,
-                     (int64_t)0, double2{1, 0}, double2{0, 0}, chunk, (double2 *)part);
+                     (int64_t)0, double2{1, 0}, double2{0, 0}, chunk, (double2 *)part, (int64_t)0,
+                     (int64_t)0, (int64_t)0);
   CHEBFI_HIP(hipGetLastError());
   const int64_t nb = (m + 31) / 32;
   hipLaunchKernelGGL(zsum_herm_kernel<double>, dim3((unsigned)(nb * (nb + 1) / 2)), dim3(256), 0, st, m,
                      (const double2 *)part, splits, (double2 *)C, ldc);
   CHEBFI_HIP(hipGetLastError());
+}
+
+void zgemm_herm_update(int64_t m, int64_t k, const void *A, int64_t lda, void *C, int64_t ldc,
+                       hipStream_t st) {
+  if (m <= 0) return;
+  const int64_t nt = (m + BM - 1) / BM;
+  hipLaunchKernelGGL((zgemm_kernel<double, OP_C, OP_N, false, 0, 1>),
+                     dim3((unsigned)(nt * (nt + 1) / 2)), dim3(256), 0, st, m, m, k,
+                     (const double2 *)A, lda, (const double2 *)A, lda, (double2 *)C, ldc,
+                     double2{-1, 0}, double2{1, 0}, k, (double2 *)nullptr, (int64_t)0, (int64_t)0,
+                     (int64_t)0);
+  CHEBFI_HIP(hipGetLastError());
+}
+
+void zgemm_diag_tiles(int64_t n, int64_t k, const void *A, int64_t lda, void *part, int splits,
+                      hipStream_t st) {
+  if (n <= 0) return;
+  const int64_t chunk = ((k + splits - 1) / splits + BK - 1) / BK * BK;
+  hipLaunchKernelGGL((zgemm_kernel<double, OP_C, OP_N, true, 0, 2>),
+                     dim3((unsigned)((n + BM - 1) / BM), 1, (unsigned)splits), dim3(256), 0, st, n,
+                     n, k, (const double2 *)A, lda, (const double2 *)A, lda, (double2 *)nullptr,
+                     (int64_t)0, double2{1, 0}, double2{0, 0}, chunk, (double2 *)part, (int64_t)0,
+                     (int64_t)0, (int64_t)0);
+  CHEBFI_HIP(hipGetLastError());
+}
+
+void zgemm_batched(int64_t m, int64_t n, int64_t k, const void *A, int64_t lda, int64_t sa,
+                   const void *B, int64_t ldb, int64_t sb, void *C, int64_t ldc, int64_t sc,
+                   double2 alpha, double2 beta, int64_t batch, hipStream_t st) {
+  if (m <= 0 || n <= 0 || batch <= 0) return;
+  launch_t<double, OP_N, OP_N, 0>(m, n, k, A, lda, B, ldb, C, ldc, alpha, beta, st, nullptr, 1,
+                                  batch, sa, sb, sc);
 }
 
 int zgemm_splits(int64_t m, int64_t n, int64_t k, bool fewest) {

@@ -130,6 +130,18 @@ int zgemm_splits(int64_t m, int64_t n, int64_t k, bool fewest = false);
 int zgemm_herm_splits(int64_t m, int64_t k);
 void zgemm_herm(int64_t m, int64_t k, const void *A, int64_t lda, const void *B, int64_t ldb,
                 void *C, int64_t ldc, hipStream_t st, void *part, int splits);
+// C -= A^H A (C m x m, A k x m): the 64 x 64 tiles on and above the diagonal.
+void zgemm_herm_update(int64_t m, int64_t k, const void *A, int64_t lda, void *C, int64_t ldc,
+                       hipStream_t st);
+// The 64 x 64 tiles on the diagonal of A^H A (A k x n), one after the other in
+// part[z] for each of `splits` chunks of k.
+void zgemm_diag_tiles(int64_t n, int64_t k, const void *A, int64_t lda, void *part, int splits,
+                      hipStream_t st);
+// C_i = alpha A_i B_i + beta C_i (m x n x k), i < batch, operands sa / sb / sc
+// elements apart.
+void zgemm_batched(int64_t m, int64_t n, int64_t k, const void *A, int64_t lda, int64_t sa,
+                   const void *B, int64_t ldb, int64_t sb, void *C, int64_t ldc, int64_t sc,
+                   double2 alpha, double2 beta, int64_t batch, hipStream_t st);
 
 // C = alpha * sum_z part[z] + beta C  (m x n, part ld = m)
 void zsum_parts(int64_t m, int64_t n, const void *part, int splits, void *C, int64_t ldc,

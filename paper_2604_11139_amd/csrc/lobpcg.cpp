@@ -35,7 +35,7 @@ bool ortho_rr_basis(abi_system_s *s, int64_t k, int64_t mout, const double2 *Z,
   zgemm_herm(k, npw, Z, ld, SZ, ld, G, k, st, part, splits);
   s->prof.end(tok, st);
   tok = s->prof.begin(PROF_CHOL, 4.0 / 3.0 * (double)k * k * k, st);
-  zpotrf_upper(k, G, k, info, nullptr, st);
+  zpotrf_upper(k, G, k, info, s->eig2.get(zpotrf_work_bytes(k)), st);
   s->prof.end(tok, st);
   int h = 0;
   CHEBFI_HIP(hipMemcpyAsync(&h, info, sizeof(int), hipMemcpyDeviceToHost, st));
