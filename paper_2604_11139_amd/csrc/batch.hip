@@ -29,14 +29,15 @@ namespace chebfi {
 
 namespace {
 
-// cubic edges with specialised batched passes
-#define CHEBFI_BATCH_SIZES(X) X(24) X(25) X(27) X(30) X(32) X(36) X(40) X(45) X(48) X(64)
-
-// item -> system by a scan of the prefix offsets off[0..nsys]
+// item -> system by the prefix offsets off[0..nsys], read by a whole wave at once
+// (item is the same on every lane)
 __device__ __forceinline__ int find_sys(const int64_t *off, int nsys, int64_t item) {
   int s = 0;
-  while (s + 1 < nsys && item >= off[s + 1]) ++s;
-  return s;
+  for (int base = 1; base < nsys; base += 64) {
+    const int i = base + (int)(threadIdx.x & 63);
+    s += __popcll(__ballot(i < nsys && item >= off[i < nsys ? i : 0]));
+  }
+  return __builtin_amdgcn_readfirstlane(s);
 }
 
 // The descriptors' pointers are read from memory, so the compiler cannot tell
@@ -432,195 +433,114 @@ __global__ __launch_bounds__(512) void bpass_c_kernel(const BatchSys *__restrict
 }
 
 // ---- specialised passes for the systems of one cubic edge N ----------------
-// Same three passes as above over the items of the systems listed in gsys,
-// with N, the radix sequence and the plane strides known at compile time (the
-// cubic building blocks).  An item is NPL consecutive planes (pass B: x-z
-// slabs) of one band, stacked in LDS N cld<N>() elements apart, so that a
-// workgroup keeps about as much box data in flight on small boxes as one 64^2
-// plane; G = ceil(N / NPL) items per band (the last may hold fewer planes).
+// The compile-time passes over the systems listed in gsys (cubic boxes of edge N),
+// goff[0 .. gns] the prefix sums of their bands: the bodies of the single-system
+// passes, one plane or one run of z pencils per workgroup.  Against groups of planes
+// walked by 2048 persistent workgroups, which scanned the prefix table and fetched
+// the descriptors serially before each item's first load, with 512 threads for 216
+// butterflies of a 36^2 plane and flat loads through the descriptors' pointers, the
+// 16-cell filter of degree 8 went from 8.2 to 6.3 ms.
 
-// item -> (system, band, plane group) inside one edge group
-__device__ __forceinline__ int group_item(const int32_t *gsys, const int64_t *goff, int gns,
-                                          int64_t item, int G, int64_t *b, int *grp) {
-  const int q = find_sys(goff, gns, item);
-  const int64_t loc = item - goff[q];
-  *b = loc / G;
-  *grp = (int)(loc - *b * G);
+// A pointer read from a descriptor, known to be global and the same on every lane
+// (through a scalar register, which also keeps the compiler from undoing the cast:
+// with flat accesses the passes took 40 more registers).
+template <typename P> __device__ __forceinline__ P *as_global(P *p) {
+  unsigned long long v = (unsigned long long)p;
+  asm("" : "+s"(v));
+  return (P *)(gptr<P>)v;
+}
+
+// The system of band `band` of the group and the band's index in it.
+__device__ __forceinline__ int group_band(const int32_t *gsys, const int64_t *goff, int gns,
+                                          int64_t band, int64_t *b) {
+  const int q = find_sys(goff, gns, band);
+  *b = band - goff[q];
   return gsys[q];
 }
 
 template <typename T, int N>
-__global__ __launch_bounds__(kCT) void bcpass_a_kernel(const BatchSys *__restrict__ sys,
-                                                       const BatchStep *__restrict__ step,
-                                                       const int32_t *__restrict__ gsys,
-                                                       const int64_t *__restrict__ goff, int gns) {
-  constexpr int NXY = N * N, LD = cld<N>(), PL = N * LD;
-  constexpr int NPL = cplanes_per_item<T, N>(), G = (N + NPL - 1) / NPL;
-  __shared__ C2<T> buf[NPL * PL];
+__global__ __launch_bounds__((cthreads<N, N>())) void bcpass_a_kernel(
+    const BatchSys *__restrict__ sys, const BatchStep *__restrict__ step,
+    const int32_t *__restrict__ gsys, const int64_t *__restrict__ goff, int gns, int64_t first) {
+  constexpr int NXY = N * N;
+  __shared__ C2<T> buf[N * cld<N>()];
   __shared__ C2<T> tw[N];
-  const int64_t total = goff[gns];
-  for (int64_t item = blockIdx.x; item < total; item += gridDim.x) {
-    int64_t b;
-    int g;
-    const int s = group_item(gsys, goff, gns, item, G, &b, &g);
-    const int i30 = g * NPL, np3 = N - i30 < NPL ? N - i30 : NPL;
-    const BatchSys &d = sys[s];
-    const BatchStep &st = step[s];
-    // planes with no sphere points stay unwritten: pass B reads them as zeros
-    const int s0 = d.plane[i30], s1 = d.plane[i30 + np3];
-    if (s0 == s1) continue;
-    for (int i = threadIdx.x; i < N; i += kCT) tw[i] = to_c2<T>(d.tw[i]);
-    for (int i = threadIdx.x; i < NPL * PL; i += kCT) buf[i] = C2<T>{0, 0};
-    __syncthreads();
-    // the sphere points of planes i30 .. i30 + np3 - 1 are contiguous; element
-    // e of the group (plane p, row r, column c) sits at (e / N) LD + e % N = p PL + r LD + c
-    const C2<T> *xb = reinterpret_cast<const C2<T> *>(st.yk) + b * st.ldk;
-    const int off = i30 * NXY;
-    for (int idx = s0 + threadIdx.x; idx < s1; idx += kCT) {
-      const int e = d.box_index[idx] - off;
-      buf[(e / N) * LD + e % N] = xb[idx];
-    }
-    __syncthreads();
-    cfft<T, N, 0, 1, NPL * N, 1, LD, +1>(buf, tw);         // x: every row of every plane
-    // y: pencil pa = (plane p, column i1), element i2; the last stage writes the box
-    C2<T> *dst = reinterpret_cast<C2<T> *>(d.box) + b * (int64_t)NXY * N + off;
-    auto ldm = [&](int pa, int e) { return buf[(pa / N) * PL + pa % N + e * LD]; };
-    auto stm = [&](int pa, int e, C2<T> v) { buf[(pa / N) * PL + pa % N + e * LD] = v; };
-    auto stg = [&](int pa, int e, C2<T> v) {
-      if (pa / N < np3) dst[(pa / N) * NXY + pa % N + e * N] = v;
-    };
-    cfft_io<T, N, 0, 1, NPL * N, +1, true, false>(tw, ldm, stg, ldm, stm);
-    __syncthreads();
-  }
-}
-
-// Waves per SIMD asked of the batched pass B: six (three workgroups of kCT
-// threads per CU instead of two) for the complex64 edges where that measured
-// faster (at 24 and 45 the compiler spills a few registers to fit, and the
-// pass is still faster), else the least a workgroup of kCT threads needs.
-template <typename T, int N>
-constexpr int bcpass_b_waves() {
-  return sizeof(T) == 4 && (N == 24 || N == 40 || N == 45) ? 6 : kCT / 256;
+  const int64_t item = first + blockIdx.x;
+  int64_t b;
+  const int s = group_band(gsys, goff, gns, item / N, &b), i3 = (int)(item % N);
+  const BatchSys &d = sys[s];
+  const BatchStep &st = step[s];
+  const int32_t *plane = as_global(d.plane);
+  // planes with no sphere points stay unwritten: pass B reads them as zeros
+  const int s0 = plane[i3], s1 = plane[i3 + 1];
+  if (s0 == s1) return;
+  pass_a_plane<T, N>(as_global((const C2<T> *)st.yk) + b * st.ldk, as_global(d.box_index), s0,
+                     s1, i3 * NXY, as_global(d.tw),
+                     as_global((C2<T> *)d.box) + b * (int64_t)NXY * N + i3 * NXY, buf, tw);
 }
 
 template <typename T, int N>
-__global__ __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(bcpass_b_waves<T, N>())))
-void bcpass_b_kernel(const BatchSys *__restrict__ sys, const int32_t *__restrict__ gsys,
-                     const int64_t *__restrict__ goff, int gns) {
-  constexpr int LD = cld<N>(), PL = N * LD;
-  constexpr int NPL = cplanes_per_item<T, N>(), G = (N + NPL - 1) / NPL;
-  __shared__ C2<T> buf[NPL * PL];
+__global__ __launch_bounds__((cthreads<N, zpencils<T>()>())) void bcpass_b_kernel(
+    const BatchSys *__restrict__ sys, const int32_t *__restrict__ gsys,
+    const int64_t *__restrict__ goff, int gns, int64_t first) {
+  constexpr int NXY = N * N, Q = zpencils<T>(), CH = (NXY + Q - 1) / Q;
+  __shared__ C2<T> buf[N * Q];
   __shared__ C2<T> tw[N];
-  const int64_t total = goff[gns];
-  if ((int64_t)blockIdx.x >= total) return;
-  // the twiddles depend on N only (the same for every system of the group)
-  for (int i = threadIdx.x; i < N; i += kCT) tw[i] = to_c2<T>(sys[gsys[0]].tw[2 * kMaxN + i]);
-  __syncthreads();
-  constexpr int64_t ZS = (int64_t)N * N;
-  for (int64_t item = blockIdx.x; item < total; item += gridDim.x) {
-    int64_t b;
-    int g;
-    const int s = group_item(gsys, goff, gns, item, G, &b, &g);
-    const int i20 = g * NPL, np2 = N - i20 < NPL ? N - i20 : NPL;
-    const BatchSys &d = sys[s];
-    // slabs i20 .. i20 + np2 - 1: for each i3 their rows are one contiguous run
-    // of np2 N elements in the box; pencil pa = p N + i1 is the position along
-    // it, element i3; the forward z transform reads the box and applies V in
-    // its last stage, the inverse's last stage writes the box
-    C2<T> *src = reinterpret_cast<C2<T> *>(d.box) + b * (int64_t)N * N * N + (int64_t)i20 * N;
-    const T *V = reinterpret_cast<const T *>(d.V) + (int64_t)i20 * N;
-    const int run = np2 * N;
-    auto ldm = [&](int pa, int e) { return buf[(pa / N) * PL + pa % N + e * LD]; };
-    auto stm = [&](int pa, int e, C2<T> v) { buf[(pa / N) * PL + pa % N + e * LD] = v; };
-    // z-planes without sphere points: zero on input (pass A leaves them
-    // unwritten) and not written on output (pass C does not read them)
-    const uint64_t zocc = d.zocc;
-    auto occ = [&](int e) { return ((zocc >> e) & 1ull) != 0; };
-    auto ldg = [&](int pa, int e) {
-      return (pa < run && occ(e)) ? src[pa + e * ZS] : C2<T>{0, 0};
-    };
-    auto stv = [&](int pa, int e, C2<T> v) {
-      buf[(pa / N) * PL + pa % N + e * LD] = pa < run ? cscale(v, V[pa + e * ZS]) : v;
-    };
-    auto stg = [&](int pa, int e, C2<T> v) {
-      if (pa < run && occ(e)) src[pa + e * ZS] = v;
-    };
-    cfft_io<T, N, 0, 1, NPL * N, +1, false, true>(tw, ldg, stv, ldm, stm);
-    cfft_io<T, N, 0, 1, NPL * N, -1, true, false>(tw, ldm, stg, ldm, stm);
-    __syncthreads();
-  }
-}
-
-// Waves per SIMD asked of the batched pass C: eight (a 64-VGPR budget, four
-// workgroups of kCT threads per CU, as the LDS allows) where the compiler
-// fits it without spilling (complex64, every edge but 36), else the least a
-// workgroup of kCT threads needs.
-template <typename T, int N>
-constexpr int bcpass_c_waves() {
-  return sizeof(T) == 4 && N != 36 ? 8 : kCT / 256;
+  const int64_t item = first + blockIdx.x;
+  int64_t b;
+  const int s = group_band(gsys, goff, gns, item / CH, &b), q0 = (int)(item % CH) * Q;
+  const BatchSys &d = sys[s];
+  // z-planes without sphere points: zero on input (pass A leaves them unwritten)
+  // and not written on output (pass C does not read them)
+  C2<T> *src = as_global((C2<T> *)d.box) + b * (int64_t)NXY * N + q0;
+  z_pencils<T, N, Z_FILTER>(src, src, as_global((const T *)d.V) + q0, NXY - q0, NXY,
+                            as_global(d.tw) + 2 * kMaxN, ZOcc{d.zocc, d.zocc_hi}, buf, tw);
 }
 
 template <typename T, int N>
-__global__ __launch_bounds__(kCT) __attribute__((amdgpu_waves_per_eu(bcpass_c_waves<T, N>())))
-void bcpass_c_kernel(const BatchSys *__restrict__ sys, const BatchStep *__restrict__ step,
-                     const int32_t *__restrict__ gsys, const int64_t *__restrict__ goff,
-                     int gns) {
-  constexpr int NXY = N * N, LD = cld<N>(), PL = N * LD;
-  constexpr int NPL = cplanes_per_item<T, N>(), G = (N + NPL - 1) / NPL;
-  __shared__ C2<T> buf[NPL * PL];
+__global__ __launch_bounds__((cthreads<N, N>())) void bcpass_c_kernel(
+    const BatchSys *__restrict__ sys, const BatchStep *__restrict__ step,
+    const int32_t *__restrict__ gsys, const int64_t *__restrict__ goff, int gns, int64_t first) {
+  constexpr int NXY = N * N, LD = cld<N>(), CT = cthreads<N, N>();
+  __shared__ C2<T> buf[N * LD];
   __shared__ C2<T> tw[N];
-  const int64_t total = goff[gns];
-  if ((int64_t)blockIdx.x >= total) return;
-  // the twiddles depend on N only (the same for every system of the group)
-  for (int i = threadIdx.x; i < N; i += kCT) tw[i] = to_c2<T>(sys[gsys[0]].tw[i]);
-  __syncthreads();
-  for (int64_t item = blockIdx.x; item < total; item += gridDim.x) {
-    int64_t b;
-    int g;
-    const int s = group_item(gsys, goff, gns, item, G, &b, &g);
-    const int i30 = g * NPL, np3 = N - i30 < NPL ? N - i30 : NPL;
-    const BatchSys &d = sys[s];
-    const BatchStep &st = step[s];
-    const int np = d.nproj;
-    // no sphere points in these planes: nothing to gather (pass B left them
-    // unwritten; in an item that also holds an occupied plane, such a plane's
-    // values stay within its own 2-D transform and are never gathered)
-    const int s0 = d.plane[i30], s1 = d.plane[i30 + np3];
-    if (s0 == s1) continue;
-    const int off = i30 * NXY;
-    const C2<T> *src = reinterpret_cast<const C2<T> *>(d.box) + b * (int64_t)NXY * N + off;
-    {  // y: pencil pa = (plane p, column i1), element i2; the first stage reads the box
-      auto ldm = [&](int pa, int e) { return buf[(pa / N) * PL + pa % N + e * LD]; };
-      auto stm = [&](int pa, int e, C2<T> v) { buf[(pa / N) * PL + pa % N + e * LD] = v; };
-      auto ldg = [&](int pa, int e) {
-        return pa / N < np3 ? src[(pa / N) * NXY + pa % N + e * N] : C2<T>{0, 0};
-      };
-      cfft_io<T, N, 0, 1, NPL * N, -1, false, true>(tw, ldg, stm, ldm, stm);
+  const int64_t item = first + blockIdx.x;
+  int64_t b;
+  const int s = group_band(gsys, goff, gns, item / N, &b), i3 = (int)(item % N);
+  const BatchSys &d = sys[s];
+  const BatchStep &st = step[s];
+  const int32_t *plane = as_global(d.plane), *box_index = as_global(d.box_index);
+  const int s0 = plane[i3], s1 = plane[i3 + 1];
+  if (s0 == s1) return;  // no sphere points to gather in this plane
+  const int off = i3 * NXY;
+  pass_c_plane<T, N>(as_global((const C2<T> *)d.box) + b * (int64_t)NXY * N + off,
+                     as_global(d.tw), buf, tw);
+  const C2<T> *yk = as_global((const C2<T> *)st.yk) + b * st.ldk;
+  const C2<T> *yp = as_global((const C2<T> *)st.yprev) + b * st.ldp;
+  const bool prev = st.yprev != nullptr, nonlocal = d.nproj > 0;
+  C2<T> *out = as_global((C2<T> *)st.out) + b * st.ldo;
+  const C2<T> *E = as_global((const C2<T> *)d.E) + b * d.npw;
+  const double *kin = as_global(d.kin);
+  const T alpha = (T)st.alpha, cshift = (T)st.cshift, beta = (T)st.beta;
+  const T scale = (T)(1.0 / ((double)NXY * N));
+  for (int idx = s0 + threadIdx.x; idx < s1; idx += CT) {
+    const int e = box_index[idx] - off;
+    const C2<T> lc = cscale(buf[(e / N) * LD + e % N], scale);
+    const C2<T> x = yk[idx];
+    const T kd = (T)kin[idx] - cshift;
+    const C2<T> h = cadd(lc, cscale(x, kd));
+    C2<T> o{alpha * h.x, alpha * h.y};
+    if (nonlocal) {
+      const C2<T> nl = E[idx];
+      o.x += nl.x;
+      o.y += nl.y;
     }
-    cfft<T, N, 0, 1, NPL * N, 1, LD, -1>(buf, tw);         // x: every row of every plane
-    const C2<T> *yk = reinterpret_cast<const C2<T> *>(st.yk) + b * st.ldk;
-    const C2<T> *yp =
-        st.yprev ? reinterpret_cast<const C2<T> *>(st.yprev) + b * st.ldp : nullptr;
-    C2<T> *out = reinterpret_cast<C2<T> *>(st.out) + b * st.ldo;
-    const C2<T> *E = np > 0 ? reinterpret_cast<const C2<T> *>(d.E) + b * d.npw : nullptr;
-    const T alpha = (T)st.alpha, cshift = (T)st.cshift, beta = (T)st.beta;
-    const T scale = (T)(1.0 / ((double)NXY * N));
-    for (int idx = s0 + threadIdx.x; idx < s1; idx += kCT) {
-      const int e = d.box_index[idx] - off;
-      const C2<T> lc = cscale(buf[(e / N) * LD + e % N], scale);
-      const C2<T> x = yk[idx];
-      const T kd = (T)d.kin[idx] - cshift;
-      const C2<T> h = cadd(lc, cscale(x, kd));
-      const C2<T> nl = E ? E[idx] : C2<T>{0, 0};
-      C2<T> o{alpha * h.x + nl.x, alpha * h.y + nl.y};
-      if (yp) {
-        const C2<T> p = yp[idx];
-        o.x -= beta * p.x;
-        o.y -= beta * p.y;
-      }
-      out[idx] = o;
+    if (prev) {
+      const C2<T> p = yp[idx];
+      o.x -= beta * p.x;
+      o.y -= beta * p.y;
     }
-    __syncthreads();
+    out[idx] = o;
   }
 }
 
@@ -672,21 +592,33 @@ void batch_step(const BatchLaunch &L, int j, hipStream_t st, hipStream_t side, h
   auto cubic = [&](int pass) {
     for (int gi = 0; gi < L.ngroups; ++gi) {
       const BatchGroup &G = L.groups[gi];
-      const dim3 gr = grid(G.items);
+      constexpr int Q = zpencils<T>();
+      // (a launch holds fewer than 2^32 threads: at most 2^20 workgroups each)
+      auto chunks = [&](int64_t per_band, auto launch) {
+        const int64_t items = G.bands * per_band, most = 1 << 20;
+        for (int64_t first = 0; first < items; first += most)
+          launch(dim3((unsigned)std::min(items - first, most)), first);
+      };
 #define CHEBFI_CASE(N_)                                                                       \
   case N_:                                                                                    \
     if (pass == 0)                                                                            \
-      hipLaunchKernelGGL((bcpass_a_kernel<T, N_>), gr, dim3(kCT), 0, st, L.d_sys, stp, G.gsys, \
-                         G.goff, G.nsys);                                                     \
+      chunks(N_, [&](dim3 gr, int64_t first) {                                                \
+        hipLaunchKernelGGL((bcpass_a_kernel<T, N_>), gr, dim3(cthreads<N_, N_>()), 0, st,     \
+                           L.d_sys, stp, G.gsys, G.goff, G.nsys, first);                      \
+      });                                                                                     \
     else if (pass == 1)                                                                       \
-      hipLaunchKernelGGL((bcpass_b_kernel<T, N_>), gr, dim3(kCT), 0, st, L.d_sys, G.gsys,      \
-                         G.goff, G.nsys);                                                     \
+      chunks((N_ * N_ + Q - 1) / Q, [&](dim3 gr, int64_t first) {                             \
+        hipLaunchKernelGGL((bcpass_b_kernel<T, N_>), gr, dim3(cthreads<N_, Q>()), 0, st,      \
+                           L.d_sys, G.gsys, G.goff, G.nsys, first);                           \
+      });                                                                                     \
     else                                                                                      \
-      hipLaunchKernelGGL((bcpass_c_kernel<T, N_>), gr, dim3(kCT), 0, st, L.d_sys, stp, G.gsys, \
-                         G.goff, G.nsys);                                                     \
+      chunks(N_, [&](dim3 gr, int64_t first) {                                                \
+        hipLaunchKernelGGL((bcpass_c_kernel<T, N_>), gr, dim3(cthreads<N_, N_>()), 0, st,     \
+                           L.d_sys, stp, G.gsys, G.goff, G.nsys, first);                      \
+      });                                                                                     \
     break;
       switch (G.n) {
-        CHEBFI_BATCH_SIZES(CHEBFI_CASE)
+        CHEBFI_EDGES(CHEBFI_CASE)
         default:
           break;
       }
@@ -715,22 +647,7 @@ void batch_step(const BatchLaunch &L, int j, hipStream_t st, hipStream_t side, h
   }
 }
 
-int batch_item_planes(int n, bool fp32) {
-  // (the host side of cplanes_per_item)
-  const int per = 34000 / (n * (n + 1) * (fp32 ? 8 : 16));
-  return per > 1 ? per : 1;
-}
-
-bool batch_edge_specialised(int n) {
-  switch (n) {
-#define CHEBFI_CASE(N_) case N_:
-    CHEBFI_BATCH_SIZES(CHEBFI_CASE)
-#undef CHEBFI_CASE
-    return true;
-    default:
-      return false;
-  }
-}
+bool batch_edge_specialised(int n) { return listed_edge(n); }
 
 template <typename T>
 void batch_prepare(const BatchLaunch &L) {

@@ -396,6 +396,7 @@ void batch_filter(abi_batch_s *B, const void *const *X, void *const *Y, const in
     d.box_index = s->d_box;
     d.plane = s->d_plane;
     d.zocc = s->zocc;
+    d.zocc_hi = s->zocc_hi;
     d.kin = s->d_kin;
     d.V = fp32 ? (const void *)s->d_Vf : (const void *)s->d_V;
     d.tw = reinterpret_cast<const double2 *>(s->d_tw);
@@ -443,10 +444,9 @@ void batch_filter(abi_batch_s *B, const void *const *X, void *const *Y, const in
     gsys_at.push_back(hgsys.size());
     goff_at.push_back(hgoff.size());
     hgoff.push_back(0);
-    const int npl = batch_item_planes(gedge[g], fp32);
     for (int32_t i : glist[g]) {
       hgsys.push_back(i);
-      hgoff.push_back(hgoff.back() + nband[i] * ((gedge[g] + npl - 1) / npl));
+      hgoff.push_back(hgoff.back() + nband[i]);
     }
   }
   // step table: Y_0 = X, Y_m = Y, Y_j (0 < j < m) in slot j % 2 (the update of
@@ -536,7 +536,7 @@ void batch_filter(abi_batch_s *B, const void *const *X, void *const *Y, const in
     G.nsys = (int)glist[g].size();
     G.gsys = (const int32_t *)(dt + t_sys + t_steps + t_off) + gsys_at[g];
     G.goff = (const int64_t *)(dt + t_sys + t_steps + t_off + t_gsys) + goff_at[g];
-    G.items = hgoff[goff_at[g] + G.nsys];
+    G.bands = hgoff[goff_at[g] + G.nsys];
   }
   L.fft_threads = B->fft_threads;
   L.proj_threads = B->proj_threads;

@@ -290,134 +290,34 @@ __global__ __launch_bounds__(256) void rho_accum_kernel(int64_t nbox, int nb, in
   rho[r] += scale * acc;
 }
 
-// ---- compile-time specialised passes (building blocks in fft_dev.h) --------------------
-// Passes A and C for square planes of a listed edge N (any n3), the z passes for
-// a listed n3 (any plane): one workgroup holds one plane, or kZRow bytes' worth of
-// neighbouring z pencils.  All are bound by their HBM bytes when the waves in
-// flight cover the latency; see cthreads for the thread count.
+// ---- compile-time specialised passes (bodies in fft_dev.h) --------------------------------
+// Passes A and C for square planes of a listed edge N (any n3), the z passes for a
+// listed n3 (any plane).
 
 template <typename T, int N>
 __global__ __launch_bounds__((cthreads<N, N>())) void cpass_a_kernel(
     const C2<T> *__restrict__ X, int64_t ldx, int band0, const int32_t *__restrict__ box_index,
     const int32_t *__restrict__ plane, const double2 *__restrict__ twg, C2<T> *__restrict__ box) {
-  constexpr int NXY = N * N, LD = cld<N>(), CT = cthreads<N, N>();
-  __shared__ C2<T> buf[N * LD];
+  __shared__ C2<T> buf[N * cld<N>()];
   __shared__ C2<T> tw[N];
-  const int i3 = blockIdx.x;
-  const int bl = blockIdx.y;
+  const int i3 = blockIdx.x, bl = blockIdx.y, off = i3 * N * N;
   const int s0 = plane[i3], s1 = plane[i3 + 1];
   // a plane with no sphere points is left unwritten: the middle passes read it as zero
   if (s0 == s1) return;
-  const C2<T> *xb = X + (int64_t)(band0 + bl) * ldx;
-  const int off = i3 * NXY;
-  // the plane's sphere rows (a disk: at most pi/4 of it when the sphere fits the
-  // box) are fetched before the plane is cleared, all in flight together
-  constexpr int FULL = (NXY * 4 / 5 + CT - 1) / CT, U = FULL < 6 ? FULL : 6;
-  T xr[U], xi[U];
-  int xe[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int idx = min(s0 + (int)threadIdx.x + u * CT, s1 - 1);
-    const C2<T> v = xb[idx];
-    xr[u] = v.x;
-    xi[u] = v.y;
-    xe[u] = box_index[idx] - off;
-  }
-  for (int i = threadIdx.x; i < N; i += CT) tw[i] = to_c2<T>(twg[i]);
-  for (int i = threadIdx.x; i < N * LD; i += CT) buf[i] = C2<T>{0, 0};
-  __syncthreads();
-#pragma unroll
-  for (int u = 0; u < U; ++u)
-    if (s0 + (int)threadIdx.x + u * CT < s1)
-      buf[(xe[u] / N) * LD + xe[u] % N] = C2<T>{xr[u], xi[u]};
-  for (int idx = s0 + threadIdx.x + U * CT; idx < s1; idx += CT) {
-    const int e = box_index[idx] - off;
-    buf[(e / N) * LD + e % N] = xb[idx];
-  }
-  __syncthreads();
-  cfft<T, N, 0, 1, N, 1, LD, +1, 1, 0, CT>(buf, tw);  // x: N pencils of stride-1 elements
-  // y: pencil i1, element i2; the last stage writes the box plane
-  C2<T> *dst = box + (int64_t)bl * NXY * gridDim.x + off;
-  auto ldm = [&](int pa, int e) { return buf[pa + e * LD]; };
-  auto stm = [&](int pa, int e, C2<T> v) { buf[pa + e * LD] = v; };
-  auto stg = [&](int pa, int e, C2<T> v) { dst[pa + e * N] = v; };
-  cfft_io<T, N, 0, 1, N, +1, true, false, CT>(tw, ldm, stg, ldm, stm);
+  pass_a_plane<T, N>(X + (int64_t)(band0 + bl) * ldx, box_index, s0, s1, off, twg,
+                     box + (int64_t)bl * N * N * gridDim.x + off, buf, tw);
 }
-
-// Reciprocal z-planes that hold sphere points, one bit each.
-struct ZOcc {
-  uint64_t lo, hi;
-};
-
-// z pencils per workgroup: 512 bytes of neighbouring pencils (64 complex64, 32
-// complex128), so that every element row of a load or store is a whole run of
-// 512 contiguous bytes whatever the plane's edges are (the pencils of a box are
-// numbered i1 + n1 i2: a slab of one i2 would give rows of n1 elements, 288
-// bytes and 216 of 512 threads busy at 36), and an LDS row is one bank sweep.
-template <typename T> constexpr int zpencils() { return 512 / (int)sizeof(C2<T>); }
-
-// Work of a z pass: the filter's pass B (inverse z transform, times V, forward
-// transform), the inverse transform alone (density, adjoint's forward bands), or
-// the adjoint's pass B (also Re[conj(adjoint) * forward] over the forward band).
-enum { Z_FILTER = 0, Z_INVERSE = 1, Z_ADJOINT = 2 };
 
 template <typename T, int N, int MODE>
 __global__ __launch_bounds__((cthreads<N, zpencils<T>()>())) void zpass_kernel(
     C2<T> *__restrict__ box, C2<T> *__restrict__ fwd, const T *__restrict__ V, int nxy,
     const double2 *__restrict__ twg, ZOcc zocc) {
-  constexpr int Q = zpencils<T>(), CT = cthreads<N, Q>();
+  constexpr int Q = zpencils<T>();
   __shared__ C2<T> buf[N * Q];
   __shared__ C2<T> tw[N];
   const int q0 = blockIdx.x * Q;
-  const int left = nxy - q0;  // pencils of this workgroup: the last one may be short
-  for (int i = threadIdx.x; i < N; i += CT) tw[i] = to_c2<T>(twg[2 * kMaxN + i]);
-  __syncthreads();
   const int64_t o = (int64_t)blockIdx.y * nxy * N + q0;
-  C2<T> *src = box + o;
-  const T *v = V + q0;
-  auto ldm = [&](int pa, int e) { return buf[pa + e * Q]; };
-  auto stm = [&](int pa, int e, C2<T> x) { buf[pa + e * Q] = x; };
-  // reciprocal planes g3 without sphere points: zero in (pass A leaves them
-  // unwritten), not written out (pass C does not read them)
-  auto occ = [&](int e) { return (((N > 64 && e >= 64 ? zocc.hi : zocc.lo) >> (e & 63)) & 1) != 0; };
-  // (every load is issued: a pencil past the end reads the last one, an empty
-  // plane's element plane 0's, which the workgroup reads anyway; a branch around
-  // each load kept them from overlapping, 48 against 40 us per 64 64^3 complex64
-  // boxes)
-  auto ldg = [&](int pa, int e) {
-    const bool in = occ(e);
-    const C2<T> x = src[min(pa, left - 1) + (in ? e * nxy : 0)];
-    return in ? x : C2<T>{0, 0};
-  };
-  if constexpr (MODE == Z_INVERSE) {  // real space out: all planes
-    auto stg = [&](int pa, int e, C2<T> x) {
-      if (pa < left) src[pa + e * nxy] = x;
-    };
-    cfft_io<T, N, 0, 1, Q, +1, false, false, CT>(tw, ldg, stg, ldm, stm);
-  } else {
-    C2<T> *fw = fwd + o;
-    // V (and the forward band) fetched ahead of the stage that multiplies by it
-    struct Pre {
-      T v;
-      C2<T> y;
-    };
-    auto pre = [&](int pa, int e) {
-      const int r = min(pa, left - 1) + e * nxy;
-      Pre p{v[r], C2<T>{0, 0}};
-      if constexpr (MODE == Z_ADJOINT) p.y = fw[r];
-      return p;
-    };
-    auto stv = [&](int pa, int e, C2<T> x, const Pre &p) {
-      if constexpr (MODE == Z_ADJOINT)
-        if (pa < left) fw[pa + e * nxy] = C2<T>{x.x * p.y.x + x.y * p.y.y, (T)0};
-      buf[pa + e * Q] = cscale(x, p.v);
-    };
-    auto stg = [&](int pa, int e, C2<T> x) {
-      if (pa < left && occ(e)) src[pa + e * nxy] = x;
-    };
-    cfft_io<T, N, 0, 1, Q, +1, false, true, CT>(tw, ldg, stv, ldm, stm, pre);
-    cfft_io<T, N, 0, 1, Q, -1, true, false, CT>(tw, ldm, stg, ldm, stm);
-  }
+  z_pencils<T, N, MODE>(box + o, fwd + o, V + q0, nxy - q0, nxy, twg + 2 * kMaxN, zocc, buf, tw);
 }
 
 // (Gathering two or three rows per thread at once, all their loads in flight
@@ -443,17 +343,8 @@ __global__ __launch_bounds__((cthreads<N, N>())) void cpass_c_kernel(
   const int bl = blockIdx.y;
   const int s0 = plane[i3], s1 = plane[i3 + 1];
   if (s0 == s1) return;  // no sphere points to gather in this plane
-  for (int i = threadIdx.x; i < N; i += CT) tw[i] = to_c2<T>(twg[i]);
-  __syncthreads();
   const int off = i3 * NXY;
-  const C2<T> *src = box + (int64_t)bl * NXY * gridDim.x + off;
-  {  // y: pencil i1, element i2; the first stage reads the box plane
-    auto ldm = [&](int pa, int e) { return buf[pa + e * LD]; };
-    auto stm = [&](int pa, int e, C2<T> v) { buf[pa + e * LD] = v; };
-    auto ldg = [&](int pa, int e) { return src[pa + e * N]; };
-    cfft_io<T, N, 0, 1, N, -1, false, true, CT>(tw, ldg, stm, ldm, stm);
-  }
-  cfft<T, N, 0, 1, N, 1, LD, -1, 1, 0, CT>(buf, tw);
+  pass_c_plane<T, N>(box + (int64_t)bl * NXY * gridDim.x + off, twg, buf, tw);
   const int64_t b = band0 + bl;
   const C2<T> *yk = Yk + b * ldk;
   C2<T> *out = Out + b * ldo;
@@ -482,22 +373,6 @@ __global__ __launch_bounds__((cthreads<N, N>())) void cpass_c_kernel(
       return o;
     });
   }
-}
-
-// Edges with compile-time transforms.
-#define CHEBFI_EDGES(X)                                                                         \
-  X(12) X(15) X(16) X(18) X(20) X(24) X(25) X(27) X(30) X(32) X(36) X(40) X(45) X(48) X(50) \
-  X(54) X(60) X(64) X(72) X(75) X(80) X(81) X(90) X(96)
-
-bool listed_edge(int n) {
-#define CHEBFI_CASE(N_) case N_:
-  switch (n) {
-    CHEBFI_EDGES(CHEBFI_CASE)
-    return true;
-    default:
-      return false;
-  }
-#undef CHEBFI_CASE
 }
 
 template <typename F> void set_lds(F kernel, size_t bytes) {

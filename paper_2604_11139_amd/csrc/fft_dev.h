@@ -484,16 +484,157 @@ __device__ __forceinline__ void cfft_io(const C2<T> *tw, Ld0 ld0, StL stl, LdM l
   }
 }
 
-// Planes (or slabs) of one band that a batched pass keeps in LDS together:
-// about 34 KB of LDS per workgroup, so that four workgroups of kCT threads per
-// CU hold as much box data in flight as the 64^3 passes do.
+// ---- whole-plane and pencil bodies of the compile-time passes -----------------------
+// One workgroup holds one plane, or 512 bytes' worth of neighbouring z pencils;
+// shared by the single-system and the batched kernels.  All are bound by their HBM
+// bytes when the waves in flight cover the latency; see cthreads for the thread
+// count.
+
+// Pass A of one plane of edge N: the sphere points [s0, s1) of xb (at box index
+// box_index - off inside the plane) -> inverse x and y transforms -> dst.
 template <typename T, int N>
-constexpr int cplanes_per_item() {
-  return 34000 / (N * cld<N>() * (int)sizeof(C2<T>)) > 1
-             ? 34000 / (N * cld<N>() * (int)sizeof(C2<T>))
-             : 1;
+__device__ __forceinline__ void pass_a_plane(const C2<T> *__restrict__ xb,
+                                             const int32_t *__restrict__ box_index, int s0, int s1,
+                                             int off, const double2 *__restrict__ twg,
+                                             C2<T> *__restrict__ dst, C2<T> *buf, C2<T> *tw) {
+  constexpr int NXY = N * N, LD = cld<N>(), CT = cthreads<N, N>();
+  // the plane's sphere rows (a disk: at most pi/4 of it when the sphere fits the
+  // box) are fetched before the plane is cleared, all in flight together
+  constexpr int FULL = (NXY * 4 / 5 + CT - 1) / CT, U = FULL < 6 ? FULL : 6;
+  T xr[U], xi[U];
+  int xe[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int idx = min(s0 + (int)threadIdx.x + u * CT, s1 - 1);
+    const C2<T> v = xb[idx];
+    xr[u] = v.x;
+    xi[u] = v.y;
+    xe[u] = box_index[idx] - off;
+  }
+  for (int i = threadIdx.x; i < N; i += CT) tw[i] = to_c2<T>(twg[i]);
+  for (int i = threadIdx.x; i < N * LD; i += CT) buf[i] = C2<T>{0, 0};
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (s0 + (int)threadIdx.x + u * CT < s1)
+      buf[(xe[u] / N) * LD + xe[u] % N] = C2<T>{xr[u], xi[u]};
+  for (int idx = s0 + threadIdx.x + U * CT; idx < s1; idx += CT) {
+    const int e = box_index[idx] - off;
+    buf[(e / N) * LD + e % N] = xb[idx];
+  }
+  __syncthreads();
+  cfft<T, N, 0, 1, N, 1, LD, +1, 1, 0, CT>(buf, tw);  // x: N pencils of stride-1 elements
+  // y: pencil i1, element i2; the last stage writes the box plane
+  auto ldm = [&](int pa, int e) { return buf[pa + e * LD]; };
+  auto stm = [&](int pa, int e, C2<T> v) { buf[pa + e * LD] = v; };
+  auto stg = [&](int pa, int e, C2<T> v) { dst[pa + e * N] = v; };
+  cfft_io<T, N, 0, 1, N, +1, true, false, CT>(tw, ldm, stg, ldm, stm);
 }
 
+// The transforms of pass C: the box plane src -> forward y and x transforms in buf
+// (element (i1, i2) at i2 cld<N>() + i1).
+template <typename T, int N>
+__device__ __forceinline__ void pass_c_plane(const C2<T> *__restrict__ src,
+                                             const double2 *__restrict__ twg, C2<T> *buf,
+                                             C2<T> *tw) {
+  constexpr int LD = cld<N>(), CT = cthreads<N, N>();
+  for (int i = threadIdx.x; i < N; i += CT) tw[i] = to_c2<T>(twg[i]);
+  __syncthreads();
+  // y: pencil i1, element i2; the first stage reads the box plane
+  auto ldm = [&](int pa, int e) { return buf[pa + e * LD]; };
+  auto stm = [&](int pa, int e, C2<T> v) { buf[pa + e * LD] = v; };
+  auto ldg = [&](int pa, int e) { return src[pa + e * N]; };
+  cfft_io<T, N, 0, 1, N, -1, false, true, CT>(tw, ldg, stm, ldm, stm);
+  cfft<T, N, 0, 1, N, 1, LD, -1, 1, 0, CT>(buf, tw);
+}
+
+// Reciprocal z-planes that hold sphere points, one bit each.
+struct ZOcc {
+  uint64_t lo, hi;
+};
+
+// z pencils per workgroup: 512 bytes of neighbouring pencils (64 complex64, 32
+// complex128), so that every element row of a load or store is a whole run of
+// 512 contiguous bytes whatever the plane's edges are (the pencils of a box are
+// numbered i1 + n1 i2: a slab of one i2 would give rows of n1 elements, 288
+// bytes and 216 of 512 threads busy at 36), and an LDS row is one bank sweep.
+template <typename T> constexpr int zpencils() { return 512 / (int)sizeof(C2<T>); }
+
+// Work of a z pass: the filter's pass B (inverse z transform, times V, forward
+// transform), the inverse transform alone (density, adjoint's forward bands), or
+// the adjoint's pass B (also Re[conj(adjoint) * forward] over the forward band).
+enum { Z_FILTER = 0, Z_INVERSE = 1, Z_ADJOINT = 2 };
+
+// z pass of the pencils [0, left) (at most zpencils) of a box whose planes hold nxy
+// elements: src, fw and v point at the first pencil's plane-0 element; tw3: the
+// transform's twiddles.
+template <typename T, int N, int MODE>
+__device__ __forceinline__ void z_pencils(C2<T> *__restrict__ src, C2<T> *__restrict__ fw,
+                                          const T *__restrict__ v, int left, int nxy,
+                                          const double2 *__restrict__ twg, ZOcc zocc, C2<T> *buf,
+                                          C2<T> *tw) {
+  constexpr int Q = zpencils<T>(), CT = cthreads<N, Q>();
+  for (int i = threadIdx.x; i < N; i += CT) tw[i] = to_c2<T>(twg[i]);
+  __syncthreads();
+  auto ldm = [&](int pa, int e) { return buf[pa + e * Q]; };
+  auto stm = [&](int pa, int e, C2<T> x) { buf[pa + e * Q] = x; };
+  // reciprocal planes g3 without sphere points: zero in (pass A leaves them
+  // unwritten), not written out (pass C does not read them)
+  auto occ = [&](int e) { return (((N > 64 && e >= 64 ? zocc.hi : zocc.lo) >> (e & 63)) & 1) != 0; };
+  // (every load is issued: a pencil past the end reads the last one, an empty
+  // plane's element plane 0's, which the workgroup reads anyway; a branch around
+  // each load kept them from overlapping, 48 against 40 us per 64 64^3 complex64
+  // boxes)
+  auto ldg = [&](int pa, int e) {
+    const bool in = occ(e);
+    const C2<T> x = src[min(pa, left - 1) + (in ? e * nxy : 0)];
+    return in ? x : C2<T>{0, 0};
+  };
+  if constexpr (MODE == Z_INVERSE) {  // real space out: all planes
+    auto stg = [&](int pa, int e, C2<T> x) {
+      if (pa < left) src[pa + e * nxy] = x;
+    };
+    cfft_io<T, N, 0, 1, Q, +1, false, false, CT>(tw, ldg, stg, ldm, stm);
+  } else {
+    // V (and the forward band) fetched ahead of the stage that multiplies by it
+    struct Pre {
+      T v;
+      C2<T> y;
+    };
+    auto pre = [&](int pa, int e) {
+      const int r = min(pa, left - 1) + e * nxy;
+      Pre p{v[r], C2<T>{0, 0}};
+      if constexpr (MODE == Z_ADJOINT) p.y = fw[r];
+      return p;
+    };
+    auto stv = [&](int pa, int e, C2<T> x, const Pre &p) {
+      if constexpr (MODE == Z_ADJOINT)
+        if (pa < left) fw[pa + e * nxy] = C2<T>{x.x * p.y.x + x.y * p.y.y, (T)0};
+      buf[pa + e * Q] = cscale(x, p.v);
+    };
+    auto stg = [&](int pa, int e, C2<T> x) {
+      if (pa < left && occ(e)) src[pa + e * nxy] = x;
+    };
+    cfft_io<T, N, 0, 1, Q, +1, false, true, CT>(tw, ldg, stv, ldm, stm, pre);
+    cfft_io<T, N, 0, 1, Q, -1, true, false, CT>(tw, ldm, stg, ldm, stm);
+  }
+}
+
+// Edges with compile-time transforms.
+#define CHEBFI_EDGES(X)                                                                         \
+  X(12) X(15) X(16) X(18) X(20) X(24) X(25) X(27) X(30) X(32) X(36) X(40) X(45) X(48) X(50) \
+  X(54) X(60) X(64) X(72) X(75) X(80) X(81) X(90) X(96)
+
+inline bool listed_edge(int n) {
+#define CHEBFI_CASE(N_) case N_:
+  switch (n) {
+    CHEBFI_EDGES(CHEBFI_CASE)
+    return true;
+    default:
+      return false;
+  }
+#undef CHEBFI_CASE
+}
 
 }  // namespace
 }  // namespace chebfi

@@ -171,7 +171,7 @@ struct BatchSys {
   int npt = 0;                // projector tiles of kBatchPT
   const int32_t *box_index = nullptr;
   const int32_t *plane = nullptr;
-  uint64_t zocc = ~0ull;      // bit i3: z-plane i3 holds sphere points
+  uint64_t zocc = 0, zocc_hi = 0;  // bit i3: z-plane i3 holds sphere points
   const double *kin = nullptr;
   const void *V = nullptr;    // float (complex64 blocks) or double
   const double2 *tw = nullptr;
@@ -196,14 +196,14 @@ struct BatchStep {
 };
 
 // Systems of one cubic edge n with specialised passes: their indices and the
-// prefix offsets of their items (bands x n per system).
+// prefix offsets of their bands.
 struct BatchGroup {
   int n = 0, nsys = 0;
   const int32_t *gsys = nullptr;
   const int64_t *goff = nullptr;
-  int64_t items = 0;
+  int64_t bands = 0;
 };
-constexpr int kBatchMaxGroups = 16;
+constexpr int kBatchMaxGroups = 24;  // as many as there are specialised edges
 
 // What one batched step launches (device pointers and launch shapes).
 struct BatchLaunch {

@@ -291,8 +291,6 @@ void batch_step(const BatchLaunch &L, int j, hipStream_t st, hipStream_t side = 
                 hipEvent_t fork = nullptr, hipEvent_t join = nullptr);
 // True if batched systems on a cubic box of this edge get specialised passes.
 bool batch_edge_specialised(int n);
-// planes (slabs) of one band per work item of the specialised batched passes
-int batch_item_planes(int n, bool fp32);
 // Sets the dynamic LDS limits of the batched kernels (call outside graph capture).
 template <typename T> void batch_prepare(const BatchLaunch &L);
 
