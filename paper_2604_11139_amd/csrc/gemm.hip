@@ -254,6 +254,125 @@ __global__ __launch_bounds__(256, 3) void zgemm_kernel(int64_t m, int64_t n, int
       }
 }
 
+// The same product for outputs of few tiles: 32 x 32 per workgroup and K split over
+// its four waves inside each staged slice of 32, their sums meeting in LDS.  The
+// FP64 matrix cores set the time of a tile (16 K of 64 x 64 take a compute unit
+// 1.7 us), so an output of fewer 64 x 64 tiles than half the compute units leaves
+// most of the chip idle for K / 16 such steps in sequence: 256 x 512 x 256 took 42
+// us, about 17 here.  MODE 1 as above.
+constexpr int SB = 32, SK = 32;
+template <int OPA, int OPB, int MODE>
+__global__ __launch_bounds__(256) void zgemm_small_kernel(
+    int64_t m, int64_t n, int64_t k, const double2 *__restrict__ A, int64_t lda,
+    const double2 *__restrict__ B, int64_t ldb, double2 *__restrict__ C, int64_t ldc,
+    double2 alpha, double2 beta, int64_t sa, int64_t sb, int64_t sc) {
+  typedef Mma<double>::acc Acc;
+  __shared__ union {
+    struct {
+      double a[2][SK][SB + PAD], b[2][SK][SB + PAD];
+    } st;
+    double2 red[4][SB][SB];
+  } sh;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int64_t row0 = (int64_t)blockIdx.x * SB, col0 = (int64_t)blockIdx.y * SB;
+  if constexpr (MODE == 1) {
+    int64_t ti, tj;
+    upper_tile(blockIdx.x, ti, tj);
+    row0 = ti * SB;
+    col0 = tj * SB;
+  } else {
+    A += (int64_t)blockIdx.z * sa;
+    B += (int64_t)blockIdx.z * sb;
+    C += (int64_t)blockIdx.z * sc;
+  }
+  Acc re[2][2], im[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) re[i][j] = im[i][j] = Acc{0, 0, 0, 0};
+  // (the thread-fastest index follows each operand's contiguous axis)
+  const int lo = tid & 31, hi = tid >> 5;
+  double2 ra[4], rb[4];
+  auto load = [&](int64_t k0) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int64_t gr = row0 + (OPA == OP_N ? lo : hi + 8 * c);
+      const int64_t ga = k0 + (OPA == OP_N ? hi + 8 * c : lo);
+      ra[c] = double2{0, 0};
+      if (gr < m && ga < k) ra[c] = OPA == OP_N ? A[gr + ga * lda] : A[ga + gr * lda];
+      const int64_t gc = col0 + (OPB == OP_N ? hi + 8 * c : lo);
+      const int64_t gb = k0 + (OPB == OP_N ? lo : hi + 8 * c);
+      rb[c] = double2{0, 0};
+      if (gc < n && gb < k) rb[c] = OPB == OP_N ? B[gb + gc * ldb] : B[gc + gb * ldb];
+    }
+  };
+  load(0);
+  for (int64_t k0 = 0; k0 < k; k0 += SK) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int x = OPA == OP_N ? lo : hi + 8 * c, xk = OPA == OP_N ? hi + 8 * c : lo;
+      sh.st.a[0][xk][x] = ra[c].x;
+      sh.st.a[1][xk][x] = OPA == OP_C ? -ra[c].y : ra[c].y;
+      const int y = OPB == OP_N ? hi + 8 * c : lo, yk = OPB == OP_N ? lo : hi + 8 * c;
+      sh.st.b[0][yk][y] = rb[c].x;
+      sh.st.b[1][yk][y] = OPB == OP_C ? -rb[c].y : rb[c].y;
+    }
+    __syncthreads();
+    if (k0 + SK < k) load(k0 + SK);
+#pragma unroll
+    for (int kq = 0; kq < 2; ++kq) {
+      const int kk = wave * 8 + kq * 4 + (lane >> 4);
+      if (k0 + wave * 8 + kq * 4 >= k) break;  // (a slice shorter than its waves)
+      double ar[2], ai[2], br[2], bi[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int x = i * 16 + (lane & 15);
+        ar[i] = sh.st.a[0][kk][x];
+        ai[i] = sh.st.a[1][kk][x];
+        br[i] = sh.st.b[0][kk][x];
+        bi[i] = sh.st.b[1][kk][x];
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          re[i][j] = Mma<double>::run(br[j], ar[i], re[i][j]);
+          im[i][j] = Mma<double>::run(bi[j], ar[i], im[i][j]);
+        }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          re[i][j] = Mma<double>::run(bi[j], -ai[i], re[i][j]);
+          im[i][j] = Mma<double>::run(br[j], ai[i], im[i][j]);
+        }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        sh.red[wave][j * 16 + Mma<double>::row(lane, r)][i * 16 + (lane & 15)] =
+            double2{re[i][j][r], im[i][j][r]};
+  __syncthreads();
+  const bool use_beta = (beta.x != 0.0 || beta.y != 0.0);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int y = hi + 8 * c;
+    const double2 v = cadd(cadd(sh.red[0][y][lo], sh.red[1][y][lo]),
+                           cadd(sh.red[2][y][lo], sh.red[3][y][lo]));
+    const int64_t row = row0 + lo, col = col0 + y;
+    if (row < m && col < n) {
+      double2 o = cmul(alpha, v);
+      if (use_beta) o = cadd(o, cmul(beta, C[row + col * ldc]));
+      C[row + col * ldc] = o;
+    }
+  }
+}
+
 __global__ void zsum_parts_kernel(int64_t m, int64_t n, const double2 *__restrict__ part,
                                   int splits, double2 *__restrict__ C, int64_t ldc, double2 alpha,
                                   double2 beta) {
@@ -303,28 +422,6 @@ __global__ __launch_bounds__(256) void zsum_herm_kernel(int64_t m, const C2<T> *
   }
 }
 
-template <typename T, int OPA, int OPB, int TAG>
-void launch_t(int64_t m, int64_t n, int64_t k, const void *A, int64_t lda, const void *B,
-              int64_t ldb, void *C, int64_t ldc, double2 alpha, double2 beta, hipStream_t st,
-              void *part, int splits, int64_t batch = 1, int64_t sa = 0, int64_t sb = 0,
-              int64_t sc = 0) {
-  typedef C2<T> V2;
-  const int64_t chunk = part ? ((k + splits - 1) / splits + BK - 1) / BK * BK : k;
-  // every chunk index gets launched; a chunk past the end of K writes zeros
-  const int64_t zs = part ? splits : batch;
-  dim3 grid((unsigned)((m + BM - 1) / BM), (unsigned)((n + BN - 1) / BN), (unsigned)zs);
-  if (part) {
-    hipLaunchKernelGGL((zgemm_kernel<T, OPA, OPB, true, TAG>), grid, dim3(256), 0, st, m, n, k,
-                       (const V2 *)A, lda, (const V2 *)B, ldb, (V2 *)C, ldc, alpha, beta, chunk,
-                       (V2 *)part, sa, sb, sc);
-  } else {
-    hipLaunchKernelGGL((zgemm_kernel<T, OPA, OPB, false, TAG>), grid, dim3(256), 0, st, m, n, k,
-                       (const V2 *)A, lda, (const V2 *)B, ldb, (V2 *)C, ldc, alpha, beta, chunk,
-                       (V2 *)nullptr, sa, sb, sc);
-  }
-  CHEBFI_HIP(hipGetLastError());
-}
-
 }  // namespace
 
 // Compute units of the current device (cached per device).
@@ -341,6 +438,48 @@ int device_cus() {
   }
   return cus[dev];
 }
+
+namespace {
+
+// 64 x 64 tiles up to which the 32 x 32 form is the faster one: four times as many
+// workgroups at a quarter of the time each, so it wins until they need more than two
+// rounds of the compute units.
+bool small_output(int64_t tiles64) { return 2 * tiles64 <= device_cus(); }
+
+template <typename T, int OPA, int OPB, int TAG>
+void launch_t(int64_t m, int64_t n, int64_t k, const void *A, int64_t lda, const void *B,
+              int64_t ldb, void *C, int64_t ldc, double2 alpha, double2 beta, hipStream_t st,
+              void *part, int splits, int64_t batch = 1, int64_t sa = 0, int64_t sb = 0,
+              int64_t sc = 0) {
+  typedef C2<T> V2;
+  const int64_t chunk = part ? ((k + splits - 1) / splits + BK - 1) / BK * BK : k;
+  // every chunk index gets launched; a chunk past the end of K writes zeros
+  const int64_t zs = part ? splits : batch;
+  if constexpr (std::is_same<T, double>::value) {
+    if (!part && small_output(((m + BM - 1) / BM) * ((n + BN - 1) / BN) * batch)) {
+      hipLaunchKernelGGL((zgemm_small_kernel<OPA, OPB, 0>),
+                         dim3((unsigned)((m + SB - 1) / SB), (unsigned)((n + SB - 1) / SB),
+                              (unsigned)batch),
+                         dim3(256), 0, st, m, n, k, (const double2 *)A, lda, (const double2 *)B,
+                         ldb, (double2 *)C, ldc, alpha, beta, sa, sb, sc);
+      CHEBFI_HIP(hipGetLastError());
+      return;
+    }
+  }
+  dim3 grid((unsigned)((m + BM - 1) / BM), (unsigned)((n + BN - 1) / BN), (unsigned)zs);
+  if (part) {
+    hipLaunchKernelGGL((zgemm_kernel<T, OPA, OPB, true, TAG>), grid, dim3(256), 0, st, m, n, k,
+                       (const V2 *)A, lda, (const V2 *)B, ldb, (V2 *)C, ldc, alpha, beta, chunk,
+                       (V2 *)part, sa, sb, sc);
+  } else {
+    hipLaunchKernelGGL((zgemm_kernel<T, OPA, OPB, false, TAG>), grid, dim3(256), 0, st, m, n, k,
+                       (const V2 *)A, lda, (const V2 *)B, ldb, (V2 *)C, ldc, alpha, beta, chunk,
+                       (V2 *)nullptr, sa, sb, sc);
+  }
+  CHEBFI_HIP(hipGetLastError());
+}
+
+}  // namespace
 
 // Split-K count for `tiles` output tiles when `per_cu` workgroups fit on a CU:
 // the launch runs in ceil(tiles * s / slots) rounds of slots = CUs x per_cu
@@ -415,7 +554,15 @@ void zgemm_herm(int64_t m, int64_t k, const void *A, int64_t lda, const void *B,
 void zgemm_herm_update(int64_t m, int64_t k, const void *A, int64_t lda, void *C, int64_t ldc,
                        hipStream_t st) {
   if (m <= 0) return;
-  const int64_t nt = (m + BM - 1) / BM;
+  const int64_t nt = (m + BM - 1) / BM, ns = (m + SB - 1) / SB;
+  if (small_output(nt * (nt + 1) / 2)) {
+    hipLaunchKernelGGL((zgemm_small_kernel<OP_C, OP_N, 1>), dim3((unsigned)(ns * (ns + 1) / 2)),
+                       dim3(256), 0, st, m, m, k, (const double2 *)A, lda, (const double2 *)A, lda,
+                       (double2 *)C, ldc, double2{-1, 0}, double2{1, 0}, (int64_t)0, (int64_t)0,
+                       (int64_t)0);
+    CHEBFI_HIP(hipGetLastError());
+    return;
+  }
   hipLaunchKernelGGL((zgemm_kernel<double, OP_C, OP_N, false, 0, 1>),
                      dim3((unsigned)(nt * (nt + 1) / 2)), dim3(256), 0, st, m, m, k,
                      (const double2 *)A, lda, (const double2 *)A, lda, (double2 *)C, ldc,
