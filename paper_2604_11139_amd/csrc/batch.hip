@@ -493,7 +493,7 @@ __global__ __launch_bounds__((cthreads<N, zpencils<T>()>())) void bcpass_b_kerne
   // z-planes without sphere points: zero on input (pass A leaves them unwritten)
   // and not written on output (pass C does not read them)
   C2<T> *src = as_global((C2<T> *)d.box) + b * (int64_t)NXY * N + q0;
-  z_pencils<T, N, Z_FILTER>(src, src, as_global((const T *)d.V) + q0, NXY - q0, NXY,
+  z_pencils<T, N>(src, as_global((const T *)d.V) + q0, NXY - q0, NXY,
                             as_global(d.tw) + 2 * kMaxN, ZOcc{d.zocc, d.zocc_hi}, buf, tw);
 }
 

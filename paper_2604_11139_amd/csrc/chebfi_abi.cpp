@@ -1468,23 +1468,33 @@ abi_status abi_filter_backward(abi_system s, const void *X, const void *W, int64
         const void *Ak1 = (k + 1 == m) ? W : (const void *)abuf[(k + 1) % 3];
         const int64_t lda1 = (k + 1 == m) ? ld : npw;
         void *Ak = abuf[k % 3];
-        const bool acc = (k + 1 < m);
-        // the adjoint local part runs beside the projections, as in the forward step
+        // A_k = gamma_k (H - c) A_{k+1} - delta_{k+1} A_{k+2}  (A_m = W)
+        const void *Ak2 = (k + 2 > m) ? nullptr : (k + 2 == m) ? W : (const void *)abuf[(k + 2) % 3];
+        const int64_t lda2 = (k + 2 == m) ? ld : npw;
+        const double dk = (k + 1 < m) ? del[k + 1] : 0.0;
+        // the adjoint local part runs beside the projections, as in the forward step;
+        // otherwise, with the split-BF16 products, it follows them and adds their
+        // expansion E while it writes A_k
         const bool side = s->overlap && nproj > 0 && s->aux;
+        const bool pre = !side && nproj > 0 && planes;
         hipStream_t fst = side ? s->aux : st;
+        void *E = pre ? s->expout.get(esz * (size_t)npw * nband) : nullptr;
+        auto local = [&] {
+          for (int64_t b0 = 0; b0 < nband; b0 += fb) {
+            const int nb = (int)std::min<int64_t>(fb, nband - b0);
+            if (fp32)
+              launch_adjoint_local<float>(s, Ak1, lda1, Yk, ldy, Ak2, lda2, dk, Ak, npw, (int)b0,
+                                          nb, box1, box2, s->d_Vf, gam[k], c, E, npw, dV_acc, fst);
+            else
+              launch_adjoint_local<double>(s, Ak1, lda1, Yk, ldy, Ak2, lda2, dk, Ak, npw, (int)b0,
+                                           nb, box1, box2, s->d_V, gam[k], c, E, npw, dV_acc, fst);
+          }
+        };
         if (side) {
           CHEBFI_HIP(hipEventRecord(s->ev_fork, st));
           CHEBFI_HIP(hipStreamWaitEvent(s->aux, s->ev_fork, 0));
         }
-        for (int64_t b0 = 0; b0 < nband; b0 += fb) {
-          const int nb = (int)std::min<int64_t>(fb, nband - b0);
-          if (fp32)
-            launch_adjoint_local<float>(s, Ak1, lda1, Yk, ldy, Ak, npw, acc, (int)b0, nb, box1,
-                                        box2, s->d_Vf, gam[k], c, dV_acc, fst);
-          else
-            launch_adjoint_local<double>(s, Ak1, lda1, Yk, ldy, Ak, npw, acc, (int)b0, nb, box1,
-                                         box2, s->d_V, gam[k], c, dV_acc, fst);
-        }
+        if (!pre) local();
         if (side) CHEBFI_HIP(hipEventRecord(s->ev_join, s->aux));
         if (nproj > 0) {
           project(Ak1, lda1, CA);
@@ -1494,18 +1504,23 @@ abi_status abi_filter_backward(abi_system s, const void *X, const void *W, int64
           else
             project(Yk, ldy, CY);
           launch_dd_accum(natom, nband, CA, cy, gam[k], dD_acc, st, fp32);
-          launch_dapply(natom, nband, CA, 1, s->d_D, gam[k], Cp, st, fp32);
+          if (!pre)
+            launch_dapply(natom, nband, CA, 1, s->d_D, gam[k], Cp, st, fp32);
         }
         if (side) CHEBFI_HIP(hipStreamWaitEvent(st, s->ev_join, 0));
-        if (nproj > 0) {
+        if (pre) {
+          // straight into the expansion's planes
+          launch_dapply(natom, nband, CA, 1, s->d_D, gam[k], nullptr, st, fp32, nullptr,
+                        s->cplanes.get(8 * (size_t)s->ldPB * nband), s->ldPB);
+          mixed_expand(s, nullptr, E, npw, nband, st, false);
+          local();
+        } else if (nproj > 0) {
           if (planes)
             mixed_expand(s, Cp, Ak, npw, nband, st, true);
           else
             expand_gemm(npw, nband, nproj, fp32 ? (const void *)s->d_Pf : (const void *)s->d_P,
                         Cp, Ak, npw, st, fp32);
         }
-        if (k >= 1)
-          launch_scale_neg(npw, nband, Ak1, lda1, del[k], abuf[(k + 2) % 3], npw, st, fp32);
       }
     }
     CHEBFI_HIP(hipMemcpyAsync(dV, dV_acc, sizeof(double) * nbox, hipMemcpyDeviceToDevice, st));

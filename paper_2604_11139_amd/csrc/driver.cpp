@@ -84,7 +84,8 @@ void mixed_project(abi_system_s *s, const void *X, int64_t ldx, int64_t nband, v
 void mixed_expand(abi_system_s *s, const void *Cp, void *Out, int64_t ldo, int64_t nband,
                   hipStream_t st, bool accumulate) {
   const int nproj = s->nproj;
-  split_planes(nproj, nband, Cp, nproj, s->cplanes.get(8 * (size_t)s->ldPB * nband), s->ldPB, st);
+  if (Cp)
+    split_planes(nproj, nband, Cp, nproj, s->cplanes.get(8 * (size_t)s->ldPB * nband), s->ldPB, st);
   expand_gemm_planes(s->npw, nband, nproj, s->d_PB, s->ldPB, s->npw * s->ldPB, s->cplanes.ptr,
                      s->ldPB, s->ldPB * nband, Out, ldo, st, s->pl_expand, accumulate);
 }

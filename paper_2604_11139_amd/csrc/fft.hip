@@ -308,16 +308,142 @@ __global__ __launch_bounds__((cthreads<N, N>())) void cpass_a_kernel(
                      box + (int64_t)bl * N * N * gridDim.x + off, buf, tw);
 }
 
-template <typename T, int N, int MODE>
+template <typename T, int N>
 __global__ __launch_bounds__((cthreads<N, zpencils<T>()>())) void zpass_kernel(
-    C2<T> *__restrict__ box, C2<T> *__restrict__ fwd, const T *__restrict__ V, int nxy,
-    const double2 *__restrict__ twg, ZOcc zocc) {
+    C2<T> *__restrict__ box, const T *__restrict__ V, int nxy, const double2 *__restrict__ twg,
+    ZOcc zocc) {
   constexpr int Q = zpencils<T>();
   __shared__ C2<T> buf[N * Q];
   __shared__ C2<T> tw[N];
   const int q0 = blockIdx.x * Q;
-  const int64_t o = (int64_t)blockIdx.y * nxy * N + q0;
-  z_pencils<T, N, MODE>(box + o, fwd + o, V + q0, nxy - q0, nxy, twg + 2 * kMaxN, zocc, buf, tw);
+  z_pencils<T, N>(box + (int64_t)blockIdx.y * nxy * N + q0, V + q0, nxy - q0, nxy,
+                  twg + 2 * kMaxN, zocc, buf, tw);
+}
+
+// A partial sum in FP64 kept in one box element.
+__device__ __forceinline__ void put_sum(C2<double> &x, double s) { x = C2<double>{s, 0.0}; }
+__device__ __forceinline__ void put_sum(C2<float> &x, double s) {
+  x = C2<float>{__int_as_float(__double2loint(s)), __int_as_float(__double2hiint(s))};
+}
+__device__ __forceinline__ double get_sum(const C2<double> &x) { return x.x; }
+__device__ __forceinline__ double get_sum(const C2<float> &x) {
+  return __hiloint2double(__float_as_int(x.y), __float_as_int(x.x));
+}
+
+// Real-space sums over bands without a real-space box in memory.  A workgroup takes
+// one run of pencils and `per` bands in turn: the inverse z transform's last stage
+// leaves real space in registers, each thread the same points for every band, and
+// the workgroup's sums (FP64, bands in order) end up in its first band's box of
+// `fwd`, whose pencils no other workgroup reads.
+//   ADJ = false, the density: sum_b w_b |psi_b(r)|^2 from the boxes fwd;
+//   ADJ = true, the adjoint's pass B: sum_b Re[conj(a_b) y_b] with the adjoint
+//   bands a in `box` and the forward bands y in `fwd`, and box <- the forward
+//   transform of V a.
+// One butterfly of the last stage per thread: with the filter's thread counts the
+// sums, V and two bands' values of two or three butterflies spilled (96: 252 B).
+template <typename T, int N> constexpr int zaccum_threads() {
+  return (zpencils<T>() * (N / CPlan<N>::r[1]) + 63) / 64 * 64;
+}
+template <typename T, int N, bool ADJ>
+__global__ __launch_bounds__((zaccum_threads<T, N>())) void zaccum_kernel(
+    C2<T> *__restrict__ box, C2<T> *__restrict__ fwd, const T *__restrict__ V,
+    const double *__restrict__ w, int nxy_, const double2 *__restrict__ twg, ZOcc zocc, int nb,
+    int per) {
+  constexpr int Q = zpencils<T>(), CT = zaccum_threads<T, N>();
+  static_assert(CPlan<N>::ns == 2, "two-stage transforms");
+  constexpr int R0 = CPlan<N>::r[0], R = CPlan<N>::r[1], MB = cstage_rounds<N, R, Q, CT>();
+  __shared__ C2<T> buf[N * Q];
+  __shared__ C2<T> tw[N];
+  const int q0 = blockIdx.x * Q, left = nxy_ - q0;
+  for (int i = threadIdx.x; i < N; i += CT) tw[i] = to_c2<T>(twg[2 * kMaxN + i]);
+  __syncthreads();
+  auto ldm = [&](int pa, int e) { return buf[pa + e * Q]; };
+  auto stm = [&](int pa, int e, C2<T> x) { buf[pa + e * Q] = x; };
+  double acc[MB][R];
+#pragma unroll
+  for (int c = 0; c < MB; ++c)
+#pragma unroll
+    for (int t = 0; t < R; ++t) acc[c][t] = 0.0;
+  const int b1 = min(nb, ((int)blockIdx.y + 1) * per);
+  for (int b = blockIdx.y * per; b < b1; ++b) {
+    const int64_t o = (int64_t)b * nxy_ * N + q0;
+    // opaque per band: otherwise every offset of the box is kept across bands, in
+    // more registers than the sums
+    int nxy = nxy_;
+    asm volatile("" : "+s"(nxy));
+    const C2<T> *f = fwd + o;
+    auto ldf = [&](int pa, int e) { return z_load<T, N>(f, zocc, left, nxy, pa, e); };
+    cstage_io<T, N, R0, 1, Q, +1, false, CT>(tw, ldf, stm);
+    __syncthreads();
+    C2<T> y[MB][R];
+    cstage_vals<T, N, R, R0, Q, +1, CT>(tw, ldm, y);
+    __syncthreads();
+    if constexpr (!ADJ) {
+      const double wb = w ? w[b] : 1.0;
+#pragma unroll
+      for (int c = 0; c < MB; ++c)
+#pragma unroll
+        for (int t = 0; t < R; ++t)
+          acc[c][t] += wb * ((double)y[c][t].x * y[c][t].x + (double)y[c][t].y * y[c][t].y);
+    } else {
+      C2<T> *a = box + o;
+      auto lda = [&](int pa, int e) { return z_load<T, N>(a, zocc, left, nxy, pa, e); };
+      cstage_io<T, N, R0, 1, Q, +1, false, CT>(tw, lda, stm);
+      T v[MB][R];
+#pragma unroll
+      for (int c = 0; c < MB; ++c) {
+        int pa, e0;
+        cstage_at<N, R, R0, Q, CT>(c, pa, e0);
+#pragma unroll
+        for (int t = 0; t < R; ++t)
+          v[c][t] = V[q0 + min(pa, left - 1) + min(e0 + t * R0, N - 1) * nxy];
+      }
+      __syncthreads();
+      C2<T> x[MB][R];
+      cstage_vals<T, N, R, R0, Q, +1, CT>(tw, ldm, x);
+      __syncthreads();
+#pragma unroll
+      for (int c = 0; c < MB; ++c) {
+        int pa, e0;
+        if (cstage_at<N, R, R0, Q, CT>(c, pa, e0)) {
+#pragma unroll
+          for (int t = 0; t < R; ++t) {
+            acc[c][t] += (double)(x[c][t].x * y[c][t].x + x[c][t].y * y[c][t].y);
+            buf[pa + (e0 + t * R0) * Q] = cscale(x[c][t], v[c][t]);
+          }
+        }
+      }
+      __syncthreads();
+      auto stg = [&](int pa, int e, C2<T> z) {
+        if (pa < left && z_occupied<N>(zocc, e)) a[pa + e * nxy] = z;
+      };
+      cfft_io<T, N, 0, 1, Q, -1, true, false, CT>(tw, ldm, stg, ldm, stm);
+      __syncthreads();
+    }
+  }
+  // (the barriers above stand between the last band's loads and these stores)
+  C2<T> *out = fwd + (int64_t)blockIdx.y * per * nxy_ * N + q0;
+#pragma unroll
+  for (int c = 0; c < MB; ++c) {
+    int pa, e0;
+    if (cstage_at<N, R, R0, Q, CT>(c, pa, e0) && pa < left) {
+#pragma unroll
+      for (int t = 0; t < R; ++t) put_sum(out[pa + (e0 + t * R0) * nxy_], acc[c][t]);
+    }
+  }
+}
+
+// out[r] += scale * the sum of element r of boxes 0, per, 2 per, ... (in order).
+template <typename T>
+__global__ __launch_bounds__(256) void zaccum_sum_kernel(int64_t nbox, int groups, int per,
+                                                         const C2<T> *__restrict__ part,
+                                                         double scale, double *__restrict__ out) {
+  const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (r >= nbox) return;
+  double s = 0.0;
+#pragma unroll 8
+  for (int g = 0; g < groups; ++g) s += get_sum(part[(int64_t)g * per * nbox + r]);
+  out[r] += scale * s;
 }
 
 // (Gathering two or three rows per thread at once, all their loads in flight
@@ -428,10 +554,10 @@ void launch_a(const abi_system_s *s, const void *X, int64_t ldx, int band0, int 
   CHEBFI_HIP(hipGetLastError());
 }
 
-// z pass of nb boxes (`fwd`: the forward bands' boxes, Z_ADJOINT only).
-template <typename T, int MODE>
-void launch_z(const abi_system_s *s, void *box, void *fwd, const void *V, int nb, hipStream_t st) {
-  C2<T> *bx = reinterpret_cast<C2<T> *>(box), *fw = reinterpret_cast<C2<T> *>(fwd);
+// Pass B of nb boxes.
+template <typename T>
+void launch_z(const abi_system_s *s, void *box, const void *V, int nb, hipStream_t st) {
+  C2<T> *bx = reinterpret_cast<C2<T> *>(box);
   const T *v = reinterpret_cast<const T *>(V);
   const double2 *tw = reinterpret_cast<const double2 *>(s->d_tw);
   if (special_z(s)) {
@@ -439,27 +565,45 @@ void launch_z(const abi_system_s *s, void *box, void *fwd, const void *V, int nb
     const int nxy = s->n1 * s->n2;
     const dim3 grid((nxy + Q - 1) / Q, nb);
     const ZOcc occ{s->zocc, s->zocc_hi};
-#define CHEBFI_CASE(N_)                                                                           \
-  case N_:                                                                                        \
-    hipLaunchKernelGGL((zpass_kernel<T, N_, MODE>), grid, dim3(cthreads<N_, Q>()), 0, st, bx, fw, \
-                       v, nxy, tw, occ);                                                          \
+#define CHEBFI_CASE(N_)                                                                          \
+  case N_:                                                                                       \
+    hipLaunchKernelGGL((zpass_kernel<T, N_>), grid, dim3(cthreads<N_, Q>()), 0, st, bx, v, nxy, \
+                       tw, occ);                                                                 \
     break;
     switch (s->n3) { CHEBFI_EDGES(CHEBFI_CASE) }
 #undef CHEBFI_CASE
   } else {
     const RuntimeShape<T> r(s->plan);
-    const dim3 grid(s->n2, nb), threads(r.tB);
-    if constexpr (MODE == Z_FILTER) {
-      set_lds(pass_b_kernel<T, T>, r.ldsB);
-      hipLaunchKernelGGL((pass_b_kernel<T, T>), grid, threads, r.ldsB, st, bx, v, s->plan, tw);
-    } else if constexpr (MODE == Z_INVERSE) {
-      set_lds(pass_b_inv_kernel<T>, r.ldsB);
-      hipLaunchKernelGGL(pass_b_inv_kernel<T>, grid, threads, r.ldsB, st, bx, s->plan, tw);
-    } else {
-      set_lds(pass_b_adj_kernel<T>, r.ldsB);
-      hipLaunchKernelGGL(pass_b_adj_kernel<T>, grid, threads, r.ldsB, st, bx, fw, v, s->plan, tw);
-    }
+    set_lds(pass_b_kernel<T, T>, r.ldsB);
+    hipLaunchKernelGGL((pass_b_kernel<T, T>), dim3(s->n2, nb), dim3(r.tB), r.ldsB, st, bx, v,
+                       s->plan, tw);
   }
+  CHEBFI_HIP(hipGetLastError());
+}
+
+// out += scale * the real-space sums of zaccum_kernel (listed n3 only).
+template <typename T, bool ADJ>
+void launch_zaccum(const abi_system_s *s, void *box, void *fwd, const void *V, const double *w,
+                   int nb, double scale, double *out, hipStream_t st) {
+  constexpr int Q = zpencils<T>();
+  const double2 *tw = reinterpret_cast<const double2 *>(s->d_tw);
+  const int nxy = s->n1 * s->n2, runs = (nxy + Q - 1) / Q;
+  const int64_t nbox = (int64_t)nxy * s->n3;
+  const ZOcc occ{s->zocc, s->zocc_hi};
+  // bands per workgroup: as many as leave six workgroups per CU
+  const int per = std::max<int>(1, (int)((int64_t)runs * nb / (6 * device_cus())));
+  const int groups = (nb + per - 1) / per;
+#define CHEBFI_CASE(N_)                                                                          \
+  case N_:                                                                                       \
+    hipLaunchKernelGGL((zaccum_kernel<T, N_, ADJ>), dim3(runs, groups),                          \
+                       dim3(zaccum_threads<T, N_>()), 0, st, (C2<T> *)box, (C2<T> *)fwd,         \
+                       (const T *)V, w, nxy, tw, occ, nb, per);                                  \
+    break;
+  switch (s->n3) { CHEBFI_EDGES(CHEBFI_CASE) }
+#undef CHEBFI_CASE
+  CHEBFI_HIP(hipGetLastError());
+  hipLaunchKernelGGL(zaccum_sum_kernel<T>, dim3((unsigned)((nbox + 255) / 256)), dim3(256), 0, st,
+                     nbox, groups, per, (const C2<T> *)fwd, scale, out);
   CHEBFI_HIP(hipGetLastError());
 }
 
@@ -510,7 +654,7 @@ void launch_local_potential(const abi_system_s *s, const void *Yk, int64_t ldk, 
   launch_a<T>(s, Yk, ldk, band0, nb, box, st);
   if (prof) prof->end(tok, st);
   tok = prof ? prof->begin(PROF_FFT_B, nb * 2.0 * nbx * es + nbx * (double)sizeof(T), st) : -1;
-  launch_z<T, Z_FILTER>(s, box, nullptr, V, nb, st);
+  launch_z<T>(s, box, V, nb, st);
   if (prof) prof->end(tok, st);
   tok = prof ? prof->begin(PROF_FFT_C,
                            nb * (nbx + np * ((Yprev ? 3.0 : 2.0) + (E ? 1.0 : 0.0))) * es, st)
@@ -522,28 +666,47 @@ void launch_local_potential(const abi_system_s *s, const void *Yk, int64_t ldk, 
 
 template <typename T>
 void launch_adjoint_local(const abi_system_s *s, const void *Ak1, int64_t lda1, const void *Yk,
-                          int64_t ldy, void *Ak, int64_t ldak, bool accumulate, int band0, int nb,
-                          void *box1, void *box2, const void *V, double gamma, double cshift,
-                          double *dV, hipStream_t st) {
+                          int64_t ldy, const void *Ak2, int64_t lda2, double delta, void *Ak,
+                          int64_t ldak, int band0, int nb, void *box1, void *box2, const void *V,
+                          double gamma, double cshift, const void *E, int64_t lde, double *dV,
+                          hipStream_t st) {
+  const int64_t nbox = (int64_t)s->n1 * s->n2 * s->n3;
   launch_a<T>(s, Ak1, lda1, band0, nb, box1, st);
   launch_a<T>(s, Yk, ldy, band0, nb, box2, st);
-  launch_z<T, Z_INVERSE>(s, box2, nullptr, nullptr, nb, st);
-  launch_z<T, Z_ADJOINT>(s, box1, box2, V, nb, st);
-  const int64_t nbox = (int64_t)s->n1 * s->n2 * s->n3;
-  hipLaunchKernelGGL(dv_reduce_kernel<T>, dim3((unsigned)((nbox + 255) / 256)), dim3(256), 0, st,
-                     nbox, nb, (const C2<T> *)box2, gamma / (double)nbox, dV);
-  CHEBFI_HIP(hipGetLastError());
-  // Ak = gamma (local + (kin - c) Ak1) + Ak   (beta = -1 adds the previous content)
-  launch_c<T>(s, box1, band0, nb, Ak1, lda1, accumulate ? Ak : nullptr, ldak, Ak, ldak, gamma,
-              cshift, -1.0, nullptr, 0, nullptr, PlanesOut{nullptr, 0, 0}, st);
+  if (special_z(s)) {
+    launch_zaccum<T, true>(s, box1, box2, V, nullptr, nb, gamma / (double)nbox, dV, st);
+  } else {
+    const RuntimeShape<T> r(s->plan);
+    const double2 *tw = reinterpret_cast<const double2 *>(s->d_tw);
+    const dim3 grid(s->n2, nb), threads(r.tB);
+    set_lds(pass_b_inv_kernel<T>, r.ldsB);
+    set_lds(pass_b_adj_kernel<T>, r.ldsB);
+    hipLaunchKernelGGL(pass_b_inv_kernel<T>, grid, threads, r.ldsB, st, (C2<T> *)box2, s->plan, tw);
+    hipLaunchKernelGGL(pass_b_adj_kernel<T>, grid, threads, r.ldsB, st, (C2<T> *)box1,
+                       (C2<T> *)box2, (const T *)V, s->plan, tw);
+    hipLaunchKernelGGL(dv_reduce_kernel<T>, dim3((unsigned)((nbox + 255) / 256)), dim3(256), 0, st,
+                       nbox, nb, (const C2<T> *)box2, gamma / (double)nbox, dV);
+    CHEBFI_HIP(hipGetLastError());
+  }
+  // Ak = gamma (local + (kin - c) Ak1) - delta Ak2 + E
+  launch_c<T>(s, box1, band0, nb, Ak1, lda1, Ak2, lda2, Ak, ldak, gamma, cshift, delta, E, lde,
+              nullptr, PlanesOut{nullptr, 0, 0}, st);
 }
 
 template <typename T>
-void launch_density(const abi_system_s *s, const void *Psi, int64_t ld, int band0, int nb,
-                    void *box, const double *w, double *rho, hipStream_t st) {
-  launch_a<T>(s, Psi, ld, band0, nb, box, st);
-  launch_z<T, Z_INVERSE>(s, box, nullptr, nullptr, nb, st);
+void launch_density(const abi_system_s *s, const void *Psi, int64_t ld, int band0, int nb, void *box,
+                    const double *w, double *rho, hipStream_t st) {
   const int64_t nbox = (int64_t)s->n1 * s->n2 * s->n3;
+  launch_a<T>(s, Psi, ld, band0, nb, box, st);
+  if (special_z(s)) {
+    launch_zaccum<T, false>(s, nullptr, box, nullptr, w ? w + band0 : nullptr, nb,
+                            1.0 / (double)nbox, rho, st);
+    return;
+  }
+  const RuntimeShape<T> r(s->plan);
+  set_lds(pass_b_inv_kernel<T>, r.ldsB);
+  hipLaunchKernelGGL(pass_b_inv_kernel<T>, dim3(s->n2, nb), dim3(r.tB), r.ldsB, st, (C2<T> *)box,
+                     s->plan, reinterpret_cast<const double2 *>(s->d_tw));
   hipLaunchKernelGGL(rho_accum_kernel<T>, dim3((unsigned)((nbox + 255) / 256)), dim3(256), 0, st,
                      nbox, nb, band0, (const C2<T> *)box, w, 1.0 / (double)nbox, rho);
   CHEBFI_HIP(hipGetLastError());
@@ -555,13 +718,13 @@ template void launch_density<float>(const abi_system_s *, const void *, int64_t,
                                     const double *, double *, hipStream_t);
 
 template void launch_adjoint_local<double>(const abi_system_s *, const void *, int64_t, const void *,
-                                           int64_t, void *, int64_t, bool, int, int, void *,
-                                           void *, const void *, double, double, double *,
-                                           hipStream_t);
+                                           int64_t, const void *, int64_t, double, void *, int64_t,
+                                           int, int, void *, void *, const void *, double, double,
+                                           const void *, int64_t, double *, hipStream_t);
 template void launch_adjoint_local<float>(const abi_system_s *, const void *, int64_t, const void *,
-                                           int64_t, void *, int64_t, bool, int, int, void *,
-                                           void *, const void *, double, double, double *,
-                                           hipStream_t);
+                                          int64_t, const void *, int64_t, double, void *, int64_t,
+                                          int, int, void *, void *, const void *, double, double,
+                                          const void *, int64_t, double *, hipStream_t);
 
 template void launch_local_potential<double>(const abi_system_s *, const void *, int64_t,
                                              const void *, int64_t, void *, int64_t, int, int,

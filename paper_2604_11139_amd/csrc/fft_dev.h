@@ -395,6 +395,48 @@ __device__ __forceinline__ void cfft(C2<T> *buf, const C2<T> *tw) {
 // and the last one write straight to it (or fuse a pointwise product into its
 // store), saving a pass of the plane through LDS.  SYNC_MID: a barrier
 // between the reads and the writes (needed when both are the same LDS plane).
+// Position of a thread's c-th butterfly of such a stage: pencil, and the element of
+// its output 0 (output t is P elements further on per t); false past the last one.
+template <int N, int R, int P, int NPEN, int CT>
+__device__ __forceinline__ bool cstage_at(int c, int &pa, int &e0) {
+  const int i = threadIdx.x + c * CT, bf = i / NPEN, k = bf % P;
+  pa = i % NPEN;
+  e0 = (bf - k) * R + k;
+  return NPEN * (N / R) % CT == 0 || i < NPEN * (N / R);
+}
+template <int N, int R, int NPEN, int CT>
+constexpr int cstage_rounds() {
+  return (NPEN * (N / R) + CT - 1) / CT;
+}
+
+// The stage's outputs in registers, y[c][t] = output t of the c-th butterfly.
+template <typename T, int N, int R, int P, int NPEN, int SGN, int CT, class Ld>
+__device__ __forceinline__ void cstage_vals(const C2<T> *tw, Ld ld,
+                                            C2<T> (&y)[cstage_rounds<N, R, NPEN, CT>()][R]) {
+  constexpr int NBF = N / R, TOTAL = NPEN * NBF, M = N / (P * R);
+#pragma unroll
+  for (int c = 0; c < cstage_rounds<N, R, NPEN, CT>(); ++c) {
+    const int i = threadIdx.x + c * CT;
+    if (TOTAL % CT == 0 || i < TOTAL) {
+      const int pa = i % NPEN, bf = i / NPEN, k = bf % P;
+      C2<T> x[R];
+#pragma unroll
+      for (int t = 0; t < R; ++t) x[t] = ld(pa, bf + t * NBF);
+      if (P > 1) {
+#pragma unroll
+        for (int t = 1; t < R; ++t) {
+          C2<T> w = tw[t * k * M];
+          if (SGN > 0) w.y = -w.y;
+          x[t] = cmul(x[t], w);
+        }
+      }
+      Dft<T, R>::run(x, SGN);
+#pragma unroll
+      for (int t = 0; t < R; ++t) y[c][t] = x[t];
+    }
+  }
+}
+
 // With `pre`, st also gets pre(pencil, element), fetched before the stage reads.
 struct NoPre {};
 template <class Pre> struct PreValue {
@@ -560,64 +602,44 @@ struct ZOcc {
 // bytes and 216 of 512 threads busy at 36), and an LDS row is one bank sweep.
 template <typename T> constexpr int zpencils() { return 512 / (int)sizeof(C2<T>); }
 
-// Work of a z pass: the filter's pass B (inverse z transform, times V, forward
-// transform), the inverse transform alone (density, adjoint's forward bands), or
-// the adjoint's pass B (also Re[conj(adjoint) * forward] over the forward band).
-enum { Z_FILTER = 0, Z_INVERSE = 1, Z_ADJOINT = 2 };
+// Loads of a z transform's first stage from the box.  Reciprocal planes g3 without
+// sphere points are zero (pass A leaves them unwritten).  Every load is issued: a
+// pencil past the end reads the last one, an empty plane's element plane 0's, which
+// the workgroup reads anyway; a branch around each load kept them from overlapping,
+// 48 against 40 us per 64 64^3 complex64 boxes.
+template <int N> __device__ __forceinline__ bool z_occupied(const ZOcc &z, int e) {
+  return (((N > 64 && e >= 64 ? z.hi : z.lo) >> (e & 63)) & 1) != 0;
+}
+template <typename T, int N>
+__device__ __forceinline__ C2<T> z_load(const C2<T> *src, const ZOcc &z, int left, int nxy, int pa,
+                                        int e) {
+  const bool in = z_occupied<N>(z, e);
+  const C2<T> x = src[min(pa, left - 1) + (in ? e * nxy : 0)];
+  return in ? x : C2<T>{0, 0};
+}
 
-// z pass of the pencils [0, left) (at most zpencils) of a box whose planes hold nxy
-// elements: src, fw and v point at the first pencil's plane-0 element; tw3: the
-// transform's twiddles.
-template <typename T, int N, int MODE>
-__device__ __forceinline__ void z_pencils(C2<T> *__restrict__ src, C2<T> *__restrict__ fw,
-                                          const T *__restrict__ v, int left, int nxy,
-                                          const double2 *__restrict__ twg, ZOcc zocc, C2<T> *buf,
-                                          C2<T> *tw) {
+// Pass B of the pencils [0, left) (at most zpencils) of a box whose planes hold nxy
+// elements: inverse z transform, times V, forward transform; src and v point at the
+// first pencil's plane-0 element, twg at the transform's twiddles.
+template <typename T, int N>
+__device__ __forceinline__ void z_pencils(C2<T> *__restrict__ src, const T *__restrict__ v,
+                                          int left, int nxy, const double2 *__restrict__ twg,
+                                          ZOcc zocc, C2<T> *buf, C2<T> *tw) {
   constexpr int Q = zpencils<T>(), CT = cthreads<N, Q>();
   for (int i = threadIdx.x; i < N; i += CT) tw[i] = to_c2<T>(twg[i]);
   __syncthreads();
   auto ldm = [&](int pa, int e) { return buf[pa + e * Q]; };
   auto stm = [&](int pa, int e, C2<T> x) { buf[pa + e * Q] = x; };
-  // reciprocal planes g3 without sphere points: zero in (pass A leaves them
-  // unwritten), not written out (pass C does not read them)
-  auto occ = [&](int e) { return (((N > 64 && e >= 64 ? zocc.hi : zocc.lo) >> (e & 63)) & 1) != 0; };
-  // (every load is issued: a pencil past the end reads the last one, an empty
-  // plane's element plane 0's, which the workgroup reads anyway; a branch around
-  // each load kept them from overlapping, 48 against 40 us per 64 64^3 complex64
-  // boxes)
-  auto ldg = [&](int pa, int e) {
-    const bool in = occ(e);
-    const C2<T> x = src[min(pa, left - 1) + (in ? e * nxy : 0)];
-    return in ? x : C2<T>{0, 0};
+  auto ldg = [&](int pa, int e) { return z_load<T, N>(src, zocc, left, nxy, pa, e); };
+  // V fetched ahead of the stage that multiplies by it
+  auto pre = [&](int pa, int e) { return v[min(pa, left - 1) + e * nxy]; };
+  auto stv = [&](int pa, int e, C2<T> x, T p) { buf[pa + e * Q] = cscale(x, p); };
+  // (pass C does not read planes without sphere points)
+  auto stg = [&](int pa, int e, C2<T> x) {
+    if (pa < left && z_occupied<N>(zocc, e)) src[pa + e * nxy] = x;
   };
-  if constexpr (MODE == Z_INVERSE) {  // real space out: all planes
-    auto stg = [&](int pa, int e, C2<T> x) {
-      if (pa < left) src[pa + e * nxy] = x;
-    };
-    cfft_io<T, N, 0, 1, Q, +1, false, false, CT>(tw, ldg, stg, ldm, stm);
-  } else {
-    // V (and the forward band) fetched ahead of the stage that multiplies by it
-    struct Pre {
-      T v;
-      C2<T> y;
-    };
-    auto pre = [&](int pa, int e) {
-      const int r = min(pa, left - 1) + e * nxy;
-      Pre p{v[r], C2<T>{0, 0}};
-      if constexpr (MODE == Z_ADJOINT) p.y = fw[r];
-      return p;
-    };
-    auto stv = [&](int pa, int e, C2<T> x, const Pre &p) {
-      if constexpr (MODE == Z_ADJOINT)
-        if (pa < left) fw[pa + e * nxy] = C2<T>{x.x * p.y.x + x.y * p.y.y, (T)0};
-      buf[pa + e * Q] = cscale(x, p.v);
-    };
-    auto stg = [&](int pa, int e, C2<T> x) {
-      if (pa < left && occ(e)) src[pa + e * nxy] = x;
-    };
-    cfft_io<T, N, 0, 1, Q, +1, false, true, CT>(tw, ldg, stv, ldm, stm, pre);
-    cfft_io<T, N, 0, 1, Q, -1, true, false, CT>(tw, ldm, stg, ldm, stm);
-  }
+  cfft_io<T, N, 0, 1, Q, +1, false, true, CT>(tw, ldg, stv, ldm, stm, pre);
+  cfft_io<T, N, 0, 1, Q, -1, true, false, CT>(tw, ldm, stg, ldm, stm);
 }
 
 // Edges with compile-time transforms.

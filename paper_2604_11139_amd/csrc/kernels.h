@@ -32,13 +32,14 @@ void launch_local_potential(const abi_system_s *s, const void *Yk, int64_t ldk, 
 
 // Local part of one reverse step of the filter adjoint for bands
 // [band0, band0+nb): dV += gamma/n^3 sum_b Re[conj(Ak1~) Yk~] and
-// Ak = gamma (V_loc Ak1 + (kin - cshift) Ak1) (+ Ak when accumulate).
-// box1/box2 hold nb boxes each.  Runtime-size passes (any grid).
+// Ak = gamma (V_loc Ak1 + (kin - cshift) Ak1) - delta Ak2 (Ak2 may be null) + E (the
+// projector part, may be null).  box1/box2 hold nb boxes each.
 template <typename T>
 void launch_adjoint_local(const abi_system_s *s, const void *Ak1, int64_t lda1, const void *Yk,
-                          int64_t ldy, void *Ak, int64_t ldak, bool accumulate, int band0, int nb,
-                          void *box1, void *box2, const void *V, double gamma, double cshift,
-                          double *dV, hipStream_t st);
+                          int64_t ldy, const void *Ak2, int64_t lda2, double delta, void *Ak,
+                          int64_t ldak, int band0, int nb, void *box1, void *box2, const void *V,
+                          double gamma, double cshift, const void *E, int64_t lde, double *dV,
+                          hipStream_t st);
 
 // rho += sum_b w[band0+b] |psi~_b(r)|^2 / (n1 n2 n3) for bands [band0, band0+nb)
 // (w may be null: unit weights).  box holds nb boxes.
@@ -209,9 +210,6 @@ void launch_tridiag_bound(int k, const double *alpha, const double *beta, int ad
 // complex double or, with fp32, complex float; dD is complex double)
 void launch_dd_accum(int natom, int64_t nband, const void *CA, const void *CY, double gamma,
                      void *dD, hipStream_t st, bool fp32 = false);
-// out = -delta * in  (complex double or, with fp32, complex float blocks)
-void launch_scale_neg(int64_t npw, int64_t nband, const void *in, int64_t ldi, double delta,
-                      void *out, int64_t ldo, hipStream_t st, bool fp32 = false);
 // out (m x n, contiguous) = sum over the `splits` partial products of a split-K GEMM
 void launch_sum_parts(int64_t m, int64_t n, const void *part, int splits, void *out,
                       hipStream_t st, bool fp32);

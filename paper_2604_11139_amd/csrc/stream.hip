@@ -469,18 +469,6 @@ __global__ __launch_bounds__(256) void dd_accum_kernel(int natom, int64_t nband,
   }
 }
 
-template <typename T>
-__global__ void scale_neg_kernel(int64_t npw, int64_t nband, const C2<T> *__restrict__ in,
-                                 int64_t ldi, double delta, C2<T> *__restrict__ out,
-                                 int64_t ldo) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= npw * nband) return;
-  const int64_t i = idx % npw, b = idx / npw;
-  const C2<T> v = in[i + b * ldi];
-  const T d = (T)delta;
-  out[i + b * ldo] = C2<T>{-d * v.x, -d * v.y};
-}
-
 // out[i + j m] = sum_z part[z][i + j m] (summed in FP64, in z order).
 template <typename T>
 __global__ void sum_parts_kernel(int64_t mn, int splits, const C2<T> *__restrict__ part,
@@ -655,17 +643,6 @@ void launch_dd_accum(int natom, int64_t nband, const void *CA, const void *CY, d
   else
     hipLaunchKernelGGL(dd_accum_kernel<double>, dim3((unsigned)natom), dim3(256), 0, st, natom,
                        nband, (const double2 *)CA, (const double2 *)CY, gamma, (double2 *)dD);
-  CHEBFI_HIP(hipGetLastError());
-}
-
-void launch_scale_neg(int64_t npw, int64_t nband, const void *in, int64_t ldi, double delta,
-                      void *out, int64_t ldo, hipStream_t st, bool fp32) {
-  if (fp32)
-    hipLaunchKernelGGL(scale_neg_kernel<float>, dim3(nblk(npw * nband, 256)), dim3(256), 0, st,
-                       npw, nband, (const float2 *)in, ldi, delta, (float2 *)out, ldo);
-  else
-    hipLaunchKernelGGL(scale_neg_kernel<double>, dim3(nblk(npw * nband, 256)), dim3(256), 0, st,
-                       npw, nband, (const double2 *)in, ldi, delta, (double2 *)out, ldo);
   CHEBFI_HIP(hipGetLastError());
 }
 
