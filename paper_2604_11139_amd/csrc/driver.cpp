@@ -462,7 +462,7 @@ void setup_overlap(abi_system_s *s, const double *qij, hipStream_t st) {
     // W = R^-1 Z, K = W diag(mu / (1 + mu)) W^H
     DevBuf tw;
     ztrtri_upper(n, R, n, tw.get(ztrtri_work_bytes(n)), st);
-    zgemm(OP_N, OP_N, n, n, n, R, n, Z, n, T, n, double2{1, 0}, double2{0, 0}, st);
+    zgemm_tri(TRI_UB, n, n, R, n, Z, n, T, n, st);
     launch_woodbury_scale(n, T, n, mu, A, n, st);
     zgemm(OP_N, OP_C, n, n, n, A, n, T, n, s->d_K, n, double2{1, 0}, double2{0, 0}, st);
     launch_hermitize(n, s->d_K, n, st);
@@ -545,9 +545,9 @@ int rr_lowprec(abi_system_s *s, void *Y, int64_t ld, void *HPsi, int64_t ldh_in,
     split_planes(M, M, C32, M, tpl, ldm, st);
     ytpl = s->rr_planes.get(8 * (size_t)npw * ldm);
   };
-  auto rotate = [&](const float2 *A, void *Out, int64_t ldo) {
+  auto rotate = [&](const float2 *A, void *Out, int64_t ldo, bool upper = false) {
     split_planes_t(npw, M, A, npw, ytpl, ldm, st);
-    rr_rotate_planes(npw, M, ytpl, ldm, tpl, ldm, Out, ldo, st);
+    rr_rotate_planes(npw, M, ytpl, ldm, tpl, ldm, Out, ldo, upper, st);
   };
   // equilibrated block Ye = Y E (E = diag of inverse column norms)
   launch_col_norms(npw, M, Y, ld, nrm, inv, st, true);
@@ -563,7 +563,7 @@ int rr_lowprec(abi_system_s *s, void *Y, int64_t ld, void *HPsi, int64_t ldh_in,
     ztrtri_upper(M, G, M, trw, st);
     launch_copy_block(M, M, G, M, U1i, M, st);
     split_coef(U1i);
-    rotate(Ye, spare, npw);
+    rotate(Ye, spare, npw, true);
     s->prof.end(tok, st);
     std::swap(Ye, spare);
     if (gram_chol(Ye) == 0.0) return 0;
@@ -578,8 +578,8 @@ int rr_lowprec(abi_system_s *s, void *Y, int64_t ld, void *HPsi, int64_t ldh_in,
   s->prof.end(tok, st);
   tok = s->prof.begin(PROF_CHOL, 16.0 * (double)M * M * M, st);
   ztrtri_upper(M, G, M, trw, st);
-  zgemm(OP_N, OP_N, M, M, M, Hs, M, G, M, T, M, double2{1, 0}, double2{0, 0}, st);
-  zgemm(OP_C, OP_N, M, M, M, G, M, T, M, Hs, M, double2{1, 0}, double2{0, 0}, st);
+  zgemm_tri(TRI_AU, M, M, Hs, M, G, M, T, M, st);
+  zgemm_tri(TRI_UHB, M, M, G, M, T, M, Hs, M, st);
   s->prof.end(tok, st);
   void *ew = s->eig1.get(zheev_work_bytes(M));
   tok = s->prof.begin(PROF_EIG, 16.0 / 3.0 * (double)M * M * M, st);
@@ -587,7 +587,7 @@ int rr_lowprec(abi_system_s *s, void *Y, int64_t ld, void *HPsi, int64_t ldh_in,
   s->prof.end(tok, st);
   // T = U^-1 Z; Psi = Ye T and H Psi = (H Ye) T as split-BF16 products
   tok = s->prof.begin(PROF_ROT, 8.0 * (double)M * M * M + 16.0 * (double)npw * M * M, st);
-  zgemm(OP_N, OP_N, M, M, M, G, M, Z, M, T, M, double2{1, 0}, double2{0, 0}, st);
+  zgemm_tri(TRI_UB, M, M, G, M, Z, M, T, M, st);
   split_coef(T);
   rotate(Ye, Y, ld);
   void *HP;
@@ -605,7 +605,7 @@ int rr_lowprec(abi_system_s *s, void *Y, int64_t ld, void *HPsi, int64_t ldh_in,
     // Psi = Y_in E [U1^-1] T
     const double2 *C = T;
     if (U1i) {
-      zgemm(OP_N, OP_N, M, M, M, U1i, M, T, M, Z, M, double2{1, 0}, double2{0, 0}, st);
+      zgemm_tri(TRI_UB, M, M, U1i, M, T, M, Z, M, st);
       C = Z;
     }
     launch_copy_block(M, M, C, M, coef, M, st);
@@ -675,8 +675,8 @@ void rr_core(abi_system_s *s, double2 *Y, int64_t ld, double2 *HPsi, int64_t ldh
   tok = s->prof.begin(PROF_CHOL, 16.0 * (double)M * M * M, st);
   void *trw = s->eig2.get(ztrtri_work_bytes(M));
   ztrtri_upper(M, G, M, trw, st);
-  zgemm(OP_N, OP_N, M, M, M, Hs, M, G, M, T, M, double2{1, 0}, double2{0, 0}, st);
-  zgemm(OP_C, OP_N, M, M, M, G, M, T, M, Hs, M, double2{1, 0}, double2{0, 0}, st);
+  zgemm_tri(TRI_AU, M, M, Hs, M, G, M, T, M, st);
+  zgemm_tri(TRI_UHB, M, M, G, M, T, M, Hs, M, st);
   s->prof.end(tok, st);
   // eigen-decomposition (Hs overwritten), W = U^-1 Z
   void *ew = s->eig1.get(zheev_work_bytes(M));
@@ -684,7 +684,7 @@ void rr_core(abi_system_s *s, double2 *Y, int64_t ld, double2 *HPsi, int64_t ldh
   const int *flag = zheev(M, Hs, M, w_dev, Z, M, ew, st);
   s->prof.end(tok, st);
   tok = s->prof.begin(PROF_ROT, 8.0 * (double)M * M * M + 16.0 * (double)npw * M * M, st);
-  zgemm(OP_N, OP_N, M, M, M, G, M, Z, M, T, M, double2{1, 0}, double2{0, 0}, st);
+  zgemm_tri(TRI_UB, M, M, G, M, Z, M, T, M, st);
   // Psi = Y W, H Psi = (H Y) W
   double2 *Psi = (double2 *)s->blk2.get(sizeof(double2) * (size_t)npw * M);
   zgemm(OP_N, OP_N, npw, M, M, Y, ld, T, M, Psi, npw, double2{1, 0}, double2{0, 0}, st);

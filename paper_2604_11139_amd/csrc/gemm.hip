@@ -83,6 +83,11 @@ __device__ __forceinline__ void grouped_tile(unsigned gm, unsigned &tm, unsigned
 // tiles on and above the diagonal (the split-K sum mirrors the rest).  MODE 2: the
 // tiles on the diagonal alone, part[z][tile] 64 x 64 each.  Unsplit, blockIdx.z
 // counts products of a batch, sa / sb / sc apart.
+// MODE 3, 4, 5: products with an upper triangular factor, C = A U, U^H B, U B: a tile's
+// K range leaves out the part of U that is zero by tiles.  The longest tiles start
+// first, and the dimension that does not set the length varies fastest, so that each
+// XCD (every eighth workgroup) gets tiles of every length.  2048^3: 655 us against
+// 1240.
 // Three workgroups per CU (168 registers; the epilogue's operands had cost the
 // unsplit form the third): with two, a SIMD's matrix core idles whenever both its
 // waves are between barriers.  At 115313 x 2048 x 864 the expansion went from 28.3
@@ -118,6 +123,14 @@ __global__ __launch_bounds__(256, 3) void zgemm_kernel(int64_t m, int64_t n, int
     col0 = (int64_t)tn * BN;
   }
   static_assert(MODE == 0 || BM == BN, "square tiles");
+  if constexpr (MODE == 3) {
+    row0 = (int64_t)blockIdx.x * BM;
+    col0 = (int64_t)(gridDim.y - 1 - blockIdx.y) * BN;
+  }
+  if constexpr (MODE == 4 || MODE == 5) {  // grid: columns, rows
+    row0 = (int64_t)(MODE == 4 ? gridDim.y - 1 - blockIdx.y : blockIdx.y) * BM;
+    col0 = (int64_t)blockIdx.x * BN;
+  }
   if constexpr (MODE == 2) row0 = col0 = (int64_t)blockIdx.x * BM;
   if constexpr (MODE == 1) {
     int64_t ti, tj;
@@ -130,8 +143,10 @@ __global__ __launch_bounds__(256, 3) void zgemm_kernel(int64_t m, int64_t n, int
     B += (int64_t)tz * sb;
     C += (int64_t)tz * sc;
   }
-  const int64_t kbeg = SPLIT ? (int64_t)tz * kchunk : 0;
-  const int64_t kend = (kbeg + kchunk < k) ? kbeg + kchunk : k;
+  const int64_t kbeg = SPLIT ? (int64_t)tz * kchunk : MODE == 5 ? row0 : 0;
+  int64_t kend = (kbeg + kchunk < k) ? kbeg + kchunk : k;
+  if constexpr (MODE == 3) kend = min(k, col0 + BN);
+  if constexpr (MODE == 4) kend = min(k, row0 + BM);
 
   Acc acc_re[2][2], acc_im[2][2];
 #pragma unroll
@@ -569,6 +584,31 @@ void zgemm_herm_update(int64_t m, int64_t k, const void *A, int64_t lda, void *C
                      double2{-1, 0}, double2{1, 0}, k, (double2 *)nullptr, (int64_t)0, (int64_t)0,
                      (int64_t)0);
   CHEBFI_HIP(hipGetLastError());
+}
+
+void zgemm_tri(TriProduct kind, int64_t m, int64_t n, const void *A, int64_t lda, const void *B,
+               int64_t ldb, void *C, int64_t ldc, hipStream_t st) {
+  if (m <= 0 || n <= 0) return;
+  const int64_t k = kind == TRI_AU ? n : m;
+  const unsigned tm = (unsigned)((m + BM - 1) / BM), tn = (unsigned)((n + BN - 1) / BN);
+  // few tiles: the small-tile form is as fast with the zeros (35 us at 512^3)
+  if (small_output((int64_t)tm * tn)) {
+    zgemm(kind == TRI_UHB ? OP_C : OP_N, OP_N, m, n, k, A, lda, B, ldb, C, ldc, double2{1, 0},
+          double2{0, 0}, st);
+    return;
+  }
+  auto go = [&](auto kern, dim3 grid) {
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, m, n, k, (const double2 *)A, lda,
+                       (const double2 *)B, ldb, (double2 *)C, ldc, double2{1, 0}, double2{0, 0}, k,
+                       (double2 *)nullptr, (int64_t)0, (int64_t)0, (int64_t)0);
+    CHEBFI_HIP(hipGetLastError());
+  };
+  if (kind == TRI_AU)
+    go(zgemm_kernel<double, OP_N, OP_N, false, 0, 3>, dim3(tm, tn));
+  else if (kind == TRI_UHB)
+    go(zgemm_kernel<double, OP_C, OP_N, false, 0, 4>, dim3(tn, tm));
+  else
+    go(zgemm_kernel<double, OP_N, OP_N, false, 0, 5>, dim3(tn, tm));
 }
 
 void zgemm_diag_tiles(int64_t n, int64_t k, const void *A, int64_t lda, void *part, int splits,
@@ -1346,7 +1386,10 @@ __device__ __forceinline__ v8bf cat4(bf2_t a, bf2_t b, bf2_t c, bf2_t d) {
 // ROLE names the instantiation: 0 for the filter's projector products, 1 for the
 // Rayleigh-Ritz rotations (same code, told apart in kernel traces), 2 for its
 // Hermitian products: a 1-D grid of the tiles on and above the diagonal (136 of
-// 256 at 2048 bands; 10.2 -> about 5.8 ms a product at 115313 plane waves).
+// 256 at 2048 bands; 10.2 -> about 5.8 ms a product at 115313 plane waves), 3 for
+// B upper triangular: a tile's K range ends with its columns (one tile per workgroup:
+// in the persistent form a workgroup keeps its columns in every round, so the longest
+// would set the time).  8.6 -> 5.2 ms for 115313 x 2048 x 2048.
 template <int BM, int BN, int NWM, int NWN, bool CONJ, bool SPLIT, bool BF32, bool PIPE = false,
           bool PERSIST = false, int ROLE = 0>
 __global__ __launch_bounds__(64 * NWM * NWN) void zgemm_dl_kernel(
@@ -1423,6 +1466,7 @@ __global__ __launch_bounds__(64 * NWM * NWN) void zgemm_dl_kernel(
     tzv = tz;
     kbeg = (int64_t)tz * kchunk;
     kend = (kbeg + kchunk < kpad) ? kbeg + kchunk : kpad;
+    if constexpr (ROLE == 3) kend = min(kend, col0 + BN);
   }
   const int ns = kend > kbeg ? (int)((kend - kbeg) >> 5) : 0;
 
@@ -2291,7 +2335,7 @@ void rr_gram_f32(int64_t m, int64_t npw, const void *Apl, int64_t lda, const voi
 }
 
 void rr_rotate_planes(int64_t npw, int64_t m, const void *Apl, int64_t lda, const void *Tpl,
-                      int64_t ldt, void *Out, int64_t ldo, hipStream_t st) {
+                      int64_t ldt, void *Out, int64_t ldo, bool upper, hipStream_t st) {
   const int64_t tiles = ((npw + 127) / 128) * ((m + 127) / 128);
   const int64_t per_xcd =
       std::max<int64_t>(1, std::min<int64_t>(device_cus() / 8, (tiles + 7) / 8));
@@ -2300,6 +2344,14 @@ void rr_rotate_planes(int64_t npw, int64_t m, const void *Apl, int64_t lda, cons
                  "split-BF16 planes must be zero-padded to a multiple of 32");
   CHEBFI_REQUIRE(128 * lda < (1ll << 31) && 128 * ldt < (1ll << 31), ABI_ERR_ARG,
                  "split-BF16 tile spans more than 2^31 elements");
+  if (upper) {
+    hipLaunchKernelGGL((zgemm_dl_kernel<128, 128, 2, 4, false, false, false, true, false, 3>),
+                       dim3((unsigned)((npw + 127) / 128), (unsigned)((m + 127) / 128)), dim3(512),
+                       0, st, npw, m, m, (const u16 *)Apl, lda, npw * lda, (const void *)Tpl, ldt,
+                       ldt * m, (float2 *)Out, ldo, kpad, kpad, (float2 *)nullptr, 0);
+    CHEBFI_HIP(hipGetLastError());
+    return;
+  }
   hipLaunchKernelGGL((zgemm_dl_kernel<128, 128, 2, 4, false, false, false, true, true, 1>),
                      dim3((unsigned)(8 * per_xcd)), dim3(512), 0, st, npw, m, m, (const u16 *)Apl,
                      lda, npw * lda, (const void *)Tpl, ldt, ldt * m, (float2 *)Out, ldo, kpad,

@@ -110,12 +110,12 @@ void expand_gemm_planes(int64_t npw, int64_t nband, int64_t nproj, const void *A
 // (part: splits x m x m complex float), the rest mirrored (the planes of Y_pl
 // zero-padded to a multiple of 32, ld lda, Y complex64 with ld ldy), and
 // Out = A T from the transposed planes of A (npw x m, ld lda) and the planes of
-// T (m x m, ld ldt), both zero-padded along m.
+// T (m x m, ld ldt; `upper`: zero below the diagonal), both zero-padded along m.
 int rr_gram_splits(int64_t m, int64_t npw);
 void rr_gram_f32(int64_t m, int64_t npw, const void *Apl, int64_t lda, const void *Y,
                  int64_t ldy, void *part, int splits, void *G, hipStream_t st);
 void rr_rotate_planes(int64_t npw, int64_t m, const void *Apl, int64_t lda, const void *Tpl,
-                      int64_t ldt, void *Out, int64_t ldo, hipStream_t st);
+                      int64_t ldt, void *Out, int64_t ldo, bool upper, hipStream_t st);
 // Single-band forms: c = P^H x, out += P c.
 void proj_gemv(int64_t npw, int nproj, const void *P, const void *x, void *c, hipStream_t st);
 void expand_gemv(int64_t npw, int nproj, const void *P, const void *c, void *out, hipStream_t st);
@@ -134,6 +134,12 @@ void zgemm_herm(int64_t m, int64_t k, const void *A, int64_t lda, const void *B,
 // C -= A^H A (C m x m, A k x m): the 64 x 64 tiles on and above the diagonal.
 void zgemm_herm_update(int64_t m, int64_t k, const void *A, int64_t lda, void *C, int64_t ldc,
                        hipStream_t st);
+// Products with an upper triangular factor U whose lower triangle is stored as zeros:
+// C = A U (A m x n, U n x n), C = U^H B or C = U B (U m x m, B m x n).  Equal to zgemm
+// bit for bit on finite operands.
+enum TriProduct { TRI_AU, TRI_UHB, TRI_UB };
+void zgemm_tri(TriProduct kind, int64_t m, int64_t n, const void *A, int64_t lda, const void *B,
+               int64_t ldb, void *C, int64_t ldc, hipStream_t st);
 // The 64 x 64 tiles on the diagonal of A^H A (A k x n), one after the other in
 // part[z] for each of `splits` chunks of k.
 void zgemm_diag_tiles(int64_t n, int64_t k, const void *A, int64_t lda, void *part, int splits,

@@ -46,13 +46,13 @@ bool ortho_rr_basis(abi_system_s *s, int64_t k, int64_t mout, const double2 *Z,
   s->prof.end(tok, st);
   tok = s->prof.begin(PROF_CHOL, 16.0 * (double)k * k * k, st);
   ztrtri_upper(k, G, k, s->eig2.get(ztrtri_work_bytes(k)), st);
-  zgemm(OP_N, OP_N, k, k, k, Hs, k, G, k, T, k, double2{1, 0}, double2{0, 0}, st);
-  zgemm(OP_C, OP_N, k, k, k, G, k, T, k, Hs, k, double2{1, 0}, double2{0, 0}, st);
+  zgemm_tri(TRI_AU, k, k, Hs, k, G, k, T, k, st);
+  zgemm_tri(TRI_UHB, k, k, G, k, T, k, Hs, k, st);
   s->prof.end(tok, st);
   tok = s->prof.begin(PROF_EIG, 16.0 / 3.0 * (double)k * k * k, st);
   const int *flag = zheev(k, Hs, k, w_dev, Y, k, s->eig1.get(zheev_work_bytes(k)), st);
   s->prof.end(tok, st);
-  zgemm(OP_N, OP_N, k, mout, k, G, k, Y, k, C, k, double2{1, 0}, double2{0, 0}, st);
+  zgemm_tri(TRI_UB, k, mout, G, k, Y, k, C, k, st);
   CHEBFI_HIP(hipStreamSynchronize(st));
   zheev_check(flag);
   return true;
