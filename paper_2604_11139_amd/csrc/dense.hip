@@ -26,6 +26,7 @@
 //   Golub & Van Loan, "Matrix Computations", chapter 8).
 #include <cfloat>
 #include <string>
+#include <type_traits>
 
 #include "cplx.h"
 #include "kernels.h"
@@ -984,7 +985,10 @@ __device__ __forceinline__ double lane_val(double v, int k) {
 // each followed by scaling to max 1 and normalisation; sign of the largest
 // component positive).  The factors and the iterate live in `work`, interleaved
 // by lane (element i of lane l at i * 64 + l within the wave's slab), so that
-// each sequential step of the 64 lanes is one coalesced access.
+// each sequential step of the 64 lanes is one coalesced access.  Bound by the
+// latency of its m / 64 waves' loads, hence every pass in blocks of kB loads and no
+// pass that only rescales: 2463 us at 2048 (2953 with two rescaling passes per solve and
+// the factorisation, the start and the last passes element by element), 459 at 512 (608).
 __global__ __launch_bounds__(64) void invit_lane_kernel(
     int64_t m, const double *__restrict__ d, const double *__restrict__ e,
     const double *__restrict__ w, const double *__restrict__ stats, double *__restrict__ S,
@@ -1005,110 +1009,137 @@ __global__ __launch_bounds__(64) void invit_lane_kernel(
   unsigned char *swp = wswp + b * slab + lane;
   const double tiny = DBL_EPSILON * scale;
   const double shift = w[q];
+  // Steps whose operands are loaded into registers before they run: one memory
+  // latency per block instead of per step.
+  constexpr int kB = 32;
+  // f(i0, count) over the blocks of [0, n): whole blocks with a compile-time count
+  auto blocks = [&](int64_t n, auto f) {
+    int64_t i0 = 0;
+    for (; i0 + kB <= n; i0 += kB) f(i0, std::integral_constant<int, kB>{});
+    for (; i0 < n; ++i0) f(i0, std::integral_constant<int, 1>{});
+  };
   // LU with partial pivoting of T - shift I
   double a = d[0] - shift;
   double cc = (m > 1) ? e[0] : 0.0;
-  for (int64_t i = 0; i < m - 1; ++i) {
-    const double bb = e[i], an = d[i + 1] - shift, cn = (i + 1 < m - 1) ? e[i + 1] : 0.0;
-    const bool keep = fabs(a) >= fabs(bb);
-    const double num = keep ? bb : a, den = keep ? a : bb;
-    const double l = (den != 0.0) ? num / den : 0.0;
-    double piv = den;
-    if (fabs(piv) < tiny) piv = (piv < 0.0) ? -tiny : tiny;
-    rud[i * 64] = 1.0 / piv;
-    u1[i * 64] = keep ? cc : an;
-    u2[i * 64] = keep ? 0.0 : cn;
-    lm[i * 64] = l;
-    swp[i * 64] = keep ? 0 : 1;
-    const double na = keep ? an - l * cc : cc - l * an;
-    cc = keep ? cn : -l * cn;
-    a = na;
-  }
-  rud[(m - 1) * 64] = 1.0 / ((fabs(a) < tiny) ? ((a < 0.0) ? -tiny : tiny) : a);
-  for (int64_t i = 0; i < m; ++i) x[i * 64] = hash_uniform(q, i);
-  // the solves load the operands of kB steps into registers before running them
-  // (one memory latency per block instead of per step)
-  constexpr int kB = 32;
-  for (int it = 0; it < 3; ++it) {
-    double cur = x[0];
-    int64_t i0 = 0;
-    for (; i0 + kB <= m - 1; i0 += kB) {
-      double nx[kB], l[kB];
-      unsigned char sw[kB];
+  blocks(m - 1, [&](int64_t i0, auto cnt) {
+    constexpr int n = decltype(cnt)::value;
+    double eb[n + 1], db[n];
 #pragma unroll
-      for (int k = 0; k < kB; ++k) {
-        nx[k] = x[(i0 + k + 1) * 64];
+    for (int k = 0; k < n; ++k) {
+      eb[k] = e[i0 + k];
+      db[k] = d[i0 + k + 1];
+    }
+    eb[n] = (i0 + n < m - 1) ? e[i0 + n] : 0.0;
+#pragma unroll
+    for (int k = 0; k < n; ++k) {
+      const int64_t i = i0 + k;
+      const double bb = eb[k], an = db[k] - shift, cn = eb[k + 1];
+      const bool keep = fabs(a) >= fabs(bb);
+      const double num = keep ? bb : a, den = keep ? a : bb;
+      const double l = (den != 0.0) ? num / den : 0.0;
+      double piv = den;
+      if (fabs(piv) < tiny) piv = (piv < 0.0) ? -tiny : tiny;
+      rud[i * 64] = 1.0 / piv;
+      u1[i * 64] = keep ? cc : an;
+      u2[i * 64] = keep ? 0.0 : cn;
+      lm[i * 64] = l;
+      swp[i * 64] = keep ? 0 : 1;
+      const double na = keep ? an - l * cc : cc - l * an;
+      cc = keep ? cn : -l * cn;
+      a = na;
+    }
+  });
+  rud[(m - 1) * 64] = 1.0 / ((fabs(a) < tiny) ? ((a < 0.0) ? -tiny : tiny) : a);
+  // Three solves.  The iterate stays as the back substitution left it; its two
+  // scalings (to max 1, then to norm 1) are applied as it is read.
+  double inv = 1.0, invn = 1.0;
+  for (int it = 0; it < 3; ++it) {
+    auto start = [&](int64_t i) {
+      return it == 0 ? hash_uniform(q, i) : x[i * 64] * inv * invn;
+    };
+    double cur = start(0);
+    blocks(m - 1, [&](int64_t i0, auto cnt) {
+      constexpr int n = decltype(cnt)::value;
+      double nx[n], l[n];
+      unsigned char sw[n];
+#pragma unroll
+      for (int k = 0; k < n; ++k) {
+        nx[k] = start(i0 + k + 1);
         l[k] = lm[(i0 + k) * 64];
         sw[k] = swp[(i0 + k) * 64];
       }
 #pragma unroll
-      for (int k = 0; k < kB; ++k) {
+      for (int k = 0; k < n; ++k) {
         const double c = sw[k] ? nx[k] : cur;
-        const double n = (sw[k] ? cur : nx[k]) - l[k] * c;
+        const double v = (sw[k] ? cur : nx[k]) - l[k] * c;
         x[(i0 + k) * 64] = c;
-        cur = n;
+        cur = v;
       }
-    }
-    for (int64_t i = i0; i < m - 1; ++i) {
-      const double nx = x[(i + 1) * 64], l = lm[i * 64];
-      const bool sw = swp[i * 64] != 0;
-      const double c = sw ? nx : cur;
-      const double n = (sw ? cur : nx) - l * c;
-      x[i * 64] = c;
-      cur = n;
-    }
+    });
     double x1 = cur * rud[(m - 1) * 64], x2 = 0.0;
     x[(m - 1) * 64] = x1;
     double mx = fabs(x1);
-    int64_t i1 = m - 2;
-    for (; i1 - kB + 1 >= 0; i1 -= kB) {
-      double xv[kB], a1[kB], a2[kB], r[kB];
+    blocks(m - 1, [&](int64_t i0, auto cnt) {
+      constexpr int n = decltype(cnt)::value;
+      double xv[n], a1[n], a2[n], r[n];
 #pragma unroll
-      for (int k = 0; k < kB; ++k) {
-        const int64_t i = i1 - k;
+      for (int k = 0; k < n; ++k) {
+        const int64_t i = m - 2 - i0 - k;
         xv[k] = x[i * 64];
         a1[k] = u1[i * 64];
         a2[k] = u2[i * 64];
         r[k] = rud[i * 64];
       }
 #pragma unroll
-      for (int k = 0; k < kB; ++k) {
+      for (int k = 0; k < n; ++k) {
         const double x0 = (xv[k] - a1[k] * x1 - a2[k] * x2) * r[k];
-        x[(i1 - k) * 64] = x0;
+        x[(m - 2 - i0 - k) * 64] = x0;
         mx = fmax(mx, fabs(x0));
         x2 = x1;
         x1 = x0;
       }
-    }
-    for (int64_t i = i1; i >= 0; --i) {
-      const double x0 = (x[i * 64] - u1[i * 64] * x1 - u2[i * 64] * x2) * rud[i * 64];
-      x[i * 64] = x0;
-      mx = fmax(mx, fabs(x0));
-      x2 = x1;
-      x1 = x0;
-    }
-    const double inv = (mx > 0) ? 1.0 / mx : 1.0;
+    });
+    inv = (mx > 0) ? 1.0 / mx : 1.0;
     double nn = 0;
-#pragma unroll 8
-    for (int64_t i = 0; i < m; ++i) {
-      const double v = x[i * 64] * inv;
-      x[i * 64] = v;
-      nn += v * v;
-    }
-    const double invn = (nn > 0) ? 1.0 / sqrt(nn) : 1.0;
-#pragma unroll 8
-    for (int64_t i = 0; i < m; ++i) x[i * 64] *= invn;
+    blocks(m, [&](int64_t i0, auto cnt) {
+      constexpr int n = decltype(cnt)::value;
+      double xv[n];
+#pragma unroll
+      for (int k = 0; k < n; ++k) xv[k] = x[(i0 + k) * 64];
+#pragma unroll
+      for (int k = 0; k < n; ++k) {
+        const double v = xv[k] * inv;
+        nn += v * v;
+      }
+    });
+    invn = (nn > 0) ? 1.0 / sqrt(nn) : 1.0;
   }
-  double best = -1.0;
-  int64_t bi = 0;
-  for (int64_t i = 0; i < m; ++i)
-    if (fabs(x[i * 64]) > best) {
-      best = fabs(x[i * 64]);
-      bi = i;
+  // sign: the first component of the largest magnitude is positive
+  double best = -1.0, bv = 0.0;
+  blocks(m, [&](int64_t i0, auto cnt) {
+    constexpr int n = decltype(cnt)::value;
+    double xv[n];
+#pragma unroll
+    for (int k = 0; k < n; ++k) xv[k] = x[(i0 + k) * 64];
+#pragma unroll
+    for (int k = 0; k < n; ++k) {
+      const double v = xv[k] * inv * invn;
+      if (fabs(v) > best) {
+        best = fabs(v);
+        bv = v;
+      }
     }
-  const double sg = (x[bi * 64] < 0) ? -1.0 : 1.0;
+  });
+  const double sg = (bv < 0) ? -1.0 : 1.0;
   double *sq = S + q * lds;
-  for (int64_t i = 0; i < m; ++i) sq[i] = sg * x[i * 64];
+  blocks(m, [&](int64_t i0, auto cnt) {
+    constexpr int n = decltype(cnt)::value;
+    double xv[n];
+#pragma unroll
+    for (int k = 0; k < n; ++k) xv[k] = x[(i0 + k) * 64];
+#pragma unroll
+    for (int k = 0; k < n; ++k) sq[i0 + k] = sg * (xv[k] * inv * invn);
+  });
 }
 
 // One workgroup per cluster of eigenvalues closer than `gaptol`; the group
