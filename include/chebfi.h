@@ -390,8 +390,8 @@ abi_status abi_zheev(int64_t m, void *A, int64_t lda, double *w, void *Z, int64_
  * boxes.  One filter step of every system of the batch is three launches for
  * the projector products (projection partial sums in tiles of 32 bands, their
  * reduction with D, the expansion P C' in tiles) and three FFT-pass launches per
- * group of boxes (the recurrence fused into the last), each a grid-stride loop
- * over the work items of all systems; the launches of a filter are captured
+ * group of boxes (the recurrence fused into the last), each over the work items
+ * of all systems of the group; the launches of a filter are captured
  * into a HIP graph on first use and replayed.  Limits: at most 1024 systems, at
  * most 256 atoms per system, FFT edges up to 96, S = I (no Q). */
 typedef struct abi_batch_s *abi_batch;

@@ -3,20 +3,22 @@
 //
 // The paper batches the bands of one system into one FFT call (section "Batch
 // processing"); here the batch spans systems as well.  One filter step of
-// every system is six launches (the passes once per group of boxes), each a
-// flat, grid-stride ("persistent") loop over the work items of all systems:
+// every system is three launches for the products and three per group of boxes,
+// each over the work items of all its systems:
 //   K1 proj   (system, band tile, projector tile, chunk): partial sums of C = P^H Y_k;
 //   K1r       (system, 8 bands, projector tile): C' = alpha D C per atom;
 //   K1b expand (system, plane-wave tile, band tile): E = P C';
-//   K2 pass A (system, band, i3 group):     sphere planes -> inverse xy FFT -> box;
-//   K3 pass B (system, band, i2 group):     z FFT, * V, z FFT;
-//   K4 pass C (system, band, i3 group):     forward xy FFT -> gather, kinetic term,
-//                                           + E, three-term recurrence.
+//   K2 pass A (system, band, plane):      sphere plane -> inverse xy FFT -> box;
+//   K3 pass B (system, band, z pencils):  z FFT, * V, z FFT;
+//   K4 pass C (system, band, plane):      forward xy FFT -> gather, kinetic term,
+//                                         + E, three-term recurrence.
+// Cubic boxes with compile-time passes: one item per workgroup, edge by edge; the
+// rest, and the products: grid-stride loops, groups of small planes per item.
 // The nonlocal products are small here (a few to a few hundred projectors):
 // plain FMA kernels tiled over bands and over projectors (32 each), so that P
 // is read once per tile of 32 bands.  Per-system tables,
 // per-step pointers and coefficients are read from device descriptors, so the
-// 4 x degree launches are captured once into a HIP graph and replayed.
+// launches are captured once into a HIP graph and replayed.
 #include <algorithm>
 #include <cstring>
 
@@ -493,8 +495,8 @@ __global__ __launch_bounds__((cthreads<N, zpencils<T>()>())) void bcpass_b_kerne
   // z-planes without sphere points: zero on input (pass A leaves them unwritten)
   // and not written on output (pass C does not read them)
   C2<T> *src = as_global((C2<T> *)d.box) + b * (int64_t)NXY * N + q0;
-  z_pencils<T, N>(src, as_global((const T *)d.V) + q0, NXY - q0, NXY,
-                            as_global(d.tw) + 2 * kMaxN, ZOcc{d.zocc, d.zocc_hi}, buf, tw);
+  z_pencils<T, N>(src, as_global((const T *)d.V) + q0, NXY - q0, NXY, as_global(d.tw) + 2 * kMaxN,
+                  ZOcc{d.zocc, d.zocc_hi}, buf, tw);
 }
 
 template <typename T, int N>

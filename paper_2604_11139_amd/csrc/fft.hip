@@ -8,15 +8,18 @@
 // of one band in LDS:
 //   pass A  (band, i3 plane): scatter the plane's sphere rows into a zeroed
 //           n1 x n2 plane, inverse FFT along x then y, store the plane;
-//   pass B  (band, i2 slab):  load n1 x n3, inverse FFT along z, multiply by
-//           V(r), forward FFT along z, store;
+//   pass B  (band, run of z pencils or i2 slab): load, inverse FFT along z,
+//           multiply by V(r), forward FFT along z, store;
 //   pass C  (band, i3 plane): load, forward FFT along y then x, gather the
 //           sphere rows, scale 1/(n1 n2 n3) and combine with the kinetic term
 //           and the Chebyshev recurrence:
 //           out = alpha (local + (kin - cshift) yk) - beta yprev.
-// Each 1D transform is a Stockham autosort FFT with radix-2/3/4/5 stages
-// executed in place in LDS (every thread holds its butterflies' outputs in
-// registers across a barrier).  Twiddles are FP64 tables built on the host.
+// Each 1D transform is a Stockham autosort FFT executed in place in LDS (every
+// thread holds its butterflies' outputs in registers across a barrier): two stages
+// of radix 3 to 12 with compile-time lengths where the plane is square and its edge,
+// or for pass B the z edge, is a {2,3,5}-smooth one from 12 to 96; radix-2/3/4/5
+// stages of runtime length otherwise (a 54^3 pass B took 234 us in those, 40 in
+// these).  Twiddles are FP64 tables built on the host.
 #include <cstdlib>
 
 #include "cplx.h"
