@@ -520,7 +520,7 @@ int rr_lowprec(abi_system_s *s, void *Y, int64_t ld, void *HPsi, int64_t ldh_in,
     split_planes(npw, M, B, npw, ypl, s->ldPA, st);
     part = s->cpart.get(sizeof(float2) * (size_t)splits * M * M);
     int tok = s->prof.begin(PROF_GRAM, gflops, st);
-    rr_gram_f32(M, npw, ypl, s->ldPA, B, npw, part, splits, G, st);
+    rr_gram_f32(M, npw, ypl, s->ldPA, nullptr, 0, part, splits, G, st);
     s->prof.end(tok, st);
     tok = s->prof.begin(PROF_CHOL, 4.0 / 3.0 * (double)M * M * M, st);
     zpotrf_upper(M, G, M, info, s->eig2.get(zpotrf_work_bytes(M)), st);

@@ -16,7 +16,7 @@
 //           out = alpha (local + (kin - cshift) yk) - beta yprev.
 // Each 1D transform is a Stockham autosort FFT executed in place in LDS (every
 // thread holds its butterflies' outputs in registers across a barrier): two stages
-// of radix 3 to 12 with compile-time lengths where the plane is square and its edge,
+// of radix 3 to 15 with compile-time lengths where the plane is square and its edge,
 // or for pass B the z edge, is a {2,3,5}-smooth one from 12 to 96; radix-2/3/4/5
 // stages of runtime length otherwise (a 54^3 pass B took 234 us in those, 40 in
 // these).  Twiddles are FP64 tables built on the host.

@@ -108,7 +108,8 @@ void expand_gemm_planes(int64_t npw, int64_t nband, int64_t nproj, const void *A
 // G = Y_pl^H Y (m x m complex double, ld m) for a product known to be Hermitian:
 // the 128 x 128 tiles on and above the diagonal in `splits` plane-wave chunks
 // (part: splits x m x m complex float), the rest mirrored (the planes of Y_pl
-// zero-padded to a multiple of 32, ld lda, Y complex64 with ld ldy), and
+// zero-padded to a multiple of 32, ld lda, Y complex64 with ld ldy, null for
+// the block of the planes itself), and
 // Out = A T from the transposed planes of A (npw x m, ld lda) and the planes of
 // T (m x m, ld ldt; `upper`: zero below the diagonal), both zero-padded along m.
 int rr_gram_splits(int64_t m, int64_t npw);
