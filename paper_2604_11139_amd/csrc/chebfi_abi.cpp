@@ -677,8 +677,13 @@ abi_status abi_set_system(const abi_system_desc *desc, void *stream, abi_system 
       s->pl_proj = 14;
       s->pl_expand = 15;
     }
-    // bands per FFT batch: keep the box buffer near 128 MiB
-    const int64_t fb = (int64_t)((128ll << 20) / (sizeof(double2) * nbox));
+    // bands per FFT batch: box buffers of at most 192 MiB, so that the infinity cache
+    // (256 MB) holds most of what a pass reads of the last one's output.  128 -> 192
+    // MiB: 347 bands on 36 x 36 x 80 5.08 -> 4.84 ms (two batches for three), 411
+    // complex128 bands on 54^3 19.5 -> 19.2, an S^-1 H filter of 512 bands on 36^3
+    // 4.61 -> 4.41, 2048 bands on 64^3 152.1 -> 151.6; 64 MiB 5.45, 21.0, 4.77, 161.8;
+    // 256 MiB 4.84, 19.2, 4.41, 155.3.
+    const int64_t fb = (int64_t)((192ll << 20) / (sizeof(double2) * nbox));
     s->fft_batch = (int)std::max<int64_t>(1, std::min<int64_t>(fb, 4096));
     // FFT passes beside the projection GEMM on a second stream (default priority)
     CHEBFI_HIP(hipStreamCreateWithFlags(&s->aux, hipStreamNonBlocking));
@@ -1435,7 +1440,7 @@ abi_status abi_filter_backward(abi_system s, const void *X, const void *W, int64
       }
     }
     // reverse sweep, one segment at a time
-    const int fb = (int)std::min<int64_t>(s->fft_batch * (fp32 ? 2 : 1), nband);
+    const int64_t fb = even_batch(nband, (int64_t)s->fft_batch * (fp32 ? 2 : 1));
     void *box1 = s->box.get(esz * (size_t)nbox * fb);
     void *box2 = s->box2.get(esz * (size_t)nbox * fb);
     for (int q = (int)starts.size() - 1; q >= 0; --q) {
@@ -1540,7 +1545,7 @@ abi_status abi_density(abi_system s, const void *Psi, int64_t nband, int64_t ld,
     const int64_t nbox = (int64_t)s->n1 * s->n2 * s->n3;
     launch_fill_zero(nbox, rho, st);
     const size_t es = elem_bytes(dtype);
-    const int fb = (int)std::min<int64_t>(s->fft_batch * (dtype == ABI_C64 ? 2 : 1), nband);
+    const int64_t fb = even_batch(nband, (int64_t)s->fft_batch * (dtype == ABI_C64 ? 2 : 1));
     void *box = s->box.get(es * (size_t)nbox * fb);
     for (int64_t b0 = 0; b0 < nband; b0 += fb) {
       const int nb = (int)std::min<int64_t>(fb, nband - b0);
@@ -1560,7 +1565,7 @@ abi_status abi_density_add(abi_system s, const void *Psi, int64_t nband, int64_t
     hipStream_t st = S(stream);
     const int64_t nbox = (int64_t)s->n1 * s->n2 * s->n3;
     const size_t es = elem_bytes(dtype);
-    const int fb = (int)std::min<int64_t>(s->fft_batch * (dtype == ABI_C64 ? 2 : 1), nband);
+    const int64_t fb = even_batch(nband, (int64_t)s->fft_batch * (dtype == ABI_C64 ? 2 : 1));
     void *box = s->box.get(es * (size_t)nbox * fb);
     for (int64_t b0 = 0; b0 < nband; b0 += fb) {
       const int nb = (int)std::min<int64_t>(fb, nband - b0);
