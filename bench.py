@@ -70,7 +70,7 @@ CLASS_KERNELS = {
     "expand_gemm": ("zgemm_dl_kernel<128, 128, 2, 4, false, false, false, true, true, 0>",
                     "gemm.hip"),
     "fft_a": ("cpass_a_kernel<float, 64>", "fft.hip"),
-    "fft_b": ("cpass_b_kernel<float, float, 64>", "fft.hip"),
+    "fft_b": ("zpass_kernel<float, 64>", "fft.hip"),
     "fft_c": ("cpass_c_kernel<float, 64>", "fft.hip"),
     "split": ("split_planes_kernel", "gemm.hip"),
 }
