@@ -1979,7 +1979,7 @@ abi_status abi_zheev(int64_t m, void *A, int64_t lda, double *w, void *Z, int64_
     try {
       const int *flag = zheev(m, A, lda, w, Z, ldz, work, st);
       CHEBFI_HIP(hipStreamSynchronize(st));
-      zheev_check(flag);
+      zheev_check(flag, st);
     } catch (...) {
       (void)hipFree(work);
       throw;

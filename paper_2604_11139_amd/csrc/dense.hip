@@ -1550,10 +1550,12 @@ size_t zheev_work_bytes(int64_t m) {
          30 * 256;  // each of the (at most 30) sub-buffers is rounded up to 256 bytes
 }
 
-void zheev_check(const int *dead) {
+void zheev_check(const int *dead, hipStream_t st) {
   if (!dead) return;
   int v = 0;
-  CHEBFI_HIP(hipMemcpy(&v, dead, sizeof(int), hipMemcpyDeviceToHost));
+  // (on the caller's stream alone: a blocking copy would wait for the default stream too)
+  CHEBFI_HIP(hipMemcpyAsync(&v, dead, sizeof(int), hipMemcpyDeviceToHost, st));
+  CHEBFI_HIP(hipStreamSynchronize(st));
   if (v != 0) throw Error{ABI_ERR_DEVICE, "tridiagonalisation: a workgroup waited in vain"};
 }
 

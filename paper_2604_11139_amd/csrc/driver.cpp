@@ -455,7 +455,7 @@ void setup_overlap(abi_system_s *s, const double *qij, hipStream_t st) {
     std::vector<double> hmu(n);
     CHEBFI_HIP(hipMemcpyAsync(hmu.data(), mu, sizeof(double) * n, hipMemcpyDeviceToHost, st));
     CHEBFI_HIP(hipStreamSynchronize(st));
-    zheev_check(flag);
+    zheev_check(flag, st);
     s->s_min = std::min(1.0, 1.0 + hmu[0]);
     if (!(1.0 + hmu[0] > 1e-10))
       throw Error{ABI_ERR_NOT_HPD, "overlap operator S = I + P Q P^H is not positive definite "
@@ -617,7 +617,7 @@ int rr_lowprec(abi_system_s *s, void *Y, int64_t ld, void *HPsi, int64_t ldh_in,
   if (resnorm)
     CHEBFI_HIP(hipMemcpyAsync(resnorm, r_dev, sizeof(double) * M, hipMemcpyDeviceToHost, st));
   CHEBFI_HIP(hipStreamSynchronize(st));
-  zheev_check(flag);
+  zheev_check(flag, st);
   return U1i ? 2 : 1;
 }
 
@@ -718,7 +718,7 @@ void rr_core(abi_system_s *s, double2 *Y, int64_t ld, double2 *HPsi, int64_t ldh
   if (resnorm)
     CHEBFI_HIP(hipMemcpyAsync(resnorm, r_dev, sizeof(double) * M, hipMemcpyDeviceToHost, st));
   CHEBFI_HIP(hipStreamSynchronize(st));
-  zheev_check(flag);
+  zheev_check(flag, st);
 }
 
 void gen_step(abi_system_s *s, const void *X, int64_t ldx, const void *Xprev, int64_t ldp,

@@ -53,8 +53,7 @@ bool ortho_rr_basis(abi_system_s *s, int64_t k, int64_t mout, const double2 *Z,
   const int *flag = zheev(k, Hs, k, w_dev, Y, k, s->eig1.get(zheev_work_bytes(k)), st);
   s->prof.end(tok, st);
   zgemm_tri(TRI_UB, k, mout, G, k, Y, k, C, k, st);
-  CHEBFI_HIP(hipStreamSynchronize(st));
-  zheev_check(flag);
+  zheev_check(flag, st);
   return true;
 }
 
