@@ -498,6 +498,15 @@ abi_status abi_apply_H_noalloc(abi_system sys, const void *X, void *HX, int64_t 
  *                      one MI355X the kernels, not the launches, bound the
  *                      filter down to the smallest workload: replays gain
  *                      nothing there, so it is off by default.)
+ *   ABI_TUNE_EIG_POLLS >= 0 (default 2^21, about two seconds): the eigensolver of
+ *                      Rayleigh-Ritz and LOBPCG reduces up to 2048 columns in one
+ *                      cooperative launch whose workgroups poll for each other's
+ *                      words.  Where something else on the GPU keeps some of
+ *                      them from starting (another process, or a kernel on another
+ *                      stream that waits itself), a workgroup gives up after this
+ *                      many polls and the matrix is reduced column by column
+ *                      instead, with the same result to rounding.  0: column by
+ *                      column at once (for a GPU that is shared for long)
  * Fails with ABI_ERR_ARG for an unknown parameter or a value out of range, and
  * with ABI_ERR_STATE for a mixed-form parameter on an FP64 handle. */
 enum {
@@ -507,7 +516,8 @@ enum {
   ABI_TUNE_OVERLAP = 3,
   ABI_TUNE_GENERIC_FFT = 4,
   ABI_TUNE_MIXED_GEMM = 5,
-  ABI_TUNE_FILTER_GRAPH = 6
+  ABI_TUNE_FILTER_GRAPH = 6,
+  ABI_TUNE_EIG_POLLS = 7
 };
 abi_status abi_set_tuning(abi_system sys, int32_t param, int32_t value);
 abi_status abi_get_tuning(abi_system sys, int32_t param, int32_t *value);

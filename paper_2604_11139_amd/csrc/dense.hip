@@ -521,14 +521,19 @@ __global__ __launch_bounds__(kTriFinT) void tri_fin_kernel(
 // which every reader of step c + 2 has seen.  A workgroup with no column left
 // stops after publishing; the words it would clear are never read again.
 //
-// The launch is cooperative: all workgroups are resident, so a published word
-// always arrives.  A wait is bounded all the same (kTriSpins polls, about two
-// seconds); a thread that gives up sets *dead, waits for nothing more, and the
-// caller reports the error.
+// The launch is cooperative: all workgroups become resident together, so a published
+// word arrives, unless something else holds compute units meanwhile (a kernel of
+// another process, or one on another stream that itself waits).  So a wait is bounded:
+// a thread whose poll number `polls` finds a word missing sets *dead and waits for
+// nothing more, and zheev then reduces the matrix again column by column.  What that
+// takes is still there: this kernel writes to A below the sub-diagonal only.
 constexpr int kTriRegT = 512;    // threads: eight waves
 constexpr int kTriRegC = 8;      // columns per workgroup
 constexpr int kTriRegR = 4;      // most rows per thread (2048 rows)
-constexpr int kTriSpins = 1 << 21;
+// fewest rows: a Rayleigh-Ritz step of 8 bands takes 486 us with the one launch and 476
+// column by column (no cooperative launch, no flag to wait for), one of 10 514 and 517,
+// one of 16 576 and 630
+constexpr int kTriRegMin = 10;
 constexpr unsigned long long kTriEmpty = 0x7FF4C0DEC0DEC0DEull;  // a NaN no result has
 
 __device__ __forceinline__ void tri_put(unsigned long long *p, double v) {
@@ -618,7 +623,8 @@ __global__ __launch_bounds__(kTriRegT) void tri_reg_kernel(int64_t m, double2 *_
                                                            double *__restrict__ d,
                                                            double *__restrict__ e,
                                                            double2 *__restrict__ tau,
-                                                           unsigned long long *xch, int *dead) {
+                                                           unsigned long long *xch, int *dead,
+                                                           int polls) {
   constexpr int C = kTriRegC, T = kTriRegT, NW = T / 64;
   static_assert(2 * C == 16, "wave_sum16 carries the dots of a workgroup");
   __shared__ double zpart[NW][2 * C];
@@ -750,7 +756,7 @@ __global__ __launch_bounds__(kTriRegT) void tri_reg_kernel(int64_t m, double2 *_
           ok = ok && w0[p] != kTriEmpty && w1[p] != kTriEmpty && w2[p] != kTriEmpty &&
                w3[p] != kTriEmpty;
         if (ok || gone) break;
-        if (++spins >= kTriSpins) {
+        if (++spins >= polls) {
           gone = true;
           __hip_atomic_store(dead, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
@@ -827,10 +833,29 @@ __global__ __launch_bounds__(kTriRegT) void tri_reg_kernel(int64_t m, double2 *_
     if (t + T * p == N - 1 && (N > 1 || g == 0)) d[c0 + N - 1] = xr[p];
 }
 
+// Lower triangle of A[c0:, c0:] <- conjugate transpose of the upper one, in 32 x 32
+// blocks (bi <= bj) through LDS.
+__global__ __launch_bounds__(256) void mirror_upper_kernel(int64_t m, double2 *__restrict__ A,
+                                                           int64_t lda, int64_t c0) {
+  __shared__ double2 t[32][33];
+  const int64_t bi = blockIdx.x, bj = blockIdx.y;
+  if (bi > bj) return;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  const int64_t r0 = c0 + 32 * bi, q0 = c0 + 32 * bj;
+  for (int c = ty; c < 32; c += 8)
+    if (r0 + tx < m && q0 + c < m) t[c][tx] = A[(r0 + tx) + (q0 + c) * lda];
+  __syncthreads();
+  for (int c = ty; c < 32; c += 8) {
+    const int64_t r = q0 + tx, q = r0 + c;
+    if (r < m && q < m && r > q) A[r + q * lda] = conj2(t[tx][c]);
+  }
+}
+
 // Launches tri_reg_kernel on A[c0:, c0:]; false (nothing launched) when the
 // device cannot hold all its workgroups at once.
 bool launch_tri_reg(int64_t m, double2 *A, int64_t lda, int64_t c0, const double2 *xv, double *d,
-                    double *e, double2 *tau, unsigned long long *xch, int *dead, hipStream_t st) {
+                    double *e, double2 *tau, unsigned long long *xch, int *dead, int polls,
+                    hipStream_t st) {
   const int64_t n = m - c0;
   const unsigned groups = nblk(n, kTriRegC);
   const void *f = n <= kTriRegT       ? reinterpret_cast<const void *>(tri_reg_kernel<1>)
@@ -838,7 +863,7 @@ bool launch_tri_reg(int64_t m, double2 *A, int64_t lda, int64_t c0, const double
                                       : reinterpret_cast<const void *>(tri_reg_kernel<kTriRegR>);
   hipLaunchKernelGGL(tri_clear_kernel, dim3(nblk(tri_words(n), 256)), dim3(256), 0, st,
                      tri_words(n), xch, dead);
-  void *args[] = {&m, &A, &lda, &c0, &xv, &d, &e, &tau, &xch, &dead};
+  void *args[] = {&m, &A, &lda, &c0, &xv, &d, &e, &tau, &xch, &dead, &polls};
   const hipError_t r = hipLaunchCooperativeKernel(f, dim3(groups), dim3(kTriRegT), args, 0, st);
   if (r == hipSuccess) return true;
   (void)hipGetLastError();
@@ -888,11 +913,24 @@ __device__ int sturm_less_lds(int64_t m, const double *d, const double *e2, doub
   return cnt;
 }
 
-__global__ __launch_bounds__(256) void tri_prep_kernel(int64_t m, const double *__restrict__ d,
-                                const double *__restrict__ e, double *__restrict__ e2,
-                                double *__restrict__ stats) {
+// (gave_up, if given, points to the flag of the tri_reg_kernel that reduced from column
+// c0 on: where it is set, d and e are no tridiagonal from there on, and the work queued
+// behind gets a harmless one, without clusters, until the host sees the flag)
+__global__ __launch_bounds__(256) void tri_prep_kernel(int64_t m, double *__restrict__ d,
+                                double *__restrict__ e, double *__restrict__ e2,
+                                double *__restrict__ stats, const int *__restrict__ gave_up,
+                                int64_t c0) {
   // stats[0] = Gershgorin lower, stats[1] = upper, stats[2] = |T| scale, stats[3] = pivmin
   __shared__ double slo[256], shi[256], smax[256];
+  if (gave_up && *gave_up) {
+    double gap = 1.0;  // above all of the columns reduced before
+    for (int64_t i = 0; i < c0; ++i) gap = fmax(gap, fabs(d[i]) + fabs(e[i]));
+    for (int64_t i = c0 + threadIdx.x; i < m; i += blockDim.x) {
+      d[i] = gap * (double)(i + 1);
+      e[i] = 0.0;
+    }
+    __syncthreads();
+  }
   double lo = 1e300, hi = -1e300, mx = 0, emax2 = 0;
   for (int64_t i = threadIdx.x; i < m; i += blockDim.x) {
     const double r = (i > 0 ? fabs(e[i - 1]) : 0.0) + (i < m - 1 ? fabs(e[i]) : 0.0);
@@ -1550,17 +1588,8 @@ size_t zheev_work_bytes(int64_t m) {
          30 * 256;  // each of the (at most 30) sub-buffers is rounded up to 256 bytes
 }
 
-void zheev_check(const int *dead, hipStream_t st) {
-  if (!dead) return;
-  int v = 0;
-  // (on the caller's stream alone: a blocking copy would wait for the default stream too)
-  CHEBFI_HIP(hipMemcpyAsync(&v, dead, sizeof(int), hipMemcpyDeviceToHost, st));
-  CHEBFI_HIP(hipStreamSynchronize(st));
-  if (v != 0) throw Error{ABI_ERR_DEVICE, "tridiagonalisation: a workgroup waited in vain"};
-}
-
-const int *zheev(int64_t m, void *Av, int64_t lda, double *wout, void *Zv, int64_t ldz, void *work,
-                 hipStream_t st) {
+void zheev(int64_t m, void *Av, int64_t lda, double *wout, void *Zv, int64_t ldz, void *work,
+           hipStream_t st, int polls) {
   CHEBFI_REQUIRE(m >= 1 && m <= kEigMaxM, ABI_ERR_ARG, "eigensolver size out of range");
   double2 *A = (double2 *)Av;
   double2 *Z = (double2 *)Zv;
@@ -1594,46 +1623,57 @@ const int *zheev(int64_t m, void *Av, int64_t lda, double *wout, void *Zv, int64
   double *lwork = (double *)take(sizeof(double) * 5 * lane_slab);
   unsigned char *lswp = (unsigned char *)take(lane_slab);
 
+  // clusters' arrays of the inverse iteration in LDS up to kLdsInvitM, else in a
+  // global slab per leader
+  const bool in_lds = m <= kLdsInvitM;
+  unsigned char *gws = in_lds ? nullptr : (unsigned char *)take((size_t)m * invit_bytes(m));
+
   launch_hermitize(m, A, lda, st);
-  // reduction to tridiagonal form: panels of kTriNB columns (two launches per
-  // column, one GEMM update of the trailing matrix and one copy of the next panel's
-  // first column) until the trailing matrix fits the registers, then one launch
-  hipLaunchKernelGGL(tri_start_kernel, dim3(nblk(m, kTriRows)), dim3(64), 0, st, m, A, lda,
-                     int64_t{0}, xv, d, normpart);
-  int64_t j0 = 0;
+  // reduction to tridiagonal form from column c0 on: panels of kTriNB columns (two
+  // launches per column, one GEMM update of the trailing matrix and one copy of the
+  // next panel's first column) until the trailing matrix fits the registers, then one
+  // launch (unless reg is false).  Returns the column that one started from, or m.
+  auto start = [&](int64_t c) {
+    hipLaunchKernelGGL(tri_start_kernel, dim3(nblk(m - c, kTriRows)), dim3(64), 0, st, m, A, lda,
+                       c, xv, d, normpart);
+  };
   auto panel_update = [&](int64_t c) {  // A[c:, c:] -= [U W] [W U]^H, then column c
     const int64_t L = m - c;
     zgemm(OP_N, OP_N, L, L, 2 * kTriNB, P1 + c, m, Q + c * 2 * kTriNB, 2 * kTriNB,
           A + c + c * lda, lda, double2{-1, 0}, double2{1, 0}, st);
-    hipLaunchKernelGGL(tri_start_kernel, dim3(nblk(L, kTriRows)), dim3(64), 0, st, m, A, lda, c,
-                       xv, d, normpart);
+    start(c);
   };
-  bool whole = false;  // the rest of the reduction ran in registers
-  for (int64_t c = 0; c + 1 < m; ++c) {
-    if (c == j0 + kTriNB) {
-      panel_update(c);
-      j0 = c;
+  auto reduce = [&](int64_t c0, bool reg) -> int64_t {
+    start(c0);
+    int64_t j0 = c0;
+    for (int64_t c = c0; c + 1 < m; ++c) {
+      if (c == j0 + kTriNB) {
+        panel_update(c);
+        j0 = c;
+      }
+      if (reg && c == j0 && m - c >= kTriRegMin && m - c <= kTriRegT * kTriRegR &&
+          m - c <= (int64_t)kTriRegC * device_cus()) {
+        if (launch_tri_reg(m, A, lda, c, xv, d, e, tau, xch, dead, polls, st)) return c;
+        reg = false;
+      }
+      const int k = (int)(c - j0);
+      const int64_t L = m - c - 1;
+      const int nrb = (int)nblk(L, kTriRows);
+      hipLaunchKernelGGL(tri_mv_kernel, dim3((unsigned)(L + nrb)), dim3(256), 0, st, m, A, lda, c,
+                         k, xv, normpart, (int)nblk(m - c, kTriRows), P1, Q, yv, yupart, stpart, e,
+                         tau);
+      const int next = (c + 1 < j0 + kTriNB) ? 1 : 0;
+      hipLaunchKernelGGL(tri_fin_kernel, dim3(nrb), dim3(kTriFinT), 0, st, m, A, lda, c, k, next,
+                         nrb, P1, Q, yv, yupart, stpart, tau, xv, d, normpart);
     }
-    if (c == j0 && m - c <= kTriRegT * kTriRegR && m - c <= (int64_t)kTriRegC * device_cus() &&
-        launch_tri_reg(m, A, lda, c, xv, d, e, tau, xch, dead, st)) {
-      whole = true;
-      break;
-    }
-    const int k = (int)(c - j0);
-    const int64_t L = m - c - 1;
-    const int nrb = (int)nblk(L, kTriRows);
-    hipLaunchKernelGGL(tri_mv_kernel, dim3((unsigned)(L + nrb)), dim3(256), 0, st, m, A, lda, c, k,
-                       xv, normpart, (int)nblk(m - c, kTriRows), P1, Q, yv, yupart, stpart, e,
-                       tau);
-    const int next = (c + 1 < j0 + kTriNB) ? 1 : 0;
-    hipLaunchKernelGGL(tri_fin_kernel, dim3(nrb), dim3(kTriFinT), 0, st, m, A, lda, c, k, next,
-                       nrb, P1, Q, yv, yupart, stpart, tau, xv, d, normpart);
-  }
-  if (!whole && m >= 2 && m - 1 == j0 + kTriNB) panel_update(m - 1);  // the last diagonal entry
-  CHEBFI_HIP(hipGetLastError());
-  // eigenvalues of the tridiagonal
-  hipLaunchKernelGGL(tri_prep_kernel, dim3(1), dim3(256), 0, st, m, d, e, e2, stats);
-  {
+    if (m >= 2 && m - 1 == j0 + kTriNB) panel_update(m - 1);  // the last diagonal entry
+    CHEBFI_HIP(hipGetLastError());
+    return m;
+  };
+  // eigenvalues and eigenvectors of the tridiagonal; below kBtMinM columns also the
+  // back-transformation, one reflector at a time (A is only read)
+  auto vectors = [&](const int *flag, int64_t c0) {
+    hipLaunchKernelGGL(tri_prep_kernel, dim3(1), dim3(256), 0, st, m, d, e, e2, stats, flag, c0);
     // d and e2 in LDS up to m = 4096 (64 KB)
     const int lds = m <= 4096 ? 1 : 0;
     const size_t lb = lds ? sizeof(double) * 2 * (size_t)m : 0;
@@ -1642,56 +1682,19 @@ const int *zheev(int64_t m, void *Av, int64_t lda, double *wout, void *Zv, int64
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lb));
     hipLaunchKernelGGL(bisect_kernel, dim3(nblk(m, 4)), dim3(256), lb, st, m, d, e2, stats, wout,
                        lds);
-  }
-  CHEBFI_HIP(hipGetLastError());
-  // eigenvectors of the tridiagonal
-  // clusters: arrays in LDS up to kLdsInvitM, else in a global slab per leader
-  const bool in_lds = m <= kLdsInvitM;
-  const size_t lds_bytes = in_lds ? sizeof(double) * 7 * (size_t)m + (size_t)m + 64 : 0;
-  unsigned char *gws = in_lds ? nullptr : (unsigned char *)take((size_t)m * invit_bytes(m));
-  if (in_lds)
-    CHEBFI_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(invit_kernel),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes));
-  hipLaunchKernelGGL(invit_lane_kernel, dim3(nblk(m, 64)), dim3(64), 0, st, m, d, e, wout, stats,
-                     S, m, lwork, lswp);
-  hipLaunchKernelGGL(invit_kernel, dim3((unsigned)m), dim3(256), lds_bytes, st, m, d, e, wout,
-                     stats, S, m, gws, invit_bytes(m));
-  CHEBFI_HIP(hipGetLastError());
-  hipLaunchKernelGGL(real_to_complex_kernel, dim3(nblk(m * m, 256)), dim3(256), 0, st, m, S, m, Z,
-                     ldz);
-  // back-transformation Z = H_0 H_1 ... H_{m-2} S, in blocks of kBtBlock reflectors
-  // from the last: Z <- (I - V T V^H) Z = Z - V (T (V^H Z)) on rows j0+1 .. m-1
-  const int64_t nref = m - 1;
-  if (m >= kBtMinM) {
-    // every block's V^H V and T first (they do not depend on Z), then the blocks
-    const int64_t nblocks = nblk(nref, kBtBlock);
-    double2 *T = (double2 *)take(sizeof(double2) * (size_t)nblocks * kBtBlock * kBtBlock);
-    double2 *W1 = (double2 *)take(sizeof(double2) * (size_t)kBtBlock * m);
-    double2 *W2 = (double2 *)take(sizeof(double2) * (size_t)kBtBlock * m);
-    double2 *Wp = (double2 *)take(sizeof(double2) * (size_t)kBtSplits * kBtBlock * (m + kBtBlock));
-    hipLaunchKernelGGL(clean_v_kernel, dim3(nblk(m, 256), (unsigned)m), dim3(256), 0, st, m, A,
-                       lda);
-    const int spg = (int)std::max<int64_t>(
-        1, std::min<int64_t>({kBtSplits, m / 64, device_cus() / nblocks}));
-    zgemm_diag_tiles(nref, m, A, lda, Wp, spg, st);
-    hipLaunchKernelGGL(larft_kernel, dim3((unsigned)nblocks), dim3(kBtBlock * kLarftLanes), 0, st,
-                       nref, spg, Wp, tau, T);
     CHEBFI_HIP(hipGetLastError());
-    for (int64_t b = nblocks - 1; b >= 0; --b) {
-      const int64_t j0 = b * kBtBlock;
-      const int nb = (int)std::min<int64_t>(kBtBlock, nref - j0);
-      const int64_t Lr = m - j0 - 1;
-      const double2 *V = A + (j0 + 1) + j0 * lda;
-      double2 *Zr = Z + (j0 + 1);
-      const int sp = std::min(kBtSplits, zgemm_splits(nb, m, Lr));
-      zgemm(OP_C, OP_N, nb, m, Lr, V, lda, Zr, ldz, nullptr, 0, double2{1, 0}, double2{0, 0}, st,
-            Wp, sp);
-      zsum_parts(nb, m, Wp, sp, W1, nb, double2{1, 0}, double2{0, 0}, st);
-      zgemm(OP_N, OP_N, nb, m, nb, T + b * kBtBlock * kBtBlock, kBtBlock, W1, nb, W2, nb,
-            double2{1, 0}, double2{0, 0}, st);
-      zgemm(OP_N, OP_N, Lr, m, nb, V, lda, W2, nb, Zr, ldz, double2{-1, 0}, double2{1, 0}, st);
-    }
-  } else {
+    const size_t lds_bytes = in_lds ? sizeof(double) * 7 * (size_t)m + (size_t)m + 64 : 0;
+    if (in_lds)
+      CHEBFI_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(invit_kernel),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes));
+    hipLaunchKernelGGL(invit_lane_kernel, dim3(nblk(m, 64)), dim3(64), 0, st, m, d, e, wout, stats,
+                       S, m, lwork, lswp);
+    hipLaunchKernelGGL(invit_kernel, dim3((unsigned)m), dim3(256), lds_bytes, st, m, d, e, wout,
+                       stats, S, m, gws, invit_bytes(m));
+    CHEBFI_HIP(hipGetLastError());
+    hipLaunchKernelGGL(real_to_complex_kernel, dim3(nblk(m * m, 256)), dim3(256), 0, st, m, S, m,
+                       Z, ldz);
+    if (m >= kBtMinM) return;
     for (int64_t j = m - 2; j >= 0; --j) {
       const int64_t L = m - j - 1;
       hipLaunchKernelGGL(load_u_kernel, dim3(nblk(L, 256)), dim3(256), 0, st, m, A, lda, j, u);
@@ -1700,9 +1703,57 @@ const int *zheev(int64_t m, void *Av, int64_t lda, double *wout, void *Zv, int64
       hipLaunchKernelGGL(bt_update_kernel, dim3(nblk(L, 256), (unsigned)m), dim3(256), 0, st, m, j,
                          tau, u, wrow, Z, ldz);
     }
+    CHEBFI_HIP(hipGetLastError());
+  };
+  const int64_t c0 = reduce(0, polls > 0);
+  vectors(c0 < m ? dead : nullptr, c0);
+  if (c0 < m) {
+    // Did the one launch end with every word read?  Asked with the tridiagonal's work
+    // queued behind it (asked at once, the host's launches of that came 20 to 115 us
+    // later) and before the blocked back-transformation overwrites A.
+    int gave_up = 0;
+    CHEBFI_HIP(hipMemcpyAsync(&gave_up, dead, sizeof(int), hipMemcpyDeviceToHost, st));
+    CHEBFI_HIP(hipStreamSynchronize(st));
+    if (gave_up) {
+      const unsigned nb = nblk(m - c0, 32);
+      hipLaunchKernelGGL(mirror_upper_kernel, dim3(nb, nb), dim3(256), 0, st, m, A, lda, c0);
+      reduce(c0, false);
+      vectors(nullptr, m);
+    }
+  }
+  if (m < kBtMinM) return;
+  // back-transformation Z = H_0 H_1 ... H_{m-2} S, in blocks of kBtBlock reflectors
+  // from the last: Z <- (I - V T V^H) Z = Z - V (T (V^H Z)) on rows j0+1 .. m-1
+  const int64_t nref = m - 1;
+  // every block's V^H V and T first (they do not depend on Z), then the blocks
+  const int64_t nblocks = nblk(nref, kBtBlock);
+  double2 *T = (double2 *)take(sizeof(double2) * (size_t)nblocks * kBtBlock * kBtBlock);
+  double2 *W1 = (double2 *)take(sizeof(double2) * (size_t)kBtBlock * m);
+  double2 *W2 = (double2 *)take(sizeof(double2) * (size_t)kBtBlock * m);
+  double2 *Wp = (double2 *)take(sizeof(double2) * (size_t)kBtSplits * kBtBlock * (m + kBtBlock));
+  hipLaunchKernelGGL(clean_v_kernel, dim3(nblk(m, 256), (unsigned)m), dim3(256), 0, st, m, A,
+                     lda);
+  const int spg = (int)std::max<int64_t>(
+      1, std::min<int64_t>({kBtSplits, m / 64, device_cus() / nblocks}));
+  zgemm_diag_tiles(nref, m, A, lda, Wp, spg, st);
+  hipLaunchKernelGGL(larft_kernel, dim3((unsigned)nblocks), dim3(kBtBlock * kLarftLanes), 0, st,
+                     nref, spg, Wp, tau, T);
+  CHEBFI_HIP(hipGetLastError());
+  for (int64_t b = nblocks - 1; b >= 0; --b) {
+    const int64_t j0 = b * kBtBlock;
+    const int nb = (int)std::min<int64_t>(kBtBlock, nref - j0);
+    const int64_t Lr = m - j0 - 1;
+    const double2 *V = A + (j0 + 1) + j0 * lda;
+    double2 *Zr = Z + (j0 + 1);
+    const int sp = std::min(kBtSplits, zgemm_splits(nb, m, Lr));
+    zgemm(OP_C, OP_N, nb, m, Lr, V, lda, Zr, ldz, nullptr, 0, double2{1, 0}, double2{0, 0}, st,
+          Wp, sp);
+    zsum_parts(nb, m, Wp, sp, W1, nb, double2{1, 0}, double2{0, 0}, st);
+    zgemm(OP_N, OP_N, nb, m, nb, T + b * kBtBlock * kBtBlock, kBtBlock, W1, nb, W2, nb,
+          double2{1, 0}, double2{0, 0}, st);
+    zgemm(OP_N, OP_N, Lr, m, nb, V, lda, W2, nb, Zr, ldz, double2{-1, 0}, double2{1, 0}, st);
   }
   CHEBFI_HIP(hipGetLastError());
-  return whole ? dead : nullptr;
 }
 
 }  // namespace chebfi

@@ -86,6 +86,7 @@ void *scratch_for_device(int dev);
 size_t scratch_bytes();
 
 // ---- FFT plan -------------------------------------------------------------
+constexpr int kEigPolls = 1 << 21;  // polls of the eigensolver's one-launch reduction: about 2 s
 constexpr int kMaxN = 96;       // largest box edge handled by the LDS passes (an FP64
                                 // 96 x 97 plane with its twiddles: 152 KB of LDS)
 constexpr int kMaxStages = 6;   // radix stages per 1D transform
@@ -261,7 +262,8 @@ struct abi_system_s {
   double *d_B = nullptr, *d_K = nullptr;
   double s_min = 1.0;
   int mixed_gemm = 0;              // 0: split-BF16 MFMA, 1: FP32 MFMA projector products
-  int generic_fft = 0;             // 1: runtime-size FFT passes also for cubic boxes
+  int generic_fft = 0;             // 1: runtime-size FFT passes also for specialised boxes
+  int eig_polls = chebfi::kEigPolls;  // zheev's polls
   int pl_proj = 0, pl_expand = 0;  // tile variants of the split-BF16 products
   // Chained planes (projection variants 15, 16, inside one filter run): the last
   // FFT pass of a step also writes the bf16 planes of its output into `planes`,

@@ -263,11 +263,11 @@ size_t zpotrf_work_bytes(int64_t m);
 void ztrtri_upper(int64_t m, void *A, int64_t lda, void *work, hipStream_t st);
 size_t ztrtri_work_bytes(int64_t m);
 // Hermitian eigensolver: A (m x m, overwritten) -> w ascending, Z.
-// Returns a device flag in `work` (or null) to hand to zheev_check, which drains the
-// stream and throws if a workgroup of the reduction gave up waiting.
-const int *zheev(int64_t m, void *A, int64_t lda, double *w, void *Z, int64_t ldz, void *work,
-                 hipStream_t st);
-void zheev_check(const int *flag, hipStream_t st);
+// polls: how often a workgroup of the one-launch reduction looks for another's words
+// before the matrix is reduced column by column instead (0: column by column at once).
+// Waits for the stream in mid-work where the one-launch reduction runs.
+void zheev(int64_t m, void *A, int64_t lda, double *w, void *Z, int64_t ldz, void *work,
+           hipStream_t st, int polls = kEigPolls);
 size_t zheev_work_bytes(int64_t m);
 
 // Threads per workgroup that one Stockham stage over npen pencils of the plan needs
