@@ -33,6 +33,12 @@ int mixed_proj_splits(abi_system_s *s, int64_t nband, bool fewest) {
   return proj_planes_splits(v, s->nproj, nband, s->npw, fewest);
 }
 
+// The projection variant in use: a no-allocation call keeps to the block-reading tile
+// (no planes buffer in the scratch array) with the same tile and K split as 15.
+static int proj_variant(const abi_system_s *s) {
+  return (g_scratch_arena && s->pl_proj >= 15) ? 14 : s->pl_proj;
+}
+
 int proj_splits(abi_system_s *s, int64_t nband, int32_t dtype) {
   const bool fp32 = dtype == ABI_C64, planes = fp32 && s->mixed_gemm == 0;
   if (nband == 1 && !fp32) return 1;
@@ -42,10 +48,13 @@ int proj_splits(abi_system_s *s, int64_t nband, int32_t dtype) {
   };
   const int n = count(false);
   if (!g_scratch_arena) return n;
-  // partials, C', its planes, the projector part E and one box, 256-byte aligned
+  // partials, C', its planes, the projector part E, the block's planes and one box,
+  // 256-byte aligned
   const size_t eb = elem_bytes(dtype), c = (size_t)s->nproj * nband;
+  const bool xplanes = planes && !proj_reads_block(proj_variant(s));
   const size_t need = eb * c * (n + 1) + (planes ? 8 * (size_t)s->ldPB * nband : 0) +
                       (planes ? eb * (size_t)s->npw * nband : 0) +
+                      (xplanes ? 8 * (size_t)s->ldPA * nband : 0) +
                       eb * (size_t)s->n1 * s->n2 * s->n3 + 8 * 256;
   return need <= g_scratch_arena->size ? n : count(true);
 }
@@ -58,9 +67,7 @@ void mixed_project(abi_system_s *s, const void *X, int64_t ldx, int64_t nband, v
                    int splits, hipStream_t st, bool have_planes) {
   const int64_t npw = s->npw;
   const int nproj = s->nproj;
-  // a no-allocation call keeps to the block-reading tile (no planes buffer in
-  // the scratch array); same tile and K split as 15
-  const int v = (g_scratch_arena && s->pl_proj >= 15) ? 14 : s->pl_proj;
+  const int v = proj_variant(s);
   const double flops = 8.0 * (double)nproj * (double)npw * (double)nband;
   if (proj_reads_block(v)) {
     const int tok = s->prof.begin(PROF_PROJ, flops, st);
