@@ -765,13 +765,13 @@ abi_status abi_apply_H_noalloc(abi_system s, const void *X, void *HX, int64_t nb
     ScratchArena arena;
     arena.base = (char *)s->scratch;
     arena.size = scratch_bytes();
-    const bool fp32 = dtype == ABI_C64;
-    if (!fp32 && s->nproj > 0) {
-      // the FP64 path runs the FFT passes before the projector products: keep
+    const bool planes = dtype == ABI_C64 && s->mixed_gemm == 0;
+    if (!planes && s->nproj > 0) {
+      // all but the split-BF16 planes products follow the FFT passes: keep
       // room for the split-K parts and C' behind the box batch
       const ArenaScope scope(&arena);
       const int64_t splits = proj_splits(s, nband, dtype);
-      arena.reserve = sizeof(double2) * (size_t)s->nproj * nband * (splits + 1) + 512;
+      arena.reserve = elem_bytes(dtype) * (size_t)s->nproj * nband * (splits + 1) + 512;
     }
     const int overlap = s->overlap;
     s->overlap = 0;  // one stream: the second one's events are not needed
