@@ -2075,8 +2075,10 @@ abi_status abi_batch_autotune(abi_batch B, const void *const *X, void *const *Y,
   return guarded([&] {
     hipStream_t st = S(stream);
     batch_filter(B, X, Y, nband, ld, dtype, degree, a, b, a0, st);  // validates, warms up
-    const bool graph = B->use_graph;
+    // eager filters in the order that later calls run: a graph holds the products in line
+    const bool graph = B->use_graph, overlap = B->overlap;
     B->use_graph = false;
+    if (graph) B->overlap = false;
     hipEvent_t e0, e1;
     CHEBFI_HIP(hipEventCreate(&e0));
     CHEBFI_HIP(hipEventCreate(&e1));
@@ -2119,6 +2121,7 @@ abi_status abi_batch_autotune(abi_batch B, const void *const *X, void *const *Y,
       (void)hipEventDestroy(e0);
       (void)hipEventDestroy(e1);
       B->use_graph = graph;
+      B->overlap = overlap;
       throw;
     }
     (void)hipEventDestroy(e0);
@@ -2127,6 +2130,7 @@ abi_status abi_batch_autotune(abi_batch B, const void *const *X, void *const *Y,
     B->proj_threads = bp;
     B->radix_desc = br;
     B->use_graph = graph;
+    B->overlap = overlap;
     batch_filter(B, X, Y, nband, ld, dtype, degree, a, b, a0, st);
     CHEBFI_HIP(hipStreamSynchronize(st));
     if (choice) {
