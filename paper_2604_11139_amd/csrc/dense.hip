@@ -100,8 +100,12 @@ __device__ __forceinline__ void invert_upper32(const double2 (&u)[NB][NB + 1],
       const int k = 8 * r + q;
       if (g == q) {
         const double2 d = u[k][k];
-        const double den = 1.0 / (d.x * d.x + d.y * d.y);
-        x[r] = cscale(cmul(x[r], double2{d.x, -d.y}), den);
+        // (a Cholesky factor's diagonal is real: one division, and no |d|^2, which
+        // underflows from 1e-154 down)
+        if (d.y == 0.0)
+          x[r] = cscale(x[r], 1.0 / d.x);
+        else
+          x[r] = cscale(cmul(x[r], double2{d.x, -d.y}), 1.0 / (d.x * d.x + d.y * d.y));
         row[k & 1][j] = x[r];
       }
       __syncthreads();
