@@ -306,8 +306,6 @@ CHEBFI_CPLAN(90, 2, 9, 10, 1)
 CHEBFI_CPLAN(96, 2, 8, 12, 1)
 #undef CHEBFI_CPLAN
 
-constexpr int kCT = 512;  // threads of the batched passes (16 waves per CU per 4 planes)
-
 // Threads of a pass over NPEN pencils of length N: one butterfly of the widest
 // stage per thread, in as few rounds as keep the workgroup at 576 threads or
 // fewer (a 36 x 36 plane has 216 radix-6 butterflies: 256 threads, not 512 of
@@ -331,14 +329,12 @@ constexpr int cld() {
   return N % 2 ? N + 2 : N + 1;
 }
 
-// NG groups of NPEN pencils (group g's pencils start at g * GS): several
-// planes of one LDS buffer transformed by one pass over all their pencils.
-template <typename T, int N, int R, int P, int NPEN, int ES, int PS, int SGN, int NG = 1,
-          int GS = 0, int CT = kCT>
+// One stage in place over NPEN pencils held in LDS, element e of pencil q at
+// buf[q * PS + e * ES], by CT threads.
+template <typename T, int N, int R, int P, int NPEN, int ES, int PS, int SGN, int CT>
 __device__ __forceinline__ void cstage(C2<T> *buf, const C2<T> *tw) {
   constexpr int NBF = N / R;
-  constexpr int NP = NG * NPEN;
-  constexpr int TOTAL = NP * NBF;
+  constexpr int TOTAL = NPEN * NBF;
   constexpr int M = N / (P * R);
   constexpr int MAXB = (TOTAL + CT - 1) / CT;
   C2<T> y[MAXB][R];
@@ -348,8 +344,8 @@ __device__ __forceinline__ void cstage(C2<T> *buf, const C2<T> *tw) {
     const int i = threadIdx.x + c * CT;
     dst[c] = -1;
     if (TOTAL % CT == 0 || i < TOTAL) {
-      const int pa = i % NP, bf = i / NP;
-      const int base = NG == 1 ? pa * PS : (pa / NPEN) * GS + (pa % NPEN) * PS;
+      const int pa = i % NPEN, bf = i / NPEN;
+      const int base = pa * PS;
       C2<T> x[R];
 #pragma unroll
       for (int t = 0; t < R; ++t) x[t] = buf[base + (bf + t * NBF) * ES];
@@ -379,13 +375,12 @@ __device__ __forceinline__ void cstage(C2<T> *buf, const C2<T> *tw) {
   __syncthreads();
 }
 
-template <typename T, int N, int S, int P, int NPEN, int ES, int PS, int SGN, int NG = 1,
-          int GS = 0, int CT = kCT>
+template <typename T, int N, int S, int P, int NPEN, int ES, int PS, int SGN, int CT>
 __device__ __forceinline__ void cfft(C2<T> *buf, const C2<T> *tw) {
   if constexpr (S < CPlan<N>::ns) {
     constexpr int R = CPlan<N>::r[S];
-    cstage<T, N, R, P, NPEN, ES, PS, SGN, NG, GS, CT>(buf, tw);
-    cfft<T, N, S + 1, P * R, NPEN, ES, PS, SGN, NG, GS, CT>(buf, tw);
+    cstage<T, N, R, P, NPEN, ES, PS, SGN, CT>(buf, tw);
+    cfft<T, N, S + 1, P * R, NPEN, ES, PS, SGN, CT>(buf, tw);
   }
 }
 
@@ -506,7 +501,7 @@ __device__ __forceinline__ void cstage_io(const C2<T> *tw, Ld ld, St st, Pre pre
 // (into LDS if OUT_LDS), the stages between through the LDS accessors ldm /
 // stm.  A barrier follows every stage whose output is in LDS.
 template <typename T, int N, int S, int P, int NPEN, int SGN, bool IN_LDS, bool OUT_LDS,
-          int CT = kCT, class Ld0, class StL, class LdM, class StM, class Pre = NoPre>
+          int CT, class Ld0, class StL, class LdM, class StM, class Pre = NoPre>
 __device__ __forceinline__ void cfft_io(const C2<T> *tw, Ld0 ld0, StL stl, LdM ldm, StM stm,
                                         Pre pre = Pre()) {
   if constexpr (S < CPlan<N>::ns) {
@@ -566,7 +561,7 @@ __device__ __forceinline__ void pass_a_plane(const C2<T> *__restrict__ xb,
     buf[(e / N) * LD + e % N] = xb[idx];
   }
   __syncthreads();
-  cfft<T, N, 0, 1, N, 1, LD, +1, 1, 0, CT>(buf, tw);  // x: N pencils of stride-1 elements
+  cfft<T, N, 0, 1, N, 1, LD, +1, CT>(buf, tw);  // x: N pencils of stride-1 elements
   // y: pencil i1, element i2; the last stage writes the box plane
   auto ldm = [&](int pa, int e) { return buf[pa + e * LD]; };
   auto stm = [&](int pa, int e, C2<T> v) { buf[pa + e * LD] = v; };
@@ -588,7 +583,7 @@ __device__ __forceinline__ void pass_c_plane(const C2<T> *__restrict__ src,
   auto stm = [&](int pa, int e, C2<T> v) { buf[pa + e * LD] = v; };
   auto ldg = [&](int pa, int e) { return src[pa + e * N]; };
   cfft_io<T, N, 0, 1, N, -1, false, true, CT>(tw, ldg, stm, ldm, stm);
-  cfft<T, N, 0, 1, N, 1, LD, -1, 1, 0, CT>(buf, tw);
+  cfft<T, N, 0, 1, N, 1, LD, -1, CT>(buf, tw);
 }
 
 // Reciprocal z-planes that hold sphere points, one bit each.
