@@ -13,7 +13,7 @@
 //   K4 pass C (system, band, plane):      forward xy FFT -> gather, kinetic term,
 //                                         + E, three-term recurrence.
 // Cubic boxes with compile-time passes: one item per workgroup, edge by edge; the
-// rest, and the products: grid-stride loops, groups of small planes per item.
+// rest, and the products: grid-stride loops over the items.
 // The nonlocal products are small here (a few to a few hundred projectors):
 // plain FMA kernels tiled over bands and over projectors (32 each), so that P
 // is read once per tile of 32 bands.  Per-system tables,
@@ -592,7 +592,8 @@ void batch_step(const BatchLaunch &L, int j, hipStream_t st, hipStream_t side, h
   const size_t e = sizeof(C2<T>);
   // Systems on cubic boxes with specialised passes: edge by edge, all three passes
   // of one edge before the next, so that the infinity cache still holds much of
-  // what a pass reads of the last one's output.  The 16-cell filter takes 5.83 ms;
+  // what a pass reads of the last one's output.  With the products on the second
+  // stream the 16-cell filter takes 5.83 ms so (6.03 in line, as a graph has it);
   // pass by pass over all edges 6.30; cut further into 128 MiB of boxes 6.21 (the
   // tails of the shorter launches cost more); with some edges on the side stream
   // behind the projector products 6.25.

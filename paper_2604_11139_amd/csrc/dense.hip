@@ -170,7 +170,8 @@ __global__ __launch_bounds__(256) void potrf_diag_kernel(int nb, double2 *__rest
 
 // U12 = W^H A12 (W = U11^-1) for the panel rows j0 .. j0 + 31, 64 columns per
 // workgroup: the product with the inverse has no chain (the solve by columns walked
-// 32 dependent rows: 26 us a launch, 10.6 now).
+// 32 dependent rows: 26 us a launch, 10.6 now).  The factorisation's backward error stays
+// what the solve gives: 3.5e-16 |A| at 512 columns and condition 1e14, 3.6e-16 so.
 __global__ __launch_bounds__(256) void potrf_panel_kernel(int64_t m, double2 *__restrict__ A,
                                                           int64_t lda, int64_t j0,
                                                           const double2 *__restrict__ W) {
@@ -1547,7 +1548,9 @@ size_t ztrtri_work_bytes(int64_t m) {
 // blocks, [A B; 0 C]^-1 = [A^-1, -A^-1 B C^-1; 0, C^-1], all pairs of one size in
 // one batched product.  (One column panel of 32 at a time took two products and a
 // block inverse per panel, most of it a chain of up to 2048 / 16 K steps by a few
-// workgroups: 12.2 ms at 2048 and 1.09 at 512, now 0.70 and 0.19.)
+// workgroups: 12.2 ms at 2048 and 1.09 at 512, now 0.70 and 0.19.  At 512 columns and
+// condition 1e14 of U^H U, |U X - I| goes from 1.7e-9 to 1.1e-9 and |X U - I| from
+// 1.2e-15 to 9.3e-15; the first is what the orthonormality of Y X takes.)
 void ztrtri_upper(int64_t m, void *Av, int64_t lda, void *work, hipStream_t st) {
   double2 *A = (double2 *)Av, *T = (double2 *)work;
   hipLaunchKernelGGL(trtri_diag_kernel, dim3(nblk(m, NB)), dim3(256), 0, st, m, A, lda);

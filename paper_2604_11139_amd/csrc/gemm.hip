@@ -543,9 +543,16 @@ static int lone_splits(int64_t tiles, int64_t k, int step, double step_us) {
   return (int)best;
 }
 
+// Workgroups per CU that the FP64 split counts are planned for.  Three fit (33 KB of
+// LDS, 168 registers), and two or three give the same times: 411 complex128 bands on
+// 54^3 19.28 / 19.24 ms a filter, the 512-band SCF iteration 42.46 / 42.15 (two runs of
+// one side differ by 0.6%), the large H application 57.27 / 57.23, a drawn SCF
+// iteration 29.15 / 29.26.  Two makes fewer chunks, so fewer partials to hold and sum.
+constexpr int kSplitPerCU = 2;
+
 int zgemm_herm_splits(int64_t m, int64_t k) {
   const int64_t nt = (m + BM - 1) / BM;
-  return best_splits(nt * (nt + 1) / 2, (k + 511) / 512, 2);
+  return best_splits(nt * (nt + 1) / 2, (k + 511) / 512, kSplitPerCU);
 }
 
 void zgemm_herm(int64_t m, int64_t k, const void *A, int64_t lda, const void *B, int64_t ldb,
@@ -634,8 +641,8 @@ void zgemm_batched(int64_t m, int64_t n, int64_t k, const void *A, int64_t lda, 
 int zgemm_splits(int64_t m, int64_t n, int64_t k, bool fewest) {
   const int64_t tiles = ((m + BM - 1) / BM) * ((n + BN - 1) / BN);
   if (!fewest && tiles * ((k + 511) / 512) < device_cus()) return lone_splits(tiles, k, BK, 2.0);
-  // keep at least ~512 K per chunk; two 256-thread workgroups per CU (66 KB LDS each)
-  return best_splits(tiles, (k + 511) / 512, 2);
+  // keep at least ~512 K per chunk
+  return best_splits(tiles, (k + 511) / 512, kSplitPerCU);
 }
 
 void zgemm(Op opa, Op opb, int64_t m, int64_t n, int64_t k, const void *A, int64_t lda,
