@@ -1538,10 +1538,12 @@ void zpotrf_upper(int64_t m, void *Av, int64_t lda, int *info, void *work, hipSt
 
 size_t ztrtri_work_bytes(int64_t m) {
   // the largest level's products: pairs of L x L blocks and a ragged one
-  size_t n = 1;
-  for (int64_t L = NB; L < m; L *= 2)
-    n = std::max(n, (size_t)(m / (2 * L) + 1) * (size_t)(L * L));
-  return sizeof(double2) * n;
+  int64_t n = 1;
+  for (int64_t L = NB; L < m; L *= 2) {
+    const int64_t full = m / (2 * L), rest = m - (2 * full + 1) * L;
+    n = std::max(n, full * L * L + std::max<int64_t>(rest, 0) * L);
+  }
+  return sizeof(double2) * (size_t)n;
 }
 
 // Inverse by doubling: the diagonal blocks of 32 at once, then pairs of neighbouring
