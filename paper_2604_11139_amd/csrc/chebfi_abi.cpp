@@ -194,6 +194,8 @@ void free_tables(abi_system_s *s) {
   if (s->h_coef) (void)hipHostFree(s->h_coef);
   s->h_coef = nullptr;
   s->h_coef_n = 0;
+  if (s->h_eig) (void)hipHostFree(s->h_eig);
+  s->h_eig = nullptr;
   if (s->cap_stream) (void)hipStreamDestroy(s->cap_stream);
   s->cap_stream = nullptr;
   if (s->ev_fork) (void)hipEventDestroy(s->ev_fork);

@@ -920,13 +920,15 @@ __device__ int sturm_less_lds(int64_t m, const double *d, const double *e2, doub
 
 // (gave_up, if given, points to the flag of the tri_reg_kernel that reduced from column
 // c0 on: where it is set, d and e are no tridiagonal from there on, and the work queued
-// behind gets a harmless one, without clusters, until the host sees the flag)
+// behind gets a harmless one, without clusters, until the host sees the flag; a copy for
+// the host goes to host_flag, pinned, if given)
 __global__ __launch_bounds__(256) void tri_prep_kernel(int64_t m, double *__restrict__ d,
                                 double *__restrict__ e, double *__restrict__ e2,
                                 double *__restrict__ stats, const int *__restrict__ gave_up,
-                                int64_t c0) {
+                                int64_t c0, int *host_flag) {
   // stats[0] = Gershgorin lower, stats[1] = upper, stats[2] = |T| scale, stats[3] = pivmin
   __shared__ double slo[256], shi[256], smax[256];
+  if (gave_up && host_flag && threadIdx.x == 0) *host_flag = *gave_up;
   if (gave_up && *gave_up) {
     double gap = 1.0;  // above all of the columns reduced before
     for (int64_t i = 0; i < c0; ++i) gap = fmax(gap, fabs(d[i]) + fabs(e[i]));
@@ -1598,7 +1600,7 @@ size_t zheev_work_bytes(int64_t m) {
 }
 
 void zheev(int64_t m, void *Av, int64_t lda, double *wout, void *Zv, int64_t ldz, void *work,
-           hipStream_t st, int polls) {
+           hipStream_t st, int polls, int *host_flag) {
   CHEBFI_REQUIRE(m >= 1 && m <= kEigMaxM, ABI_ERR_ARG, "eigensolver size out of range");
   double2 *A = (double2 *)Av;
   double2 *Z = (double2 *)Zv;
@@ -1682,7 +1684,8 @@ void zheev(int64_t m, void *Av, int64_t lda, double *wout, void *Zv, int64_t ldz
   // eigenvalues and eigenvectors of the tridiagonal; below kBtMinM columns also the
   // back-transformation, one reflector at a time (A is only read)
   auto vectors = [&](const int *flag, int64_t c0) {
-    hipLaunchKernelGGL(tri_prep_kernel, dim3(1), dim3(256), 0, st, m, d, e, e2, stats, flag, c0);
+    hipLaunchKernelGGL(tri_prep_kernel, dim3(1), dim3(256), 0, st, m, d, e, e2, stats, flag, c0,
+                       host_flag);
     // d and e2 in LDS up to m = 4096 (64 KB)
     const int lds = m <= 4096 ? 1 : 0;
     const size_t lb = lds ? sizeof(double) * 2 * (size_t)m : 0;
@@ -1719,10 +1722,14 @@ void zheev(int64_t m, void *Av, int64_t lda, double *wout, void *Zv, int64_t ldz
   if (c0 < m) {
     // Did the one launch end with every word read?  Asked with the tridiagonal's work
     // queued behind it (asked at once, the host's launches of that came 20 to 115 us
-    // later) and before the blocked back-transformation overwrites A.
+    // later) and before the blocked back-transformation overwrites A.  (A copy of the
+    // flag to pageable memory is another 20 us: Rayleigh-Ritz of 24 complex128 bands
+    // 706 us with it, 686 with the pinned flag, 680 without the question.)
     int gave_up = 0;
-    CHEBFI_HIP(hipMemcpyAsync(&gave_up, dead, sizeof(int), hipMemcpyDeviceToHost, st));
+    if (!host_flag)
+      CHEBFI_HIP(hipMemcpyAsync(&gave_up, dead, sizeof(int), hipMemcpyDeviceToHost, st));
     CHEBFI_HIP(hipStreamSynchronize(st));
+    if (host_flag) gave_up = *(volatile int *)host_flag;
     if (gave_up) {
       const unsigned nb = nblk(m - c0, 32);
       hipLaunchKernelGGL(mirror_upper_kernel, dim3(nb, nb), dim3(256), 0, st, m, A, lda, c0);

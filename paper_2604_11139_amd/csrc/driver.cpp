@@ -59,6 +59,12 @@ int proj_splits(abi_system_s *s, int64_t nband, int32_t dtype) {
   return need <= g_scratch_arena->size ? n : count(true);
 }
 
+int *eig_flag(abi_system_s *s) {
+  if (!s->h_eig)
+    CHEBFI_HIP(hipHostMalloc((void **)&s->h_eig, sizeof(int), hipHostMallocDefault));
+  return s->h_eig;
+}
+
 bool proj_chains_planes(const abi_system_s *s) {
   return s->pl_proj >= 15 && s->mixed_gemm == 0 && s->nproj > 0;
 }
@@ -590,7 +596,7 @@ int rr_lowprec(abi_system_s *s, void *Y, int64_t ld, void *HPsi, int64_t ldh_in,
   s->prof.end(tok, st);
   void *ew = s->eig1.get(zheev_work_bytes(M));
   tok = s->prof.begin(PROF_EIG, 16.0 / 3.0 * (double)M * M * M, st);
-  zheev(M, Hs, M, w_dev, Z, M, ew, st, s->eig_polls);
+  zheev(M, Hs, M, w_dev, Z, M, ew, st, s->eig_polls, eig_flag(s));
   s->prof.end(tok, st);
   // T = U^-1 Z; Psi = Ye T and H Psi = (H Ye) T as split-BF16 products
   tok = s->prof.begin(PROF_ROT, 8.0 * (double)M * M * M + 16.0 * (double)npw * M * M, st);
@@ -687,7 +693,7 @@ void rr_core(abi_system_s *s, double2 *Y, int64_t ld, double2 *HPsi, int64_t ldh
   // eigen-decomposition (Hs overwritten), W = U^-1 Z
   void *ew = s->eig1.get(zheev_work_bytes(M));
   tok = s->prof.begin(PROF_EIG, 16.0 / 3.0 * (double)M * M * M, st);
-  zheev(M, Hs, M, w_dev, Z, M, ew, st, s->eig_polls);
+  zheev(M, Hs, M, w_dev, Z, M, ew, st, s->eig_polls, eig_flag(s));
   s->prof.end(tok, st);
   tok = s->prof.begin(PROF_ROT, 8.0 * (double)M * M * M + 16.0 * (double)npw * M * M, st);
   zgemm_tri(TRI_UB, M, M, G, M, Z, M, T, M, st);

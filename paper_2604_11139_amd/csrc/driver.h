@@ -52,6 +52,9 @@ inline int64_t even_batch(int64_t nband, int64_t most) {
   return (nband + n - 1) / n;
 }
 
+// The handle's pinned flag for zheev, allocated on first use.
+int *eig_flag(abi_system_s *s);
+
 // Split-BF16 projector products of the mixed form with the handle's tile
 // variants (s->pl_proj, s->pl_expand).  mixed_proj_splits: K-split count of the
 // projection of nband bands; mixed_project: part[z] = P^H X over K chunk z

@@ -264,6 +264,7 @@ struct abi_system_s {
   int mixed_gemm = 0;              // 0: split-BF16 MFMA, 1: FP32 MFMA projector products
   int generic_fft = 0;             // 1: runtime-size FFT passes also for specialised boxes
   int eig_polls = chebfi::kEigPolls;  // zheev's polls
+  int *h_eig = nullptr;               // zheev's pinned flag (eig_flag)
   int pl_proj = 0, pl_expand = 0;  // tile variants of the split-BF16 products
   // Chained planes (projection variants 15, 16, inside one filter run): the last
   // FFT pass of a step also writes the bf16 planes of its output into `planes`,

@@ -266,8 +266,10 @@ size_t ztrtri_work_bytes(int64_t m);
 // polls: how often a workgroup of the one-launch reduction looks for another's words
 // before the matrix is reduced column by column instead (0: column by column at once).
 // Waits for the stream in mid-work where the one-launch reduction runs.
+// host_flag: one pinned int of the caller's (without it a flag is copied to pageable
+// memory).
 void zheev(int64_t m, void *A, int64_t lda, double *w, void *Z, int64_t ldz, void *work,
-           hipStream_t st, int polls = kEigPolls);
+           hipStream_t st, int polls = kEigPolls, int *host_flag = nullptr);
 size_t zheev_work_bytes(int64_t m);
 
 // Threads per workgroup that one Stockham stage over npen pencils of the plan needs

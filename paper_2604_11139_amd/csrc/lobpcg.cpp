@@ -50,7 +50,7 @@ bool ortho_rr_basis(abi_system_s *s, int64_t k, int64_t mout, const double2 *Z,
   zgemm_tri(TRI_UHB, k, k, G, k, T, k, Hs, k, st);
   s->prof.end(tok, st);
   tok = s->prof.begin(PROF_EIG, 16.0 / 3.0 * (double)k * k * k, st);
-  zheev(k, Hs, k, w_dev, Y, k, s->eig1.get(zheev_work_bytes(k)), st, s->eig_polls);
+  zheev(k, Hs, k, w_dev, Y, k, s->eig1.get(zheev_work_bytes(k)), st, s->eig_polls, eig_flag(s));
   s->prof.end(tok, st);
   zgemm_tri(TRI_UB, k, mout, G, k, Y, k, C, k, st);
   return true;
