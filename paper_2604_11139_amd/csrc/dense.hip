@@ -535,10 +535,10 @@ __global__ __launch_bounds__(kTriFinT) void tri_fin_kernel(
 constexpr int kTriRegT = 512;    // threads: eight waves
 constexpr int kTriRegC = 8;      // columns per workgroup
 constexpr int kTriRegR = 4;      // most rows per thread (2048 rows)
-// fewest rows: a Rayleigh-Ritz step of 8 bands takes 486 us with the one launch and 476
-// column by column (no cooperative launch, no flag to wait for), one of 10 514 and 517,
-// one of 16 576 and 630
-constexpr int kTriRegMin = 10;
+// fewest rows: a Rayleigh-Ritz step of 4 bands takes 427 us with the one launch and 408
+// column by column (no cooperative launch, no flag to wait for), one of 7 464 and 464,
+// one of 8 475 and 486, one of 12 524 and 563
+constexpr int kTriRegMin = 7;
 constexpr unsigned long long kTriEmpty = 0x7FF4C0DEC0DEC0DEull;  // a NaN no result has
 
 __device__ __forceinline__ void tri_put(unsigned long long *p, double v) {

@@ -86,7 +86,6 @@ void *scratch_for_device(int dev);
 size_t scratch_bytes();
 
 // ---- FFT plan -------------------------------------------------------------
-constexpr int kEigPolls = 1 << 21;  // polls of the eigensolver's one-launch reduction: about 2 s
 constexpr int kMaxN = 96;       // largest box edge handled by the LDS passes (an FP64
                                 // 96 x 97 plane with its twiddles: 152 KB of LDS)
 constexpr int kMaxStages = 6;   // radix stages per 1D transform
@@ -223,6 +222,10 @@ struct BatchLaunch {
   BatchGroup groups[kBatchMaxGroups];
 };
 
+// Polls of a workgroup of the eigensolver's one-launch reduction for another's words
+// (zheev): about two seconds.
+constexpr int kEigPolls = 1 << 21;
+
 }  // namespace chebfi
 
 // ---- the handle -----------------------------------------------------------
@@ -263,7 +266,7 @@ struct abi_system_s {
   double s_min = 1.0;
   int mixed_gemm = 0;              // 0: split-BF16 MFMA, 1: FP32 MFMA projector products
   int generic_fft = 0;             // 1: runtime-size FFT passes also for specialised boxes
-  int eig_polls = chebfi::kEigPolls;  // zheev's polls
+  int eig_polls = chebfi::kEigPolls;  // polls of zheev's one-launch reduction
   int *h_eig = nullptr;               // zheev's pinned flag (eig_flag)
   int pl_proj = 0, pl_expand = 0;  // tile variants of the split-BF16 products
   // Chained planes (projection variants 15, 16, inside one filter run): the last

@@ -83,7 +83,7 @@ def test_after_a_panel():
         assert float((G - torch.eye(M, device="cuda")).abs().max()) <= 1e-11
 
 
-@pytest.mark.parametrize("m", [1, 9, 10, 11])
+@pytest.mark.parametrize("m", [1, 2, 6, 7, 8, 9])
 def test_smallest(m):
     import torch
     rng = np.random.default_rng(m)
